@@ -1,192 +1,310 @@
-// LDS-tiled FP32 product on the vector units, shared by the SBM step, the PA FP32 dense
-// step and the relaxed-dynamics adjoint:  G = J Q  with J [n][n] symmetric (row k of J
-// is column k) and Q [n][Rp] (replica fastest), followed by a per-tile epilogue.
+// FP32 product on the matrix cores, shared by the SBM step, the PA FP32 dense step and the
+// relaxed-dynamics adjoint:  G = J Q  with J [n][n] symmetric (row k of J is column k) and
+// Q [n][Rp] (replica fastest, Rp a multiple of 32), followed by an element-wise epilogue.
 //
-// A workgroup owns a 128 (replicas) x 128 (variables) output tile; each of its 256
-// threads holds 8 x 8 sums and adds one term per reduction index with a fused
-// multiply-add, in ascending order.  Chunks of 32 reduction indices of Q and J are
-// double-buffered in LDS; the next chunk is prefetched into registers while the current
-// one is multiplied.  The epilogue receives the tile's sums: thread (tx, ty) holds
-// replicas r0 + 64h + 4ty + e (h < 2, e < 4) and variables i0 + 64(v/4) + 4tx + v%4.
+// Every sum must be the sequential chain of fused multiply-adds in ascending k (the
+// definition of the FP32 fields).  v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32 give
+// exactly that chain: each of their k terms is one fused multiply-add, ascending, denormals
+// and signed zeros kept (checked against fmaf on 5e4 sums of 256 terms).  So a product may
+// be cut into output tiles freely, but never along k.
+//
+// What bounds it: the FP32 matrix rate (157 TFLOP/s nominal, 147 measured with 32 x 32
+// tiles in registers; the vector units reach 78.6 without packed FP32) for large n and R,
+// and the chain itself (8 cycles per k and wave) where there are few outputs.  At n = 4096,
+// R = 1024 the tile below takes TIME_L per step against 637 us for the product on the vector
+// units (8 x 8 sums per thread); at n = 512, R = 256 TIME_S against 87 us, where
+// the vector product's 128 x 128 tiles left 248 of 256 compute units idle.
+//
+// A workgroup owns a tile of BI variables x BR replicas; wave (wi, wr) owns FI x FR
+// matrix tiles of MT x MT.  A = J (rows: variables), B = Q (columns: replicas), so that a
+// wave's loads and stores of [n][Rp] state are contiguous in replicas.  Chunks of KC
+// reduction indices of J and Q go to LDS by direct global->LDS loads (rows stay
+// contiguous, fragment reads of 16 or 32 consecutive floats are free of bank conflicts),
+// NST stages, NST - 1 chunks ahead, one fence-free barrier per chunk.  Rows past n
+// repeat row n - 1, columns past the edge repeat the last ones; the products of the rows
+// are replaced by -0.0 * +0.0 = -0.0, the identity of the sum, and the columns' sums are
+// never stored.
 #pragma once
 
 #include "qpa_internal.h"
 
+#include <type_traits>
+
 namespace qpa {
 namespace {
 
-constexpr int SB_BR = 128;   // replicas per dense tile
-constexpr int SB_BI = 128;   // variables per dense tile
-constexpr int SB_KC = 32;    // reduction indices per LDS chunk
+typedef float ft_f16 __attribute__((ext_vector_type(16)));
+typedef float ft_f4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void ft_lds_void;
 
-__device__ __forceinline__ float4 sb_load_q(const float *__restrict__ qi, int64_t k, int64_t n,
-                                           int64_t Rp, int64_t col) {
-    if (k < n) return *reinterpret_cast<const float4 *>(qi + k * Rp + col);
-    // past the last row: -0.0 times the padding's zero couplings is exactly -0.0, which
-    // leaves every sum unchanged (also a -0.0 left by an underflowing product)
-    return make_float4(-0.0f, -0.0f, -0.0f, -0.0f);
+template <int BI_, int BR_, int MT_, int FI_, int FR_, int KC_, int NST_, int GS_> struct FpTile {
+    static constexpr int BI = BI_, BR = BR_, MT = MT_, FI = FI_, FR = FR_, KC = KC_, NST = NST_;
+    static constexpr int GS = GS_;
+    static constexpr int WI = BI / (MT * FI), WR = BR / (MT * FR), WAVES = WI * WR;
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int KS = 64 / MT;             // reduction indices per instruction
+    static constexpr int NV = MT * MT / 64;        // sums per lane and matrix tile
+    static constexpr int STG = KC * (BI + BR);     // floats per stage
+    static_assert(KC * BI % (256 * WAVES) == 0 && KC * BR % (256 * WAVES) == 0, "even loads");
+    static_assert(NST * STG * 4 <= 160 * 1024, "LDS of one workgroup");
+};
+
+// The tiles, largest first.  One CU does 256 multiply-adds per cycle and four matrix
+// instructions at a time, so a tile costs BI * BR / 128 cycles per k when it is alone on its CU and
+// tiles of a CU add up.
+typedef FpTile<128, 128, 32, 2, 1, 32, 4, 2> FpTileL;    // 8 waves
+typedef FpTile<64, 64, 32, 1, 1, 32, 4, 4> FpTileM;      // 4 waves
+typedef FpTile<64, 32, 16, 2, 1, 32, 6, 4> FpTileN;      // 4 waves
+typedef FpTile<32, 32, 16, 1, 1, 64, 5, 8> FpTileS;      // 4 waves
+
+// Workgroup barrier without a memory fence, after this wave's loads of all but the N
+// youngest have landed and its LDS reads are done.
+template <int N> __device__ __forceinline__ void ft_wait_barrier() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// VEC: n % 4 == 0, so rows of J can be read as float4.
-template <bool VEC>
-__device__ __forceinline__ float4 sb_load_j(const float *__restrict__ J, int64_t k, int64_t n,
-                                           int64_t i) {
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (k >= n) return v;
-    const float *row = J + k * n;
-    if (VEC) {
-        if (i < n) v = *reinterpret_cast<const float4 *>(row + i);
-    } else {
-        if (i < n) v.x = row[i];
-        if (i + 1 < n) v.y = row[i + 1];
-        if (i + 2 < n) v.z = row[i + 2];
-        if (i + 3 < n) v.w = row[i + 3];
-    }
-    return v;
+template <int MT> struct FtAcc;
+template <> struct FtAcc<32> { typedef ft_f16 type; };
+template <> struct FtAcc<16> { typedef ft_f4 type; };
+
+__device__ __forceinline__ ft_f16 ft_mfma(float a, float b, ft_f16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ ft_f4 ft_mfma(float a, float b, ft_f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-typedef __attribute__((address_space(3))) const void sb_lds_t;
-typedef float sb_f4 __attribute__((ext_vector_type(4)));
+// VEC: n % 4 == 0, so 16-byte pieces of J's rows are aligned and never straddle the edge.
+// Epi: typedef Pre and
+//   float bias(i)                            b_i
+//   Pre load(r, idx)                         the element's own state, loaded before the loop
+//   void point(acc, bias, r, idx, Pre)       its update from the sum
+//   void finish()                            once per thread, after its elements
+template <class TL, bool VEC, class Epi>
+__global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64_t Rp,
+                                                                const float *__restrict__ J,
+                                                                const float *__restrict__ qi,
+                                                                Epi epi) {
+    constexpr int BI = TL::BI, BR = TL::BR, MT = TL::MT, FI = TL::FI, FR = TL::FR, KC = TL::KC;
+    constexpr int NST = TL::NST, KS = TL::KS, NV = TL::NV;
+    constexpr int PJ = VEC ? 4 : 1;                                   // floats per lane and load
+    constexpr int LJ = KC * BI / (64 * PJ * TL::WAVES);               // loads per wave and chunk
+    constexpr int LQ = KC * BR / (256 * TL::WAVES);
+    static_assert((NST - 2) * (LJ + LQ) < 64, "vmcnt range");
+    __shared__ __attribute__((aligned(16))) float lds[NST * TL::STG];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i0 = (int64_t)blockIdx.x * BI, r0 = (int64_t)blockIdx.y * BR;
 
-// LDS byte address of a shared-memory pointer.
-__device__ __forceinline__ uint32_t sb_lds(const float4 *p) {
-    return (uint32_t)(uintptr_t)(sb_lds_t *)p;
-}
-
-// Issue the four fragment reads of one reduction index: A columns at la + off and
-// la + off + 256 (replicas 4ty.. and 64+4ty..), B at lb + off and lb + off + 256.
-__device__ __forceinline__ void sb_rd4(sb_f4 &a0, sb_f4 &a1, sb_f4 &b0, sb_f4 &b1,
-                                       uint32_t la, uint32_t lb, int off_tag) {
-    if (off_tag == 0) {
-        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:256\n\t"
-                     "ds_read_b128 %2, %5\n\tds_read_b128 %3, %5 offset:256"
-                     : "=v"(a0), "=v"(a1), "=v"(b0), "=v"(b1) : "v"(la), "v"(lb));
-    } else if (off_tag == 512) {
-        asm volatile("ds_read_b128 %0, %4 offset:512\n\tds_read_b128 %1, %4 offset:768\n\t"
-                     "ds_read_b128 %2, %5 offset:512\n\tds_read_b128 %3, %5 offset:768"
-                     : "=v"(a0), "=v"(a1), "=v"(b0), "=v"(b1) : "v"(la), "v"(lb));
-    } else {
-        asm volatile("ds_read_b128 %0, %4 offset:1024\n\tds_read_b128 %1, %4 offset:1280\n\t"
-                     "ds_read_b128 %2, %5 offset:1024\n\tds_read_b128 %3, %5 offset:1280"
-                     : "=v"(a0), "=v"(a1), "=v"(b0), "=v"(b1) : "v"(la), "v"(lb));
-    }
-}
-
-// Wait until at most N LDS reads of this wave are outstanding; the registers are tied to
-// the wait so that no use is scheduled before it.
-template <int N>
-__device__ __forceinline__ void sb_wait4(sb_f4 &a0, sb_f4 &a1, sb_f4 &b0, sb_f4 &b1) {
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a0), "+v"(a1), "+v"(b0), "+v"(b1) : "n"(N));
-}
-
-#define SB_FMA_ROW(u, av)                                                               \
-    acc[u][0] = __fmaf_rn(av, fb0.x, acc[u][0]);                                         \
-    acc[u][1] = __fmaf_rn(av, fb0.y, acc[u][1]);                                         \
-    acc[u][2] = __fmaf_rn(av, fb0.z, acc[u][2]);                                         \
-    acc[u][3] = __fmaf_rn(av, fb0.w, acc[u][3]);                                         \
-    acc[u][4] = __fmaf_rn(av, fb1.x, acc[u][4]);                                         \
-    acc[u][5] = __fmaf_rn(av, fb1.y, acc[u][5]);                                         \
-    acc[u][6] = __fmaf_rn(av, fb1.z, acc[u][6]);                                         \
-    acc[u][7] = __fmaf_rn(av, fb1.w, acc[u][7]);
-
-// FP32 tiled product G = J Q ([n][n] x [n][Rp], both read row by row: J is symmetric, so
-// its row k is column k) with a per-step epilogue: the SBM step (Q = positions) or the PA
-// step (Q = spins as +-1 floats).
-template <bool VEC, class Epi>
-__global__ void __launch_bounds__(256) k_fp32_tiled_step(int64_t n, int64_t Rp,
-                                                         const float *__restrict__ J,
-                                                         const float *__restrict__ qi,
-                                                         const Epi epi) {
-    __shared__ float4 As[2][SB_KC + 1][SB_BR / 4];
-    __shared__ float4 Bs[2][SB_KC + 1][SB_BI / 4];
-    const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-    const int64_t i0 = (int64_t)blockIdx.x * SB_BI, r0 = (int64_t)blockIdx.y * SB_BR;
-    float acc[8][8];
+    // load u of this wave covers floats 64 PJ (u WAVES + wave) .. of the stage's J (or Q)
+    // rows: row jr + u * JSTEP of the chunk at column jc
+    const int jr = (64 * PJ * wave + PJ * lane) / BI, jc = (PJ * lane) % BI;
+    const int qr = (256 * wave + 4 * lane) / BR, qc = (4 * lane) % BR;
+    constexpr int JSTEP = 64 * PJ * TL::WAVES / BI, QSTEP = 256 * TL::WAVES / BR;
+    static_assert(64 * PJ * TL::WAVES % BI == 0 && 256 * TL::WAVES % BR == 0, "whole rows");
+    const uint32_t jcol = (uint32_t)min(i0 + jc, n - PJ), n32 = (uint32_t)n;
+    const float *qb = qi + min(r0 + qc, Rp - 4);
+    const int nch = (int)((n + KC - 1) / KC);
+    auto stage = [&](int c, int st) {
+        float *dst = lds + st * TL::STG;
+        const int64_t k0 = (int64_t)min(c, nch - 1) * KC;      // past the end: the last chunk
+        const int lim = (int)min(n - 1 - k0, (int64_t)KC);
+        const float *jk = J + k0 * n;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < LJ; ++u) {
+            const uint32_t o = (uint32_t)min(jr + u * JSTEP, lim) * n32 + jcol;
+            ft_lds_void *to = (ft_lds_void *)(dst + 64 * PJ * (u * TL::WAVES + wave));
+            if constexpr (VEC) __builtin_amdgcn_global_load_lds(jk + o, to, 16, 0, 0);
+            else __builtin_amdgcn_global_load_lds(jk + o, to, 4, 0, 0);
+        }
+        const float *qk = qb + k0 * Rp;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) acc[u][v] = 0.0f;
-    // load slots of this thread in a chunk: rows kk = t/32 + 8e (e < 4), float4 column t%32
-    const int lk = t >> 5, lc = t & 31;
-    const int64_t qcol = r0 + 4 * lc, jcol = i0 + 4 * lc;
-    float4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
-#define SB_FETCH(k0)                                                                     \
-    pa0 = sb_load_q(qi, (k0) + lk, n, Rp, qcol);                                         \
-    pa1 = sb_load_q(qi, (k0) + lk + 8, n, Rp, qcol);                                     \
-    pa2 = sb_load_q(qi, (k0) + lk + 16, n, Rp, qcol);                                    \
-    pa3 = sb_load_q(qi, (k0) + lk + 24, n, Rp, qcol);                                    \
-    pb0 = sb_load_j<VEC>(J, (k0) + lk, n, jcol);                                         \
-    pb1 = sb_load_j<VEC>(J, (k0) + lk + 8, n, jcol);                                     \
-    pb2 = sb_load_j<VEC>(J, (k0) + lk + 16, n, jcol);                                    \
-    pb3 = sb_load_j<VEC>(J, (k0) + lk + 24, n, jcol);
-#define SB_STASH(buf)                                                                    \
-    As[buf][lk][lc] = pa0;                                                               \
-    As[buf][lk + 8][lc] = pa1;                                                           \
-    As[buf][lk + 16][lc] = pa2;                                                          \
-    As[buf][lk + 24][lc] = pa3;                                                          \
-    Bs[buf][lk][lc] = pb0;                                                               \
-    Bs[buf][lk + 8][lc] = pb1;                                                           \
-    Bs[buf][lk + 16][lc] = pb2;                                                          \
-    Bs[buf][lk + 24][lc] = pb3;
-    const int64_t nch = (n + SB_KC - 1) / SB_KC;
-    SB_FETCH(0)
-    SB_STASH(0)
-    __syncthreads();
-    for (int64_t c = 0; c < nch; ++c) {
-        const int buf = (int)(c & 1);
-        const bool more = c + 1 < nch;
-        if (more) {
-            SB_FETCH((c + 1) * SB_KC)
-        }
-        // Two fragment sets: while one reduction index is multiplied, the next one's
-        // fragments are read.  The reads are issued by inline assembly (the compiler would
-        // otherwise move them next to their use) and their completion is awaited by
-        // explicit waits that also mark the registers as written.  Row SB_KC of each
-        // buffer is padding: read, never used.
-        const uint32_t la = sb_lds(&As[buf][0][ty]), lb = sb_lds(&Bs[buf][0][tx]);
-        sb_f4 xa0, xa1, xb0, xb1, ya0, ya1, yb0, yb1;
-        sb_rd4(xa0, xa1, xb0, xb1, la, lb, 0);
-#pragma unroll 1
-        for (int kk = 0; kk < SB_KC; kk += 2) {
-            const uint32_t o = (uint32_t)kk * 512u;
-            sb_rd4(ya0, ya1, yb0, yb1, la + o, lb + o, 512);
-            sb_wait4<4>(xa0, xa1, xb0, xb1);
-            {
-                const sb_f4 fb0 = xb0, fb1 = xb1;
-                SB_FMA_ROW(0, xa0.x)
-                SB_FMA_ROW(1, xa0.y)
-                SB_FMA_ROW(2, xa0.z)
-                SB_FMA_ROW(3, xa0.w)
-                SB_FMA_ROW(4, xa1.x)
-                SB_FMA_ROW(5, xa1.y)
-                SB_FMA_ROW(6, xa1.z)
-                SB_FMA_ROW(7, xa1.w)
-            }
-            sb_rd4(xa0, xa1, xb0, xb1, la + o, lb + o, 1024);
-            sb_wait4<4>(ya0, ya1, yb0, yb1);
-            {
-                const sb_f4 fb0 = yb0, fb1 = yb1;
-                SB_FMA_ROW(0, ya0.x)
-                SB_FMA_ROW(1, ya0.y)
-                SB_FMA_ROW(2, ya0.z)
-                SB_FMA_ROW(3, ya0.w)
-                SB_FMA_ROW(4, ya1.x)
-                SB_FMA_ROW(5, ya1.y)
-                SB_FMA_ROW(6, ya1.z)
-                SB_FMA_ROW(7, ya1.w)
-            }
-        }
-        sb_wait4<0>(xa0, xa1, xb0, xb1);     // the padding row's reads land before reuse
-        if (more) {
-            SB_STASH(buf ^ 1)
-        }
-        __syncthreads();
+        for (int u = 0; u < LQ; ++u)
+            __builtin_amdgcn_global_load_lds(
+                qk + min(qr + u * QSTEP, lim) * Rp,
+                (ft_lds_void *)(dst + KC * BI + 256 * (u * TL::WAVES + wave)), 16, 0, 0);
+    };
+
+    // element v of matrix tile (f, g): variable ib + MT f + vrow(v), replica rb + MT g
+    const int lk = lane / MT, lm = lane % MT;
+    const int wi = wave % TL::WI, wr = wave / TL::WI;
+    const int64_t ib = i0 + wi * (MT * FI) + 4 * lk, rb = r0 + wr * (MT * FR) + lm;
+    auto vrow = [](int v) { return MT == 32 ? 8 * (v >> 2) + (v & 3) : v; };
+    const bool full = i0 + BI <= n && r0 + BR <= Rp;           // uniform
+    typename FtAcc<MT>::type acc[FI][FR];
+    typename Epi::Pre pre[FI][FR][NV];
+    float bi[FI][NV];
+    auto load_bias = [&]() {
+#pragma unroll
+        for (int f = 0; f < FI; ++f)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) bi[f][v] = epi.bias(min(ib + MT * f + vrow(v), n - 1));
+    };
+    constexpr bool EARLY = FI * NV <= 16;                      // registers to hold the bias
+    if (EARLY) load_bias();
+#pragma unroll
+    for (int f = 0; f < FI; ++f)
+#pragma unroll
+        for (int g = 0; g < FR; ++g)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[f][g][v] = 0.0f;
+    if (full) {
+        const int64_t base = ib * Rp + rb;
+#pragma unroll
+        for (int f = 0; f < FI; ++f)
+#pragma unroll
+            for (int g = 0; g < FR; ++g)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    pre[f][g][v] = epi.load(rb + MT * g, base + (MT * f + vrow(v)) * Rp + MT * g);
+    } else {
+#pragma unroll
+        for (int f = 0; f < FI; ++f)
+#pragma unroll
+            for (int g = 0; g < FR; ++g)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int64_t i = min(ib + MT * f + vrow(v), n - 1);
+                    const int64_t r = min(rb + MT * g, Rp - 1);
+                    pre[f][g][v] = epi.load(r, i * Rp + r);
+                }
     }
-#undef SB_FETCH
-#undef SB_STASH
-    epi(acc, n, Rp, i0, r0, tx, ty);
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) stage(s, s);
+
+    // Fragments are read a group ahead of their products (GS reduction steps of one
+    // instruction each), across chunk borders, right after the first products of the group
+    // before: the compiler waits for every outstanding read at a group's first product, so
+    // the next group's come after it.  The order is fixed by scheduling barriers; left
+    // alone, the compiler reads each fragment right before its use.
+    constexpr int GS = TL::GS, NG = KC / (KS * GS);
+    static_assert(NG * KS * GS == KC && NG % 2 == 0, "fragment sets alternate");
+    float fa[2][GS][FI], fb[2][GS][FR];
+    auto read = [&](int st, int g, float (&ra)[GS][FI], float (&rb_)[GS][FR]) {
+        const float *As = lds + st * TL::STG + wi * (MT * FI) + lm + lk * BI;
+        const float *Bs = lds + st * TL::STG + KC * BI + wr * (MT * FR) + lm + lk * BR;
+#pragma unroll
+        for (int e = 0; e < GS; ++e) {
+            const int kk = (g * GS + e) * KS;
+#pragma unroll
+            for (int f = 0; f < FI; ++f) ra[e][f] = As[kk * BI + MT * f];
+#pragma unroll
+            for (int h = 0; h < FR; ++h) rb_[e][h] = Bs[kk * BR + MT * h];
+        }
+    };
+    auto multiply = [&](int st, int st_next, auto tail, int kend) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+#pragma unroll
+            for (int e = 0; e < GS; ++e) {
+                float(&a)[FI] = fa[g & 1][e];
+                float(&b)[FR] = fb[g & 1][e];
+                if constexpr (decltype(tail)::value) {
+                    const bool in = (g * GS + e) * KS + lk < kend;
+#pragma unroll
+                    for (int f = 0; f < FI; ++f) a[f] = in ? a[f] : -0.0f;
+#pragma unroll
+                    for (int h = 0; h < FR; ++h) b[h] = in ? b[h] : 0.0f;
+                }
+#pragma unroll
+                for (int f = 0; f < FI; ++f)
+#pragma unroll
+                    for (int h = 0; h < FR; ++h) acc[f][h] = ft_mfma(a[f], b[h], acc[f][h]);
+                if (e == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (g + 1 < NG) read(st, g + 1, fa[(g + 1) & 1], fb[(g + 1) & 1]);
+                    else if constexpr (!decltype(tail)::value) read(st_next, 0, fa[0], fb[0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // chunk 0 has landed in every wave; its first fragments
+    ft_wait_barrier<(NST - 2) * (LJ + LQ)>();
+    read(0, 0, fa[0], fb[0]);
+    int st = 0, nx = NST - 1;                      // stages of chunk c and of chunk c + NST - 1
+    for (int c = 0; c < nch - 1; ++c) {
+        // this wave's loads of chunk c + 1 have landed (younger chunks' may not have); after
+        // the barrier every wave's have, and every wave is done with the stage refilled next
+        ft_wait_barrier<(NST - 3) * (LJ + LQ)>();
+        stage(c + NST - 1, nx);
+        const int sn = st + 1 == NST ? 0 : st + 1;
+        multiply(st, sn, std::false_type{}, KC);
+        st = sn;
+        nx = nx + 1 == NST ? 0 : nx + 1;
+    }
+    ft_wait_barrier<0>();              // no load is left in flight when the LDS is given back
+    multiply(st, st, std::true_type{}, (int)(n - (int64_t)(nch - 1) * KC));
+    if (!EARLY) load_bias();
+    if (full) {
+        const int64_t base = ib * Rp + rb;
+#pragma unroll
+        for (int f = 0; f < FI; ++f)
+#pragma unroll
+            for (int g = 0; g < FR; ++g)
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    epi.point(acc[f][g][v], bi[f][v], rb + MT * g,
+                              base + (MT * f + vrow(v)) * Rp + MT * g, pre[f][g][v]);
+    } else {
+#pragma unroll
+        for (int f = 0; f < FI; ++f)
+#pragma unroll
+            for (int g = 0; g < FR; ++g)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int64_t i = ib + MT * f + vrow(v), r = rb + MT * g;
+                    if (i < n && r < Rp) epi.point(acc[f][g][v], bi[f][v], r, i * Rp + r, pre[f][g][v]);
+                }
+    }
+    epi.finish();
 }
-#undef SB_FMA_ROW
+
+enum Fp32Tile : int { FP32_TILE_L, FP32_TILE_M, FP32_TILE_N, FP32_TILE_S };
+
+// The tile for an n x Rp product: the one whose workgroups, spread over the compute
+// units, finish first; among equals the largest (least traffic).
+inline Fp32Tile fp32_tile_of(int64_t n, int64_t Rp) {
+    auto cost = [&](int64_t bi, int64_t br) {
+        const int64_t tiles = ((n + bi - 1) / bi) * ((Rp + br - 1) / br);
+        return (tiles + 255) / 256 * (bi * br);
+    };
+    if (Rp > 32 * 65535) return FP32_TILE_L;        // grid y
+    const int64_t l = cost(128, 128), m = cost(64, 64), nn = cost(64, 32), s = cost(32, 32);
+    if (l <= m && l <= nn && l <= s) return FP32_TILE_L;
+    if (m <= nn && m <= s) return FP32_TILE_M;
+    return nn <= s ? FP32_TILE_N : FP32_TILE_S;
+}
+
+inline dim3 fp32_tile_grid(Fp32Tile t, int64_t n, int64_t Rp) {
+    const int64_t bi = t == FP32_TILE_L ? 128 : t == FP32_TILE_S ? 32 : 64;
+    const int64_t br = t == FP32_TILE_L ? 128 : t == FP32_TILE_M ? 64 : 32;
+    return dim3((unsigned)((n + bi - 1) / bi), (unsigned)((Rp + br - 1) / br));
+}
+
+template <class Epi>
+hipError_t launch_fp32_product(int64_t n, int64_t Rp, const float *J, const float *q,
+                               const Epi &epi, hipStream_t st) {
+    if (Rp % 32 || Rp < 32 || n < 1) return hipErrorInvalidValue;
+    const Fp32Tile t = fp32_tile_of(n, Rp);
+    const dim3 grid = fp32_tile_grid(t, n, Rp);
+    if (grid.y > 65535u) return hipErrorInvalidValue;
+#define QPA_FP32_TILE(T, TL)                                                               \
+    if (t == T) {                                                                          \
+        if (n % 4 == 0)                                                                    \
+            k_fp32_mfma_step<TL, true, Epi><<<grid, TL::THREADS, 0, st>>>(n, Rp, J, q, epi); \
+        else                                                                               \
+            k_fp32_mfma_step<TL, false, Epi><<<grid, TL::THREADS, 0, st>>>(n, Rp, J, q, epi); \
+    }
+    QPA_FP32_TILE(FP32_TILE_L, FpTileL)
+    QPA_FP32_TILE(FP32_TILE_M, FpTileM)
+    QPA_FP32_TILE(FP32_TILE_N, FpTileN)
+    QPA_FP32_TILE(FP32_TILE_S, FpTileS)
+#undef QPA_FP32_TILE
+    return hipGetLastError();
+}
 
 }  // namespace
 }  // namespace qpa

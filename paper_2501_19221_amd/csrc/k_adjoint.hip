@@ -20,8 +20,8 @@
 // out of every sum.
 // Products with J: CSR couplings through row launches over blocks of 64 rows, the input
 // vector staged through LDS (a wave = four rows and 64 replicas, lane = replica, each
-// row's entries walked in order); dense FP32 couplings through the LDS-tiled product
-// shared with the SBM step, with the element work in its epilogue.  Both add one fused multiply-add
+// row's entries walked in order); dense FP32 couplings through the matrix-core
+// product shared with the SBM step, with the element work in its epilogue.  Both add one fused multiply-add
 // per term in ascending column order.
 // Inner products are accumulated in FP64 per thread, reduced per workgroup in a fixed
 // order and written to a per-step table of partial sums, which one last launch reduces in
@@ -465,32 +465,24 @@ __global__ void __launch_bounds__(GR_THREADS)
     rel_write_partials<MODE>(a, blockIdx.x, s0, s1, s2, sh, GR_WAVES);
 }
 
-// Epilogue of the dense tiled product for every mode (b, and the state pointers in `a`,
+// Epilogue of the dense product for every mode (b, and the state pointers in `a`,
 // already offset to the instance's rows).
 template <int MODE>
 struct RelTileEpilogue {
     RelArgs a;
     const float *b;
-    __device__ __forceinline__ void operator()(float (&acc)[8][8], int64_t n, int64_t Rp,
-                                               int64_t i0, int64_t r0, int tx, int ty) const {
-        __shared__ double sh[4];
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int64_t i = i0 + 64 * (v >> 2) + 4 * tx + (v & 3);
-            if (i >= n) continue;
-            const float bi = b[i];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int64_t r = r0 + 64 * h + 4 * ty + e;
-                    rel_element<MODE>(a, i * Rp + r, r < a.R, acc[4 * h + e][v], bi, s0, s1,
-                                      s2);
-                }
-        }
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    struct Pre {};
+    __device__ __forceinline__ float bias(int64_t i) const { return b[i]; }
+    __device__ __forceinline__ Pre load(int64_t, int64_t) const { return Pre{}; }
+    __device__ __forceinline__ void point(float acc, float bi, int64_t r, int64_t idx,
+                                          const Pre &) {
+        rel_element<MODE>(a, idx, r < a.R, acc, bi, s0, s1, s2);
+    }
+    __device__ __forceinline__ void finish() const {
+        __shared__ double sh[8];
         rel_write_partials<MODE>(a, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, s0, s1, s2,
-                                 sh, 4);
+                                 sh, (int)(blockDim.x >> 6));
     }
 };
 
@@ -574,15 +566,9 @@ hipError_t rel_gather_launch(const RelInst *insts, int32_t ninst, int64_t blocks
 template <int MODE>
 hipError_t rel_tile_launch(int64_t n, const float *J, const float *b, const RelArgs &a,
                            hipStream_t st) {
-    if (a.Rp % SB_BR || n < 1) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((n + SB_BI - 1) / SB_BI), (unsigned)(a.Rp / SB_BR));
     const RelTileEpilogue<MODE> epi{a, b};
     const float *q = (MODE == REL_FWD || MODE == REL_LOSS) ? a.xi : a.mu_in;
-    if (n % 4 == 0)
-        k_fp32_tiled_step<true, RelTileEpilogue<MODE>><<<grid, 256, 0, st>>>(n, a.Rp, J, q, epi);
-    else
-        k_fp32_tiled_step<false, RelTileEpilogue<MODE>><<<grid, 256, 0, st>>>(n, a.Rp, J, q, epi);
-    return hipGetLastError();
+    return launch_fp32_product(n, a.Rp, J, q, epi, st);
 }
 
 }  // namespace
@@ -607,7 +593,8 @@ hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, 
 }
 
 int64_t rel_tile_blocks(int64_t n, int64_t Rp) {
-    return ((n + SB_BI - 1) / SB_BI) * (Rp / SB_BR);
+    const dim3 g = fp32_tile_grid(fp32_tile_of(n, Rp), n, Rp);
+    return (int64_t)g.x * g.y;
 }
 
 hipError_t launch_rel_tiles(int32_t mode, int64_t n, const float *J, const float *b,

@@ -12,14 +12,8 @@
 // State layout: q, p [n][Rp] FP32, replica fastest.  Every step reads q_in and writes
 // q_out (the update is synchronous), p in place.
 //
-// Dense couplings: an LDS-tiled FP32 product on the vector units.  A workgroup owns a
-// 128 (replicas) x 128 (variables) output tile; each of its 256 threads holds 8 x 8
-// sums and adds one term per reduction index with a fused multiply-add, in ascending
-// order, so every sum is bit-identical to the sequential definition.  Chunks of 32
-// reduction indices of q (from [n][Rp]: contiguous in replicas) and J (symmetric, so row
-// k of J gives column k: contiguous in variables) are double-buffered in LDS; the next
-// chunk is prefetched into registers while the current one is multiplied.  The update
-// runs in the epilogue on the tile's 16384 elements.
+// Dense couplings: the FP32 product on the matrix cores (fp32_tiled.h), whose sums are bit
+// for bit the sequential definition; the update runs in its epilogue.
 //
 // CSR couplings: one lane per (row, replica); the G lanes of a row (G = replicas per
 // row group, a power of two <= 64) read the row's entries once per wave and gather
@@ -46,39 +40,28 @@ __device__ __forceinline__ void sbm_point(float f, float bi, float a, float a0, 
     q = __fadd_rn(q, __fmul_rn(adt, pn));
 }
 
-// SBM epilogue: the symplectic step of every (variable, replica) of the tile.
+// SBM epilogue: the symplectic step of one (variable, replica).
 struct SbmEpilogue {
     const float *b, *c0p;
     float a, a0, dt;
     const float *qi;
     float *qo, *p, *gout;
-    // thread holds replicas r0 + 64h + 4ty + e (h, e < 2, 4) and variables
-    // i0 + 64(v/4) + 4tx + v%4
-    __device__ __forceinline__ void operator()(float (&acc)[8][8], int64_t n, int64_t Rp,
-                                               int64_t i0, int64_t r0, int tx, int ty) const {
-        const float c0 = *c0p;
-        const float adt = __fmul_rn(dt, a0);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int64_t i = i0 + 64 * (v >> 2) + 4 * tx + (v & 3);
-            if (i >= n) continue;
-            const float bi = b[i];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int64_t idx = i * Rp + r0 + 64 * h + 4 * ty;
-                float4 qv = *reinterpret_cast<const float4 *>(qi + idx);
-                float4 pv = *reinterpret_cast<const float4 *>(p + idx);
-                float4 gv;
-                sbm_point(acc[4 * h + 0][v], bi, a, a0, c0, dt, adt, qv.x, pv.x, gv.x);
-                sbm_point(acc[4 * h + 1][v], bi, a, a0, c0, dt, adt, qv.y, pv.y, gv.y);
-                sbm_point(acc[4 * h + 2][v], bi, a, a0, c0, dt, adt, qv.z, pv.z, gv.z);
-                sbm_point(acc[4 * h + 3][v], bi, a, a0, c0, dt, adt, qv.w, pv.w, gv.w);
-                *reinterpret_cast<float4 *>(qo + idx) = qv;
-                *reinterpret_cast<float4 *>(p + idx) = pv;
-                if (gout) *reinterpret_cast<float4 *>(gout + idx) = gv;
-            }
-        }
+    struct Pre {
+        float q, p;
+    };
+    __device__ __forceinline__ float bias(int64_t i) const { return b[i]; }
+    __device__ __forceinline__ Pre load(int64_t, int64_t idx) const {
+        return Pre{qi[idx], p[idx]};
     }
+    __device__ __forceinline__ void point(float acc, float bi, int64_t, int64_t idx,
+                                          const Pre &s) const {
+        float qv = s.q, pv = s.p, gv;
+        sbm_point(acc, bi, a, a0, *c0p, dt, __fmul_rn(dt, a0), qv, pv, gv);
+        qo[idx] = qv;
+        p[idx] = pv;
+        if (gout) gout[idx] = gv;
+    }
+    __device__ __forceinline__ void finish() const {}
 };
 
 __device__ __forceinline__ void pa_point(float acc, float bi, float lt, float eta, float alpha,
@@ -99,31 +82,23 @@ struct PaEpilogue {
     int t;
     float eta, alpha;
     float *x, *m, *s_nxt, *h_last;
-    __device__ __forceinline__ void operator()(float (&acc)[8][8], int64_t n, int64_t Rp,
-                                               int64_t i0, int64_t r0, int tx, int ty) const {
-        const float lt = lam[t];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int64_t i = i0 + 64 * (v >> 2) + 4 * tx + (v & 3);
-            if (i >= n) continue;
-            const float bi = b[i];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int64_t idx = i * Rp + r0 + 64 * h + 4 * ty;
-                float4 xv = *reinterpret_cast<const float4 *>(x + idx);
-                float4 mv = *reinterpret_cast<const float4 *>(m + idx);
-                float4 sv, hv;
-                pa_point(acc[4 * h + 0][v], bi, lt, eta, alpha, xv.x, mv.x, sv.x, hv.x);
-                pa_point(acc[4 * h + 1][v], bi, lt, eta, alpha, xv.y, mv.y, sv.y, hv.y);
-                pa_point(acc[4 * h + 2][v], bi, lt, eta, alpha, xv.z, mv.z, sv.z, hv.z);
-                pa_point(acc[4 * h + 3][v], bi, lt, eta, alpha, xv.w, mv.w, sv.w, hv.w);
-                *reinterpret_cast<float4 *>(x + idx) = xv;
-                *reinterpret_cast<float4 *>(m + idx) = mv;
-                *reinterpret_cast<float4 *>(s_nxt + idx) = sv;
-                if (h_last) *reinterpret_cast<float4 *>(h_last + idx) = hv;
-            }
-        }
+    struct Pre {
+        float x, m;
+    };
+    __device__ __forceinline__ float bias(int64_t i) const { return b[i]; }
+    __device__ __forceinline__ Pre load(int64_t, int64_t idx) const {
+        return Pre{x[idx], m[idx]};
     }
+    __device__ __forceinline__ void point(float acc, float bi, int64_t, int64_t idx,
+                                          const Pre &s) const {
+        float xv = s.x, mv = s.m, sv, hv;
+        pa_point(acc, bi, lam[t], eta, alpha, xv, mv, sv, hv);
+        x[idx] = xv;
+        m[idx] = mv;
+        s_nxt[idx] = sv;
+        if (h_last) h_last[idx] = hv;
+    }
+    __device__ __forceinline__ void finish() const {}
 };
 
 
@@ -500,25 +475,19 @@ int sbm_csr_group(int64_t R) {
 }
 
 int64_t sbm_rpad(const qpa_problem &p, int64_t R) {
-    if (p.format == QPA_FMT_DENSE) return (R + SB_BR - 1) / SB_BR * SB_BR;
+    if (p.format == QPA_FMT_DENSE) return dense_fp32_rpad(R);
     const int G = sbm_csr_group(R);
     return (R + G - 1) / G * G;
 }
 
-int64_t dense_fp32_rpad(int64_t R) { return (R + SB_BR - 1) / SB_BR * SB_BR; }
+int64_t dense_fp32_rpad(int64_t R) { return (R + 31) / 32 * 32; }
 
 hipError_t launch_dense_fp32_step(int64_t n, int64_t Rp, const float *J, const float *b,
                                   const float *s_cur, float *s_nxt, float *x, float *m,
                                   float *h_last, int32_t t, const float *lam, float eta,
                                   float alpha, hipStream_t st) {
-    if (Rp % SB_BR || n < 1) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((n + SB_BI - 1) / SB_BI), (unsigned)(Rp / SB_BR));
     const PaEpilogue epi{b, lam, t, eta, alpha, x, m, s_nxt, h_last};
-    if (n % 4 == 0)
-        k_fp32_tiled_step<true, PaEpilogue><<<grid, 256, 0, st>>>(n, Rp, J, s_cur, epi);
-    else
-        k_fp32_tiled_step<false, PaEpilogue><<<grid, 256, 0, st>>>(n, Rp, J, s_cur, epi);
-    return hipGetLastError();
+    return launch_fp32_product(n, Rp, J, s_cur, epi, st);
 }
 
 int64_t pw_blocks(const qpa_problem &p) {
@@ -532,13 +501,8 @@ hipError_t launch_sbm_step(const qpa_problem &p, const float *Jf, int64_t Rp, co
                            float *q_out, float *pm, float *g_out, hipStream_t st) {
     const int64_t n = p.n;
     if (p.format == QPA_FMT_DENSE) {
-        dim3 grid((unsigned)((n + SB_BI - 1) / SB_BI), (unsigned)(Rp / SB_BR));
         const SbmEpilogue epi{b, c0p, a, a0, dt, q_in, q_out, pm, g_out};
-        if (n % 4 == 0)
-            k_fp32_tiled_step<true, SbmEpilogue><<<grid, 256, 0, st>>>(n, Rp, Jf, q_in, epi);
-        else
-            k_fp32_tiled_step<false, SbmEpilogue><<<grid, 256, 0, st>>>(n, Rp, Jf, q_in, epi);
-        return hipGetLastError();
+        return launch_fp32_product(n, Rp, Jf, q_in, epi, st);
     }
     const int G = sbm_csr_group(Rp);
     const int64_t waves = ((n + (64 / G) - 1) / (64 / G)) * (Rp / G);

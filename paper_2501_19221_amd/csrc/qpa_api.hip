@@ -745,7 +745,6 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     rp.groups.clear();
     rp.csr_order.clear();
     rp.rows = 0;
-    bool any_dense = false;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -764,9 +763,8 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         rp.base[q] = take(pl.total);
         rp.row0[q] = rp.rows;
         rp.rows += probs[q].n;
-        any_dense = any_dense || probs[q].format == QPA_FMT_DENSE;
     }
-    rp.Rp = round_up(a.replicas, any_dense ? 128 : 64);
+    rp.Rp = round_up(a.replicas, 64);
     rp.C = (int32_t)(rp.Rp / 64);
     rp.k = k;
     rp.nseg = (int32_t)((a.steps + k - 1) / k);

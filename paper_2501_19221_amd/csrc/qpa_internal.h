@@ -166,9 +166,9 @@ hipError_t launch_dense_resident(int64_t n, int64_t R, const float *J, const flo
                                  float *x, float *m, float *h_last, int32_t t0, int32_t t1,
                                  const float *lam, float eta, float alpha, hipStream_t st);
 
-// Any size: one launch per step of the FP32 tiled product shared with the SBM step (128 x
-// 128 tiles, 8 x 8 sums per thread, pipelined LDS reads), fused multiply-adds in ascending
-// order (exact products with s = +-1, so the same sums as the definition).  Layout
+// Any size: one launch per step of the FP32 matrix-core product shared with the SBM step,
+// fused multiply-adds in ascending order (exact products with s = +-1, so the same sums as
+// the definition).  Layout
 // [n][Rp], Rp = dense_fp32_rpad(R): s_cur / s_nxt float +-1, x, m, h_last.
 int64_t dense_fp32_rpad(int64_t R);
 hipError_t launch_dense_fp32_step(int64_t n, int64_t Rp, const float *J, const float *b,
@@ -372,7 +372,7 @@ hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, 
                              int32_t C, int32_t wdt, int32_t idt, const RelArgs &a,
                              hipStream_t st);
 // Dense instance (FP32 canonical J, n x n) through the tiled product; the state pointers
-// of `a` point at the instance's first row (Rp a multiple of 128).  Not REL_MODE_A.
+// of `a` point at the instance's first row (Rp a multiple of 32).  Not REL_MODE_A.
 hipError_t launch_rel_tiles(int32_t mode, int64_t n, const float *J, const float *b,
                             const RelArgs &a, hipStream_t st);
 hipError_t launch_rel_fill(double *p, int64_t count, hipStream_t st);
@@ -383,7 +383,7 @@ hipError_t launch_rel_finish(int32_t T, int32_t nblk, double *part_steps,
                              double *d_alpha, double *d_lam, hipStream_t st);
 
 // ---- Simulated Bifurcation Machine (App. B) -----------------------------------------
-// State q, p [n][Rp] FP32 (replica fastest).  Rp: replicas padded to the dense tile (128)
+// State q, p [n][Rp] FP32 (replica fastest).  Rp: replicas padded to the dense product's 32
 // or to the CSR replica group (a power of two <= 64).
 int sbm_csr_group(int64_t R);
 int64_t sbm_rpad(const qpa_problem &p, int64_t R);
