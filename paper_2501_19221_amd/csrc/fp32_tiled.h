@@ -1,6 +1,7 @@
 // FP32 product on the matrix cores, shared by the SBM step, the PA FP32 dense step and the
-// relaxed-dynamics adjoint:  G = J Q  with J [n][n] symmetric (row k of J is column k) and
-// Q [n][Rp] (replica fastest, Rp a multiple of 32), followed by an element-wise epilogue.
+// relaxed-dynamics adjoint:  G = J Q  with J [n][dense_ld(n)] symmetric (row k of J is column
+// k; rows padded to 16 bytes) and Q [n][Rp] (replica fastest, Rp a multiple of 32),
+// followed by an element-wise epilogue.
 //
 // Every sum must be the sequential chain of fused multiply-adds in ascending k (the
 // definition of the FP32 fields).  v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32 give
@@ -52,10 +53,10 @@ template <int BI_, int BR_, int MT_, int FI_, int FR_, int KC_, int NST_, int GS
 // The tiles, largest first.  One CU does 256 multiply-adds per cycle and four matrix
 // instructions at a time, so a tile costs BI * BR / 128 cycles per k when it is alone on its CU and
 // tiles of a CU add up.
-typedef FpTile<128, 128, 32, 2, 1, 32, 4, 2> FpTileL;    // 8 waves
+typedef FpTile<128, 128, 32, 2, 1, 32, 4, 4> FpTileL;    // 8 waves
 typedef FpTile<64, 64, 32, 1, 1, 32, 4, 4> FpTileM;      // 4 waves
 typedef FpTile<64, 32, 16, 2, 1, 32, 6, 4> FpTileN;      // 4 waves
-typedef FpTile<32, 32, 16, 1, 1, 64, 5, 8> FpTileS;      // 4 waves
+typedef FpTile<32, 32, 16, 1, 1, 64, 5, 4> FpTileS;      // 4 waves
 
 // Workgroup barrier without a memory fence, after this wave's loads of all but the N
 // youngest have landed and its LDS reads are done.
@@ -75,21 +76,20 @@ __device__ __forceinline__ ft_f4 ft_mfma(float a, float b, ft_f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// VEC: n % 4 == 0, so 16-byte pieces of J's rows are aligned and never straddle the edge.
 // Epi: typedef Pre and
 //   float bias(i)                            b_i
+//   void begin()                             uniform values, read while the first chunks load
 //   Pre load(r, idx)                         the element's own state, loaded before the loop
 //   void point(acc, bias, r, idx, Pre)       its update from the sum
 //   void finish()                            once per thread, after its elements
-template <class TL, bool VEC, class Epi>
+template <class TL, class Epi>
 __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64_t Rp,
                                                                 const float *__restrict__ J,
                                                                 const float *__restrict__ qi,
                                                                 Epi epi) {
     constexpr int BI = TL::BI, BR = TL::BR, MT = TL::MT, FI = TL::FI, FR = TL::FR, KC = TL::KC;
     constexpr int NST = TL::NST, KS = TL::KS, NV = TL::NV;
-    constexpr int PJ = VEC ? 4 : 1;                                   // floats per lane and load
-    constexpr int LJ = KC * BI / (64 * PJ * TL::WAVES);               // loads per wave and chunk
+    constexpr int LJ = KC * BI / (256 * TL::WAVES);                   // loads per wave and chunk
     constexpr int LQ = KC * BR / (256 * TL::WAVES);
     static_assert((NST - 2) * (LJ + LQ) < 64, "vmcnt range");
     __shared__ __attribute__((aligned(16))) float lds[NST * TL::STG];
@@ -97,33 +97,53 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t i0 = (int64_t)blockIdx.x * BI, r0 = (int64_t)blockIdx.y * BR;
 
-    // load u of this wave covers floats 64 PJ (u WAVES + wave) .. of the stage's J (or Q)
+    // load u of this wave covers floats 256 (u WAVES + wave) .. of the stage's J (or Q)
     // rows: row jr + u * JSTEP of the chunk at column jc
-    const int jr = (64 * PJ * wave + PJ * lane) / BI, jc = (PJ * lane) % BI;
+    const int jr = (256 * wave + 4 * lane) / BI, jc = (4 * lane) % BI;
     const int qr = (256 * wave + 4 * lane) / BR, qc = (4 * lane) % BR;
-    constexpr int JSTEP = 64 * PJ * TL::WAVES / BI, QSTEP = 256 * TL::WAVES / BR;
-    static_assert(64 * PJ * TL::WAVES % BI == 0 && 256 * TL::WAVES % BR == 0, "whole rows");
-    const uint32_t jcol = (uint32_t)min(i0 + jc, n - PJ), n32 = (uint32_t)n;
-    const float *qb = qi + min(r0 + qc, Rp - 4);
+    constexpr int JSTEP = 256 * TL::WAVES / BI, QSTEP = 256 * TL::WAVES / BR;
+    static_assert(256 * TL::WAVES % BI == 0 && 256 * TL::WAVES % BR == 0, "whole rows");
+    // the MT-column blocks of row k sit at block ^ (row of k within an instruction), as far
+    // as there are blocks, so that the KS rows of a fragment read fall on distinct banks
+    // (the steps between a lane's loads are whole instructions, so its block is fixed)
+    static_assert(JSTEP % KS == 0 && QSTEP % KS == 0, "a lane's rows share their swizzle");
+    constexpr int SWJ = (BI / MT < KS ? BI / MT : KS) - 1, SWQ = (BR / MT < KS ? BR / MT : KS) - 1;
+    auto swz = [](int k, int mask) { return ((KS / (mask + 1) > 1 ? k / (KS / (mask + 1)) : k) & mask) * MT; };
+    const int64_t ldj = dense_ld(n);
+    const uint32_t jcol = (uint32_t)min(i0 + (jc ^ swz(jr % KS, SWJ)), ldj - 4);
+    const uint32_t ldj32 = (uint32_t)ldj;
+    const int64_t qcol = min(r0 + (qc ^ swz(qr % KS, SWQ)), Rp - 4);
     const int nch = (int)((n + KC - 1) / KC);
-    auto stage = [&](int c, int st) {
+    // load u of a chunk (u < LJ: J, then Q); the last chunk's rows past n repeat row n - 1,
+    // and past the end the last chunk is loaded again, unused
+    uint32_t oj[2][LJ];
+    int64_t oq[2][LQ];
+    const int lim = (int)(n - 1 - (int64_t)(nch - 1) * KC);
+#pragma unroll
+    for (int u = 0; u < LJ; ++u) {
+        oj[0][u] = (uint32_t)(jr + u * JSTEP) * ldj32 + jcol;
+        oj[1][u] = (uint32_t)min(jr + u * JSTEP, lim) * ldj32 + jcol;
+    }
+#pragma unroll
+    for (int u = 0; u < LQ; ++u) {
+        oq[0][u] = (qr + u * QSTEP) * Rp + qcol;
+        oq[1][u] = min(qr + u * QSTEP, lim) * Rp + qcol;
+    }
+    auto load = [&](int c, int st, int u) {
         float *dst = lds + st * TL::STG;
-        const int64_t k0 = (int64_t)min(c, nch - 1) * KC;      // past the end: the last chunk
-        const int lim = (int)min(n - 1 - k0, (int64_t)KC);
-        const float *jk = J + k0 * n;
-#pragma unroll
-        for (int u = 0; u < LJ; ++u) {
-            const uint32_t o = (uint32_t)min(jr + u * JSTEP, lim) * n32 + jcol;
-            ft_lds_void *to = (ft_lds_void *)(dst + 64 * PJ * (u * TL::WAVES + wave));
-            if constexpr (VEC) __builtin_amdgcn_global_load_lds(jk + o, to, 16, 0, 0);
-            else __builtin_amdgcn_global_load_lds(jk + o, to, 4, 0, 0);
-        }
-        const float *qk = qb + k0 * Rp;
-#pragma unroll
-        for (int u = 0; u < LQ; ++u)
+        const bool last = c >= nch - 1;                            // uniform
+        const int64_t k0 = (int64_t)(last ? nch - 1 : c) * KC;
+        if (u < LJ) {
+            const uint32_t o = last ? oj[1][u] : oj[0][u];
             __builtin_amdgcn_global_load_lds(
-                qk + min(qr + u * QSTEP, lim) * Rp,
-                (ft_lds_void *)(dst + KC * BI + 256 * (u * TL::WAVES + wave)), 16, 0, 0);
+                J + k0 * ldj + o, (ft_lds_void *)(dst + 256 * (u * TL::WAVES + wave)), 16, 0, 0);
+        } else {
+            u -= LJ;
+            const int64_t o = last ? oq[1][u] : oq[0][u];
+            __builtin_amdgcn_global_load_lds(
+                qi + k0 * Rp + o, (ft_lds_void *)(dst + KC * BI + 256 * (u * TL::WAVES + wave)),
+                16, 0, 0);
+        }
     };
 
     // element v of matrix tile (f, g): variable ib + MT f + vrow(v), replica rb + MT g
@@ -171,7 +191,10 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
                 }
     }
 #pragma unroll
-    for (int s = 0; s < NST - 1; ++s) stage(s, s);
+    for (int s = 0; s < NST - 1; ++s)
+#pragma unroll
+        for (int u = 0; u < LJ + LQ; ++u) load(s, s, u);
+    epi.begin();
 
     // Fragments are read a group ahead of their products (GS reduction steps of one
     // instruction each), across chunk borders, right after the first products of the group
@@ -181,19 +204,27 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
     constexpr int GS = TL::GS, NG = KC / (KS * GS);
     static_assert(NG * KS * GS == KC && NG % 2 == 0, "fragment sets alternate");
     float fa[2][GS][FI], fb[2][GS][FR];
-    auto read = [&](int st, int g, float (&ra)[GS][FI], float (&rb_)[GS][FR]) {
-        const float *As = lds + st * TL::STG + wi * (MT * FI) + lm + lk * BI;
-        const float *Bs = lds + st * TL::STG + KC * BI + wr * (MT * FR) + lm + lk * BR;
+    int aofs[FI], bofs[FR];
 #pragma unroll
-        for (int e = 0; e < GS; ++e) {
+    for (int f = 0; f < FI; ++f) aofs[f] = (MT * (wi * FI + f)) ^ swz(lk, SWJ);
+#pragma unroll
+    for (int h = 0; h < FR; ++h) bofs[h] = (MT * (wr * FR + h)) ^ swz(lk, SWQ);
+    auto read = [&](int st, int g, int e0, int e1, float (&ra)[GS][FI], float (&rb_)[GS][FR]) {
+        const float *As = lds + st * TL::STG + lm + lk * BI;
+        const float *Bs = lds + st * TL::STG + KC * BI + lm + lk * BR;
+#pragma unroll
+        for (int e = e0; e < e1; ++e) {
             const int kk = (g * GS + e) * KS;
 #pragma unroll
-            for (int f = 0; f < FI; ++f) ra[e][f] = As[kk * BI + MT * f];
+            for (int f = 0; f < FI; ++f) ra[e][f] = As[kk * BI + aofs[f]];
 #pragma unroll
-            for (int h = 0; h < FR; ++h) rb_[e][h] = Bs[kk * BR + MT * h];
+            for (int h = 0; h < FR; ++h) rb_[e][h] = Bs[kk * BR + bofs[h]];
         }
     };
-    auto multiply = [&](int st, int st_next, auto tail, int kend) {
+    // the products of a chunk; after them the reads of the next group, then (not in the
+    // last chunk) the loads of chunk cl into its stage, a few after each product
+    constexpr int SLOTS = NG * (GS / 2), LPS = (LJ + LQ + SLOTS - 1) / SLOTS;
+    auto multiply = [&](int st, int st_next, auto tail, int kend, int cl, int stl) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
 #pragma unroll
@@ -211,10 +242,19 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
                 for (int f = 0; f < FI; ++f)
 #pragma unroll
                     for (int h = 0; h < FR; ++h) acc[f][h] = ft_mfma(a[f], b[h], acc[f][h]);
-                if (e == 0) {
+                if (2 * e < GS) {
                     __builtin_amdgcn_sched_barrier(0);
-                    if (g + 1 < NG) read(st, g + 1, fa[(g + 1) & 1], fb[(g + 1) & 1]);
-                    else if constexpr (!decltype(tail)::value) read(st_next, 0, fa[0], fb[0]);
+                    if (g + 1 < NG)
+                        read(st, g + 1, 2 * e, 2 * e + 2, fa[(g + 1) & 1], fb[(g + 1) & 1]);
+                    else if constexpr (!decltype(tail)::value)
+                        read(st_next, 0, 2 * e, 2 * e + 2, fa[0], fb[0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                } else if constexpr (!decltype(tail)::value) {
+#pragma unroll
+                    for (int q = 0; q < LPS; ++q) {
+                        const int u = (g * (GS / 2) + e - GS / 2) * LPS + q;
+                        if (u < LJ + LQ) load(cl, stl, u);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -223,20 +263,19 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
     };
     // chunk 0 has landed in every wave; its first fragments
     ft_wait_barrier<(NST - 2) * (LJ + LQ)>();
-    read(0, 0, fa[0], fb[0]);
+    read(0, 0, 0, GS, fa[0], fb[0]);
     int st = 0, nx = NST - 1;                      // stages of chunk c and of chunk c + NST - 1
     for (int c = 0; c < nch - 1; ++c) {
         // this wave's loads of chunk c + 1 have landed (younger chunks' may not have); after
         // the barrier every wave's have, and every wave is done with the stage refilled next
         ft_wait_barrier<(NST - 3) * (LJ + LQ)>();
-        stage(c + NST - 1, nx);
         const int sn = st + 1 == NST ? 0 : st + 1;
-        multiply(st, sn, std::false_type{}, KC);
+        multiply(st, sn, std::false_type{}, KC, c + NST - 1, nx);
         st = sn;
         nx = nx + 1 == NST ? 0 : nx + 1;
     }
     ft_wait_barrier<0>();              // no load is left in flight when the LDS is given back
-    multiply(st, st, std::true_type{}, (int)(n - (int64_t)(nch - 1) * KC));
+    multiply(st, st, std::true_type{}, (int)(n - (int64_t)(nch - 1) * KC), 0, 0);
     if (!EARLY) load_bias();
     if (full) {
         const int64_t base = ib * Rp + rb;
@@ -292,12 +331,7 @@ hipError_t launch_fp32_product(int64_t n, int64_t Rp, const float *J, const floa
     const dim3 grid = fp32_tile_grid(t, n, Rp);
     if (grid.y > 65535u) return hipErrorInvalidValue;
 #define QPA_FP32_TILE(T, TL)                                                               \
-    if (t == T) {                                                                          \
-        if (n % 4 == 0)                                                                    \
-            k_fp32_mfma_step<TL, true, Epi><<<grid, TL::THREADS, 0, st>>>(n, Rp, J, q, epi); \
-        else                                                                               \
-            k_fp32_mfma_step<TL, false, Epi><<<grid, TL::THREADS, 0, st>>>(n, Rp, J, q, epi); \
-    }
+    if (t == T) k_fp32_mfma_step<TL, Epi><<<grid, TL::THREADS, 0, st>>>(n, Rp, J, q, epi);
     QPA_FP32_TILE(FP32_TILE_L, FpTileL)
     QPA_FP32_TILE(FP32_TILE_M, FpTileM)
     QPA_FP32_TILE(FP32_TILE_N, FpTileN)

@@ -472,6 +472,7 @@ struct RelTileEpilogue {
     RelArgs a;
     const float *b;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    __device__ __forceinline__ void begin() const {}
     struct Pre {};
     __device__ __forceinline__ float bias(int64_t i) const { return b[i]; }
     __device__ __forceinline__ Pre load(int64_t, int64_t) const { return Pre{}; }

@@ -41,7 +41,8 @@ __global__ void __launch_bounds__(RES_THREADS) k_dense_resident(
     const int tid = threadIdx.x;
     const int r0 = blockIdx.x * RB;
     const int nr = min(RB, R - r0);
-    for (int k = tid; k < n * n; k += RES_THREADS) sJ[k] = J[k];
+    const int ldj = (int)dense_ld(n);
+    for (int k = tid; k < n * n; k += RES_THREADS) sJ[k] = J[k / n * ldj + k % n];
     for (int k = tid; k < n; k += RES_THREADS) sb[k] = b[k];
 
     float xr[RES_PAIRS], mr[RES_PAIRS], hr[RES_PAIRS];
@@ -110,7 +111,7 @@ __global__ void __launch_bounds__(64) k_dense_wave(int n, const float *__restric
     const int64_t g = (int64_t)blockIdx.x * n + i;
     float Jr[NW];
 #pragma unroll
-    for (int j = 0; j < NW; ++j) Jr[j] = (act && j < n) ? J[(int64_t)i * n + j] : 0.0f;
+    for (int j = 0; j < NW; ++j) Jr[j] = (act && j < n) ? J[i * dense_ld(n) + j] : 0.0f;
     float xi = 0.0f, mi = 0.0f, bi = 0.0f, hi = 0.0f;
     if (act) {
         xi = x[g];

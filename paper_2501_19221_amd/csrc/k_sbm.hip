@@ -46,6 +46,8 @@ struct SbmEpilogue {
     float a, a0, dt;
     const float *qi;
     float *qo, *p, *gout;
+    float c0 = 0.0f;
+    __device__ __forceinline__ void begin() { c0 = *c0p; }
     struct Pre {
         float q, p;
     };
@@ -56,7 +58,7 @@ struct SbmEpilogue {
     __device__ __forceinline__ void point(float acc, float bi, int64_t, int64_t idx,
                                           const Pre &s) const {
         float qv = s.q, pv = s.p, gv;
-        sbm_point(acc, bi, a, a0, *c0p, dt, __fmul_rn(dt, a0), qv, pv, gv);
+        sbm_point(acc, bi, a, a0, c0, dt, __fmul_rn(dt, a0), qv, pv, gv);
         qo[idx] = qv;
         p[idx] = pv;
         if (gout) gout[idx] = gv;
@@ -82,6 +84,8 @@ struct PaEpilogue {
     int t;
     float eta, alpha;
     float *x, *m, *s_nxt, *h_last;
+    float lt = 0.0f;
+    __device__ __forceinline__ void begin() { lt = lam[t]; }
     struct Pre {
         float x, m;
     };
@@ -92,7 +96,7 @@ struct PaEpilogue {
     __device__ __forceinline__ void point(float acc, float bi, int64_t, int64_t idx,
                                           const Pre &s) const {
         float xv = s.x, mv = s.m, sv, hv;
-        pa_point(acc, bi, lam[t], eta, alpha, xv, mv, sv, hv);
+        pa_point(acc, bi, lt, eta, alpha, xv, mv, sv, hv);
         x[idx] = xv;
         m[idx] = mv;
         s_nxt[idx] = sv;

@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(256) k_dense_rows(int64_t n, const TQ *__restr
             sabs += fabs(q);
             smax = fmax(smax, fabs(q));
         }
-        if (J_f32) J_f32[i * n + j] = (j == i) ? 0.0f : (float)row[j];
+        if (J_f32) J_f32[i * dense_ld(n) + j] = (j == i) ? 0.0f : (float)row[j];
     }
     sum = wave_sum(sum);
     sabs = wave_sum(sabs);

@@ -190,7 +190,7 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_rk = take(sizeof(double) * n);
     pl.o_cpart = take(sizeof(double) * 4 * (size_t)CANON_PARTS);
     pl.o_Jf = (pl.path == Path::DenseResident || pl.path == Path::DenseTiled)
-                  ? take(sizeof(float) * n * n) : 0;
+                  ? take(sizeof(float) * n * (size_t)dense_ld(pl.n)) : 0;
     pl.o_Jb = pl.path == Path::DenseMfma ? take(sizeof(uint16_t) * np * np) : 0;
     pl.o_x = state ? take(sizeof(float) * Rp * np) : 0;
     pl.o_m = state ? take(sizeof(float) * Rp * np) : 0;

@@ -42,11 +42,14 @@ inline size_t dtype_size(int32_t dt) {
 }
 inline bool dtype_is_int(int32_t dt) { return dt == QPA_I8 || dt == QPA_I16 || dt == QPA_I32; }
 
+// Floats per row of the canonical FP32 couplings: rows start at multiples of 16 bytes.
+__host__ __device__ inline int64_t dense_ld(int64_t n) { return (n + 3) / 4 * 4; }
+
 // -------------------------------------------------------------------------------------
 // Launchers (each returns hipSuccess or the first HIP error).
 // -------------------------------------------------------------------------------------
 
-// Canonicalisation of a dense problem: J_f32 (n*n, diagonal zero), b_f32 (n),
+// Canonicalisation of a dense problem: J_f32 (n rows of dense_ld(n), diagonal zero), b_f32 (n),
 // b_i64 / b_f64 (n), per-row partials, then scalars.  Jb (npad*npad bf16) is filled when
 // non-null with bf16(J / 2^e), zero padded.
 // parts: scratch of 4 * CANON_PARTS doubles for the two-launch reduction of large
@@ -371,7 +374,7 @@ int64_t rel_gather_blocks(int64_t blocks, int32_t C);
 hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, int64_t blocks,
                              int32_t C, int32_t wdt, int32_t idt, const RelArgs &a,
                              hipStream_t st);
-// Dense instance (FP32 canonical J, n x n) through the tiled product; the state pointers
+// Dense instance (FP32 canonical J, n x dense_ld(n)) through the tiled product; the state pointers
 // of `a` point at the instance's first row (Rp a multiple of 32).  Not REL_MODE_A.
 hipError_t launch_rel_tiles(int32_t mode, int64_t n, const float *J, const float *b,
                             const RelArgs &a, hipStream_t st);
