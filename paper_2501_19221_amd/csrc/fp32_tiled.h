@@ -12,9 +12,10 @@
 // What bounds it: the FP32 matrix rate (157 TFLOP/s nominal, 147 measured with 32 x 32
 // tiles in registers; the vector units reach 78.6 without packed FP32) for large n and R,
 // and the chain itself (8 cycles per k and wave) where there are few outputs.  At n = 4096,
-// R = 1024 the tile below takes TIME_L per step against 637 us for the product on the vector
-// units (8 x 8 sums per thread); at n = 512, R = 256 TIME_S against 87 us, where
-// the vector product's 128 x 128 tiles left 248 of 256 compute units idle.
+// R = 1024 a step takes 254 us (135 TFLOP/s) against 637 us for the product on the vector
+// units (8 x 8 sums per thread); at n = 512, R = 256 6.8 us against 87 us, where
+// the vector product's 128 x 128 tiles left 248 of 256 compute units idle.  About 4 us of
+// a small step are the launch, the first chunk's latency and the state.
 //
 // A workgroup owns a tile of BI variables x BR replicas; wave (wi, wr) owns FI x FR
 // matrix tiles of MT x MT.  A = J (rows: variables), B = Q (columns: replicas), so that a

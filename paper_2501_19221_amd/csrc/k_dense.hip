@@ -23,118 +23,127 @@ __device__ __forceinline__ void pa_update(float h, float lam, float eta, float a
 
 __device__ __forceinline__ float spin_of(float x) { return x >= 0.0f ? 1.0f : -1.0f; }
 
-// ---------------------------------------------------------------- LDS-resident (small n)
-// A block owns RB replicas and all n variables for every step in [t0, t1): couplings,
-// fields and both spin buffers live in LDS, analog state in registers.  Thread p of the
-// block handles pairs p, p + 256, ... of the RB x n (replica, variable) grid.
-constexpr int RES_THREADS = 256;
-constexpr int RES_PAIRS = 2;
+// ------------------------------------------------- all steps in one launch (small n)
+// A workgroup owns one replica, lane i of its ceil(n / 64) waves variable i: row i of J in
+// registers (16 NC >= n of them) with x_i, m_i, for every step in [t0, t1).  A step is a
+// serial chain of n fused multiply-adds per lane (the sums must ascend in j), so what
+// bounds it is the instructions per term and the exchange of the spins.  The spins of 16
+// variables sit in one register, the same in each row of 16 lanes, and the DPP operand
+// row_newbcast:j hands spin j of the row to every lane: one vector instruction per
+// term and nothing on the scalar unit.  The registers come from
+//   * n <= 64: the wave's own spins, its four rows of lanes copied across by
+//     v_permlane32_swap / v_permlane16_swap -- no LDS, no barrier;
+//   * larger n: the replica's spins in LDS (two buffers), one barrier per step.
+// Terms j >= n are +0.0 (zero couplings, +1 spins): a sum that starts at +0.0 never becomes
+// -0.0 under round-to-nearest, so adding them changes no bit.  The schedule is read 64
+// steps at a time, one value per lane.
+// Measured: n = 20, R = 256, 2000 steps 244 us (signs from a ballot, a bit extraction
+// and a sign flip per term: 448 us); n = 100, R = 150, 1000 steps 378 us (J and the
+// spins of several replicas in LDS, one LDS read of each per term: 3.98 ms); 5 cycles per
+// term.  Past 208 columns the registers run out; the per-step product takes 5.2 us there
+// (n = 209, R = 256) against 0.64 us here at 208.
+constexpr int DR_MAXC = 13;              // columns in groups of 16: n <= 208 (registers)
 
-__global__ void __launch_bounds__(RES_THREADS) k_dense_resident(
-    int n, int R, int RB, const float *__restrict__ J, const float *__restrict__ b,
-    float *__restrict__ x, float *__restrict__ m, float *__restrict__ h_last, int t0, int t1,
-    const float *__restrict__ lam, float eta, float alpha) {
-    extern __shared__ float sh[];
-    float *sJ = sh;
-    float *sb = sJ + n * n;
-    float *sS = sb + n;   // [2][RB][n]
-    const int tid = threadIdx.x;
-    const int r0 = blockIdx.x * RB;
-    const int nr = min(RB, R - r0);
-    const int ldj = (int)dense_ld(n);
-    for (int k = tid; k < n * n; k += RES_THREADS) sJ[k] = J[k / n * ldj + k % n];
-    for (int k = tid; k < n; k += RES_THREADS) sb[k] = b[k];
-
-    float xr[RES_PAIRS], mr[RES_PAIRS], hr[RES_PAIRS];
-    int rl[RES_PAIRS], iv[RES_PAIRS];
-    bool act[RES_PAIRS];
-#pragma unroll
-    for (int q = 0; q < RES_PAIRS; ++q) {
-        int p = tid + q * RES_THREADS;
-        act[q] = p < nr * n;
-        rl[q] = act[q] ? p / n : 0;
-        iv[q] = act[q] ? p - rl[q] * n : 0;
-        xr[q] = mr[q] = hr[q] = 0.0f;
-        if (act[q]) {
-            int64_t g = (int64_t)(r0 + rl[q]) * n + iv[q];
-            xr[q] = x[g];
-            mr[q] = m[g];
-            sS[rl[q] * n + iv[q]] = spin_of(xr[q]);
-        }
-    }
-    __syncthreads();
-    int cur = 0;
-    for (int t = t0; t < t1; ++t) {
-        const float lt = lam[t];
-        const float *scur = sS + cur * RB * n;
-        float *snxt = sS + (cur ^ 1) * RB * n;
-#pragma unroll
-        for (int q = 0; q < RES_PAIRS; ++q) {
-            if (!act[q]) continue;
-            const float *Jrow = sJ + iv[q] * n;
-            const float *srow = scur + rl[q] * n;
-            float acc = 0.0f;
-            for (int j = 0; j < n; ++j) acc = __fmaf_rn(Jrow[j], srow[j], acc);
-            float h = __fadd_rn(acc, sb[iv[q]]);
-            hr[q] = h;
-            pa_update(h, lt, eta, alpha, xr[q], mr[q]);
-            snxt[rl[q] * n + iv[q]] = spin_of(xr[q]);
-        }
-        __syncthreads();
-        cur ^= 1;
-    }
-#pragma unroll
-    for (int q = 0; q < RES_PAIRS; ++q) {
-        if (!act[q]) continue;
-        int64_t g = (int64_t)(r0 + rl[q]) * n + iv[q];
-        x[g] = xr[q];
-        m[g] = mr[q];
-        if (h_last && t1 > t0) h_last[g] = hr[q];
-    }
+// acc += s_j J_j for the 16 columns of a group, ascending.  The leading nop separates a
+// vector write of the spins from their use as a DPP operand.
+__device__ __forceinline__ void dr_fma16(float &acc, float s, const float (&J)[16]) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %6 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %7 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %8 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %10 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %12 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %13 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %14 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %15 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %16 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc)
+        : "v"(s), "v"(J[0]), "v"(J[1]), "v"(J[2]), "v"(J[3]), "v"(J[4]), "v"(J[5]), "v"(J[6]),
+          "v"(J[7]), "v"(J[8]), "v"(J[9]), "v"(J[10]), "v"(J[11]), "v"(J[12]), "v"(J[13]),
+          "v"(J[14]), "v"(J[15]));
 }
 
-// ---------------------------------------------------------------- one wave per replica
-// n <= 64: lane i holds row i of J (NW >= n registers), x_i and m_i.  The spins of a step
-// are one 64-bit ballot (bit j set <=> x_j < 0), so the sign of term j is the same in every
-// lane, and J_ij * s_j is J_ij with its sign bit flipped where s_j = -1 (the FP32 product,
-// exactly).  The sums ascend in j from zero as in the block kernel; no LDS, no barrier.
-// The schedule is read 64 steps at a time, one value per lane.
-template <int NW>
-__global__ void __launch_bounds__(64) k_dense_wave(int n, const float *__restrict__ J,
-                                                   const float *__restrict__ b,
-                                                   float *__restrict__ x, float *__restrict__ m,
-                                                   float *__restrict__ h_last, int t0, int t1,
-                                                   const float *__restrict__ lam, float eta,
-                                                   float alpha) {
-    const int i = threadIdx.x;
+// The first 4 columns of a group only (n just past a multiple of 16).
+__device__ __forceinline__ void dr_fma4(float &acc, float s, const float (&J)[16]) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:3 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc)
+        : "v"(s), "v"(J[0]), "v"(J[1]), "v"(J[2]), "v"(J[3]));
+}
+
+// Rows of 16 lanes of v, each copied to all four rows: r[c] holds row c.
+__device__ __forceinline__ void dr_rows(float v, float (&r)[4]) {
+    const unsigned u = __float_as_uint(v);
+    const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // rows 0 1 0 1, 2 3 2 3
+    const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+    r[0] = __uint_as_float(lo[0]);
+    r[1] = __uint_as_float(lo[1]);
+    r[2] = __uint_as_float(hi[0]);
+    r[3] = __uint_as_float(hi[1]);
+}
+
+template <int NC, bool LAST4>
+__global__ void __launch_bounds__(NC <= 4 ? 64 : NC <= 8 ? 128 : 256, 1) k_dense_resident(
+    int n, const float *__restrict__ J, const float *__restrict__ b, float *__restrict__ x,
+    float *__restrict__ m, float *__restrict__ h_last, int t0, int t1,
+    const float *__restrict__ lam, float eta, float alpha) {
+    constexpr bool ONE = NC <= 4;                    // one wave: no exchange through LDS
+    __shared__ float sp[ONE ? 1 : 2][ONE ? 1 : 16 * NC];
+    const int i = threadIdx.x, lane = i & 63;
     const bool act = i < n;
-    const int64_t g = (int64_t)blockIdx.x * n + i;
-    float Jr[NW];
+    const int64_t g = (int64_t)blockIdx.x * n + i, ldj = dense_ld(n);
+    float Jr[NC][16];                                // J is symmetric: column i, coalesced
 #pragma unroll
-    for (int j = 0; j < NW; ++j) Jr[j] = (act && j < n) ? J[i * dense_ld(n) + j] : 0.0f;
+    for (int j = 0; j < 16 * NC; ++j) Jr[j / 16][j % 16] = (act && j < n) ? J[j * ldj + i] : 0.0f;
     float xi = 0.0f, mi = 0.0f, bi = 0.0f, hi = 0.0f;
     if (act) {
         xi = x[g];
         mi = m[g];
         bi = b[i];
     }
-    uint64_t neg = __ballot(act && xi < 0.0f);
+    float s = act ? spin_of(xi) : 1.0f;
+    int cur = 0;
+    if (!ONE) {
+        if (i < 16 * NC) sp[0][i] = s;
+        __syncthreads();
+    }
     for (int tb = t0; tb < t1; tb += 64) {
-        const float lv = tb + i < t1 ? lam[tb + i] : 0.0f;
+        const float lv = tb + lane < t1 ? lam[tb + lane] : 0.0f;
         const int te = t1 - tb < 64 ? t1 - tb : 64;
         for (int k = 0; k < te; ++k) {
             const float lt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv), k));
-            float acc = 0.0f;
-            // terms j >= n are +0.0 (zero coupling, spin bit clear): a sum that starts at
-            // +0.0 never becomes -0.0 under round-to-nearest, so adding them changes no bit
+            float sv[ONE ? 4 : NC];
+            if constexpr (ONE) {
+                dr_rows(s, sv);
+            } else {
 #pragma unroll
-            for (int j = 0; j < NW; ++j) {
-                const uint32_t sgn = (uint32_t)((neg >> j) & 1u) << 31;
-                acc = __fadd_rn(acc, __uint_as_float(__float_as_uint(Jr[j]) ^ sgn));
+                for (int c = 0; c < NC; ++c) sv[c] = sp[cur][16 * c + (lane & 15)];
+            }
+            float acc = 0.0f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (LAST4 && c == NC - 1) dr_fma4(acc, sv[c], Jr[c]);
+                else dr_fma16(acc, sv[c], Jr[c]);
             }
             hi = __fadd_rn(acc, bi);
             pa_update(hi, lt, eta, alpha, xi, mi);
-            neg = __ballot(act && xi < 0.0f);
+            s = act ? spin_of(xi) : 1.0f;
+            if (!ONE) {
+                cur ^= 1;
+                if (i < 16 * NC) sp[cur][i] = s;
+                __syncthreads();
+            }
         }
     }
     if (act) {
@@ -144,7 +153,6 @@ __global__ void __launch_bounds__(64) k_dense_wave(int n, const float *__restric
     }
 }
 
-
 __global__ void __launch_bounds__(256) k_sign_f32(int64_t count, const float *__restrict__ x,
                                                   float *__restrict__ s) {
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count;
@@ -152,43 +160,36 @@ __global__ void __launch_bounds__(256) k_sign_f32(int64_t count, const float *__
         s[k] = spin_of(x[k]);
 }
 
-int resident_rb(int64_t n) {
-    int rb = (int)((RES_THREADS * RES_PAIRS) / n);
-    return rb < 1 ? 1 : rb;
-}
-
-size_t resident_lds_bytes(int64_t n) {
-    return sizeof(float) * (size_t)(n * n + n + 2 * resident_rb(n) * n);
-}
-
 }  // namespace
 
-bool dense_resident_fits(int64_t n) {
-    return n >= 1 && n <= 128 && resident_lds_bytes(n) <= 64 * 1024;
-}
+bool dense_resident_fits(int64_t n) { return n >= 1 && n <= 16 * DR_MAXC; }
 
 hipError_t launch_dense_resident(int64_t n, int64_t R, const float *J, const float *b,
                                  float *x, float *m, float *h_last, int32_t t0, int32_t t1,
                                  const float *lam, float eta, float alpha, hipStream_t st) {
     if (!dense_resident_fits(n)) return hipErrorInvalidValue;
-    if (n <= 64 && R <= INT32_MAX) {
-        const unsigned grid = (unsigned)R;
-        if (n <= 16)
-            k_dense_wave<16><<<grid, 64, 0, st>>>((int)n, J, b, x, m, h_last, t0, t1, lam, eta,
-                                                  alpha);
-        else if (n <= 32)
-            k_dense_wave<32><<<grid, 64, 0, st>>>((int)n, J, b, x, m, h_last, t0, t1, lam, eta,
-                                                  alpha);
-        else
-            k_dense_wave<64><<<grid, 64, 0, st>>>((int)n, J, b, x, m, h_last, t0, t1, lam, eta,
-                                                  alpha);
-        return hipGetLastError();
+    const int nc = (int)((n + 15) / 16);
+    const bool last4 = n - 16 * (nc - 1) <= 4;
+    const unsigned threads = (unsigned)((n + 63) / 64 * 64);
+    constexpr int64_t PART = (int64_t)1 << 23;      // replicas a launch: a grid has < 2^32 threads
+    for (int64_t r0 = 0; r0 < R; r0 += PART) {
+        const unsigned grid = (unsigned)(R - r0 < PART ? R - r0 : PART);
+        float *xr = x + r0 * n, *mr = m + r0 * n, *hr = h_last ? h_last + r0 * n : nullptr;
+        switch (nc) {
+#define QPA_DR(C)                                                                          \
+    case C:                                                                                \
+        if (last4)                                                                         \
+            k_dense_resident<C, true><<<grid, threads, 0, st>>>((int)n, J, b, xr, mr, hr, t0, \
+                                                                t1, lam, eta, alpha);      \
+        else                                                                               \
+            k_dense_resident<C, false><<<grid, threads, 0, st>>>((int)n, J, b, xr, mr, hr, t0, \
+                                                                 t1, lam, eta, alpha);     \
+        break;
+            QPA_DR(1) QPA_DR(2) QPA_DR(3) QPA_DR(4) QPA_DR(5) QPA_DR(6) QPA_DR(7)
+            QPA_DR(8) QPA_DR(9) QPA_DR(10) QPA_DR(11) QPA_DR(12) QPA_DR(13)
+#undef QPA_DR
+        }
     }
-    const int rb = resident_rb(n);
-    const unsigned grid = (unsigned)((R + rb - 1) / rb);
-    const size_t lds = resident_lds_bytes(n);
-    k_dense_resident<<<grid, RES_THREADS, lds, st>>>((int)n, (int)R, rb, J, b, x, m, h_last,
-                                                     t0, t1, lam, eta, alpha);
     return hipGetLastError();
 }
 

@@ -1,0 +1,95 @@
+"""The FP32 dense kernels at the edges of their tiles and sizes, bit for bit against the oracle:
+the matrix-core product (each tile, ragged in variables and replicas) and the kernel that
+keeps couplings and state in registers for all steps.  Their sums are the sequential chain
+of the definition, so no tolerance applies."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2501_19221_amd import instances as gen
+
+pytestmark = pytest.mark.gpu
+
+
+def say(msg):
+    print("[gpu-dense] " + msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def q():
+    from paper_2501_19221_amd import qpa
+    return qpa
+
+
+@pytest.fixture(scope="module")
+def eng(q):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    e = q.Engine(0)
+    yield e
+    e.close()
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+# 32 x 32 tiles: one partial tile, one k chunk and a term past it, several; then 64 x 32,
+# 64 x 64 and 128 x 128 tiles, ragged (sizes the choice by work assigns to them)
+@pytest.mark.parametrize("n,R", [(5, 3), (32, 33), (64, 1), (65, 32), (257, 40), (301, 129),
+                                 (2041, 250), (2998, 330), (4089, 1017)])
+def test_sbm_product_tiles(q, eng, n, R):
+    T, c0 = 3, 0.5
+    inst = gen.sk_ising(n, 0.1, seed=n)
+    sp = q.make_sbm_params(R, T, 0.5, c0=c0, sigma0=0.1, seed=4)
+    say("sbm n=%d R=%d" % (n, R))
+    out = eng.sbm_solve(q.Problem.from_instance(inst), sp, want_state=True)
+    x, m = host(out["x"]), host(out["m"])
+    for r in sorted({0, R // 2, R - 1}):
+        qv, _ = orc.pa_init(n, 1, 4, np.float32(0.1), r0=r)
+        p = np.zeros_like(qv)
+        orc.sbm_steps_dense(inst.dense, inst.lin, qv, p, 0, T, T, 1.0, c0, 0.5)
+        assert np.array_equal(x[r:r + 1], qv) and np.array_equal(m[r:r + 1], p)
+
+
+@pytest.mark.parametrize("n,R", [(209, 3), (2041, 250), (4089, 1017)])
+def test_pa_product_tiles(q, eng, n, R):
+    T = 4
+    inst = gen.sk_ising(n, 0.1, seed=n)
+    p = q.make_params(R, T, 0.2, 0.8, 4.0, 0.1, 6)
+    say("pa n=%d R=%d" % (n, R))
+    out = eng.solve(q.Problem.from_instance(inst), p, want_state=True)
+    x, m = host(out["x"]), host(out["m"])
+    lam = orc.lambda_linear(T, 4.0)
+    for r in sorted({0, R // 2, R - 1}):
+        xr, mr = orc.pa_init(n, 1, 6, np.float32(0.1), r0=r)
+        orc.pa_steps_dense_float(inst.dense, inst.lin, xr, mr, 0, T, lam, 0.2, 0.8)
+        assert np.array_equal(x[r:r + 1], xr) and np.array_equal(m[r:r + 1], mr)
+
+
+# every register width of the resident kernel (groups of 16 columns, the 4-column tail
+# past a group), one wave and several, the last size that fits
+@pytest.mark.parametrize("n", [1, 4, 5, 16, 17, 20, 21, 36, 49, 64, 65, 80, 81, 95, 113, 128, 132,
+                               145, 164, 177, 192, 193, 196, 208])
+def test_dense_resident_widths(q, eng, n):
+    R, T, t1 = 3, 70, 67
+    inst = gen.sk_ising(n, 0.1, seed=n)
+    prob = q.Problem.from_instance(inst)
+    p = q.make_params(R, T, 0.2, 0.8, 4.0, 0.1, 8)
+    say("resident n=%d" % n)
+    lam = orc.lambda_linear(T, 4.0)
+    x, m = orc.pa_init(n, R, 8, np.float32(0.1))
+    import torch
+    xd, md = torch.from_numpy(x.copy()).cuda(), torch.from_numpy(m.copy()).cuda()
+    h = eng.steps(prob, p, 0, t1, xd, md, want_h=True)
+    orc.pa_steps_dense_float(inst.dense, inst.lin, x, m, 0, t1 - 1, lam, 0.2, 0.8)
+    s = np.where(x >= 0, 1, -1).astype(np.float32)
+    orc.pa_steps_dense_float(inst.dense, inst.lin, x, m, t1 - 1, t1, lam, 0.2, 0.8)
+    assert np.array_equal(host(xd), x) and np.array_equal(host(md), m)
+    acc = np.zeros((R, n), np.float32)
+    for j in range(n):
+        acc = acc + s[:, j:j + 1] * inst.dense[j][None, :]
+    assert np.array_equal(host(h), acc + inst.lin[None, :])
