@@ -2,35 +2,39 @@
 // couplings stored as bf16(J / 2^e), FP32 accumulation, result scaled back by 2^e).
 //
 // One launch advances every replica by one step.  A workgroup owns an output tile of
-// 128 replicas x 128 variables and has 16 waves, four per SIMD:
-//   * 8 matrix waves: a 2 x 2 arrangement of 64 x 64 sub-tiles, each worked on by two
-//     waves that split every chunk's eight k steps between them (steps 0..3 and 4..7),
+// 256 replicas x 64 variables (128 x 128 where the replicas are no multiple of 256, and
+// for batch instances) and has 16 waves, four per SIMD:
+//   * 8 matrix waves: 64 x 64 sub-tiles, each worked on by two waves that split every
+//     chunk's eight k steps between them (steps 0..3 and 4..7),
 //     so that every SIMD runs two matrix waves whose instruction streams interleave (one
 //     wave alone cannot issue its operand expansion while its matrix ops run); each wave
 //     keeps 2 x 2 accumulators of 32 x 32 and the two halves are summed in LDS at the end;
 //   * 8 state waves: they load the tile's x and m into registers while the reduction
 //     runs, then wait for the field and run the PA update and write x, m and the spins.
+// What bounds the reduction is the rate at which a compute unit can read J and the spins
+// (measured 37..53 GB/s per CU, 16..22 bytes a cycle, however they are loaded), so a tile is
+// chosen for its bytes: spins travel as sign bits (1 bit per variable and replica; as
+// pre-expanded words of 4 bits each before), which makes replicas nearly free, and a tile
+// of 256 x 64 then needs 160 bytes per reduction index against 272 for 128 x 128.
+// sk4096 (n = 4096, R = 1024): 38.5 us per step against 42.7 with 4-bit words and 128 x
+// 128 tiles (320 bytes).
 // Chunks are staged through LDS with direct global->LDS loads issued by the matrix waves
-// only (NST stages, NST-1 chunks in flight): per chunk the 128 x 128 bf16 block of J
-// (4 loads of 16 bytes per lane and wave, each filling 4 rows of 256 bytes) and the spins
-// of the tile's 128 replicas for those 128 variables (1 load of 16 bytes per lane and
-// wave, 64 bytes per replica).
-// Inside a J row the sixteen 16-byte pieces sit at position piece ^ (row % 16), and inside
-// a replica's 64 spin bytes the four 16-byte pieces at (piece + row / 4) % 4, so that the
+// only (NST stages, NST-1 chunks in flight): per chunk the BN x 128 bf16 block of J
+// (loads of 16 bytes per lane, each filling 4 rows of 256 bytes) and the sign bits
+// of the tile's replicas for those 128 variables (16 bytes per replica, the first BM / 64
+// waves one load each).
+// Inside a J row the sixteen 16-byte pieces sit at position piece ^ (row % 16), so that the
 // fragment reads of 16 consecutive rows fall on distinct banks.  One barrier per
 // chunk publishes a stage and frees the one that is loaded next; the state waves take
 // part in every barrier and issue no loads in between, so that the matrix waves' waits
 // count their own loads only.  After the loop the raw sums go to the state waves
-// through LDS, one 128 x 128 FP32 buffer per k half (rows padded to 136 so that the two
+// through LDS, one FP32 buffer per k half (rows padded by 8 floats so that the two
 // halves of a wave's stores use different banks), added by the state waves.
 //
-// Spins ("pair words", chunk-major): for replica r and chunk kc (variables 128 kc ..
-// 128 kc + 127) there are 16 u32 words at (kc * Rp + r) * 16.  Word 8 h + q covers the
-// eight variables 128 kc + 16 q + 8 h + j (j = 0..7) -- exactly the k values of one lane
-// half h of the matrix instruction's operand at k step q -- as the byte B (bit j set <=>
-// spin -1) in its low half and B >> 1 in its high half, the form the sign expansion
-// starts from.  The state waves write this form once per step; each word is expanded by
-// every tile of its replicas' row, so work moved into the writer is saved many times.
+// Spin bits, chunk-major: for replica r and chunk kc (variables 128 kc .. 128 kc + 127)
+// there are 4 u32 words at (kc * Rp + r) * 4; bit j of word w is set where variable
+// 128 kc + 32 w + j has spin -1.  The bf16 operand is made from them in registers, two
+// full-rate operations per pair of spins (expand_spins).
 //
 // Matrix instruction: v_mfma_f32_32x32x16_bf16.  Operand layout (64 lanes):
 //   A (32 x 16, rows = replicas): lane l holds row l%32, k = 8*(l/32) .. +7
@@ -39,6 +43,7 @@
 #include "qpa_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace qpa {
 namespace {
@@ -48,14 +53,25 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = MF_BM, BN = MF_BN;
 constexpr int KC = 128;                      // reduction chunk (variables)
-constexpr int JSTG = BN * KC * 2;            // J block of a stage: 128 rows x 256 bytes
-constexpr int SSTG = BM * 64;                // spin words of a stage: 128 rows x 64 bytes
-constexpr int STG = JSTG + SSTG;
-constexpr int NST = 4;                       // stages
-constexpr int LDS_BYTES = NST * STG;
+// A BF16 tile shape: replicas, variables and stages.
+template <int BM_, int BN_, int NST_> struct BfTile {
+    static constexpr int BM = BM_, BN = BN_, NST = NST_;
+    static constexpr int JSTG = BN * KC * 2;         // J block of a stage: rows of 256 bytes
+    static constexpr int STG = JSTG + BM * 16;       // and 16 bytes of sign bits per replica
+    static constexpr int HS = BN + 8;                // row stride of the field handoff (floats)
+    static constexpr int LDS = NST * STG > 2 * BM * HS * 4 ? NST * STG : 2 * BM * HS * 4;
+    static constexpr int WC = BN / 64;               // 64-column sub-tiles
+    static constexpr int JL = BN / 32;               // J loads per matrix wave and chunk
+    static constexpr int SL = BM / 64;               // matrix waves that load spins
+    static constexpr int RS = 512 / BN;              // row step of a state thread
+    static_assert(BM * BN == 128 * 128, "8 matrix waves of 64 x 64, 32 elements per state thread");
+    static_assert(LDS <= 160 * 1024, "LDS of one workgroup");
+};
+typedef BfTile<256, 64, 7> BfWide;
+typedef BfTile<128, 128, 4> BfSquare;
 // Integer couplings with |J| <= 127 (exact in int8) run on tiles of 64 replicas x 256
 // variables (see the int8 section below): J rows of 128 bytes per chunk, spins one byte per
 // (replica, variable) (+1 = 0x01, -1 = 0xFF), chunk-major (128 bytes per replica and
@@ -67,16 +83,13 @@ constexpr int STG8 = JSTG8 + SSTG8;
 constexpr int NST8 = 4;
 constexpr int HS8 = BN8 + 8;                 // row stride of the int8 handoff (int32)
 constexpr int SR8 = BM8 / 2;                 // rows per state thread of an int8 tile
-static_assert(NST8 * STG8 <= LDS_BYTES, "int8 stages fit the same LDS");
-static_assert(2 * BM8 * HS8 * 4 <= LDS_BYTES, "the int8 handoff's two partial-sum buffers");
+constexpr int LDS8_BYTES = NST8 * STG8;
+static_assert(LDS8_BYTES <= 160 * 1024, "LDS of one workgroup");
+static_assert(2 * BM8 * HS8 * 4 <= LDS8_BYTES, "the int8 handoff's two partial-sum buffers");
 static_assert(BN8 % KC == 0 && BN8 / 16 == 16, "16 row groups of 16 per int8 tile");
-constexpr int HS = BN + 8;                   // row stride of the field handoff (floats)
 constexpr int THREADS = 1024;                // 8 matrix waves + 8 state waves
 constexpr int MW = 8;                        // matrix waves
-constexpr int SR = BM / 4;                   // rows per state thread
-static_assert(LDS_BYTES >= BM * HS * 4, "the field handoff reuses the stages");
-static_assert(LDS_BYTES >= 2 * BM * HS * 4, "the two k halves' handoff buffers");
-static_assert(LDS_BYTES <= 160 * 1024, "LDS of one workgroup");
+constexpr int SR = 32;                       // rows per state thread
 static_assert(MF_NPAD % KC == 0, "np must be a multiple of the chunk");
 
 __device__ __forceinline__ void pa_update(float h, float lam, float eta, float alpha, float &x,
@@ -91,25 +104,24 @@ __device__ __forceinline__ void pa_update(float h, float lam, float eta, float a
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
-// Pair word (low half: byte B of 8 sign bits, bit j <=> element j is -1; high half:
-// B >> 1) -> eight bf16 +-1 values: dword q holds elements 2q (low half) and 2q+1 (high
-// half); a set bit sets the half's sign bit on top of 0x3F80 (= 1.0).  One packed 16-bit
-// shift by 15 - 2q brings bit 2q to the top of the low half and bit 2q+1 to the top of
-// the high half; a mask keeps the two sign positions.  Two full-rate operations per dword.
-__device__ __forceinline__ uint32_t spin_pair(uint32_t byte) { return byte | ((byte >> 1) << 16); }
-
-__device__ __forceinline__ bf16x8 expand_spins(uint32_t pair, uint32_t sign_mask) {
+// Eight sign bits (the low byte of the low or high half of w) -> eight bf16 +-1 values:
+// dword q holds elements 2q (low half) and 2q+1 (high half); a set bit sets the half's
+// sign bit on top of 0x3F80 (= 1.0).  One packed 16-bit shift of the same half by 15 - 2q
+// and 14 - 2q brings the two bits to the tops of the halves (whatever lies above the byte
+// is shifted out); a mask keeps the two sign positions.  Two full-rate operations per dword.
+template <int HI>
+__device__ __forceinline__ bf16x8 expand_spins(uint32_t w, uint32_t sign_mask) {
+    const u16x2 src = __builtin_bit_cast(u16x2, w);
     u32x4 d;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const uint16_t sh = (uint16_t)(15 - 2 * q);
-        const u16x2 v = __builtin_bit_cast(u16x2, pair) << (u16x2){sh, sh};
-        // (v & 0x80008000) | 0x3F803F80 in one instruction; the mask comes in a VGPR
-        // because one VOP3 instruction can read only one scalar operand here
-        uint32_t r;
-        asm("v_and_or_b32 %0, %1, %2, %3"
-            : "=v"(r)
-            : "v"(__builtin_bit_cast(uint32_t, v)), "v"(sign_mask), "s"(0x3F803F80u));
+        const u16x2 v = (u16x2){src[HI], src[HI]} << (u16x2){(uint16_t)(15 - 2 * q),
+                                                             (uint16_t)(14 - 2 * q)};
+        // one v_and_or_b32: the mask comes in a VGPR because a VOP3 instruction can read only
+        // one scalar operand here.  (Not as inline assembly: the compiler would not see a
+        // vector result on its way into a matrix instruction and leave out the wait states
+        // between them.)
+        const uint32_t r = (__builtin_bit_cast(uint32_t, v) & sign_mask) | 0x3F803F80u;
         d[q] = r;
     }
     return __builtin_bit_cast(bf16x8, d);
@@ -129,11 +141,9 @@ template <int N> __device__ __forceinline__ void wait_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-constexpr int LOADS_PER_CHUNK = 5;           // per matrix wave: 4 J pieces + 1 spin piece
-
-// The tile of a workgroup: replicas R0 .. R0+127 (rows at or past `rlive` are padding:
+// The tile of a workgroup: replicas from R0 (rows at or past `rlive` are padding:
 // their state is neither read nor written and they report +1 spins), variables
-// I0 .. I0+127 of an instance with np padded variables and Rp padded replicas.
+// from I0 of an instance with np padded variables and Rp padded replicas.
 struct Tile {
     int64_t np, Rp, I0, R0, rlive;
     const uint16_t *Jb;
@@ -145,46 +155,54 @@ struct Tile {
 };
 
 // ---- matrix waves: the reduction of one step, left in LDS as raw sums --------------
-// Executes nchunk + 2 workgroup barriers (the state waves execute as many).
-__device__ __forceinline__ void matrix_step(uint8_t *lds, const Tile &tl, int nchunk,
-                                            const uint32_t *__restrict__ s_cur, int wave,
-                                            int lane) {
+// Executes nchunk + 3 workgroup barriers (the state waves execute as many).
+template <class TL> struct MatrixStep {
+    static __device__ __forceinline__ void run(uint8_t *lds, const Tile &tl, int nchunk,
+                                               const uint32_t *__restrict__ s_cur, int wave,
+                                               int lane);
+};
+template <class TL>
+__device__ __forceinline__ void MatrixStep<TL>::run(uint8_t *lds, const Tile &tl, int nchunk,
+                                                    const uint32_t *__restrict__ s_cur,
+                                                    int wave, int lane) {
+    constexpr int BM = TL::BM, NST = TL::NST, JL = TL::JL, HS = TL::HS;
     const int64_t np = tl.np, I0 = tl.I0, R0 = tl.R0;
     const uint16_t *__restrict__ Jb = tl.Jb;
     float *hs = reinterpret_cast<float *>(lds);
     const int kh = wave >> 2;                      // k steps 4 kh .. 4 kh + 3 of a chunk
-    const int wr = (wave >> 1) & 1, wc = wave & 1;
+    const int wr = (wave & 3) / TL::WC, wc = (wave & 3) % TL::WC;
     const int half = lane >> 5, l32 = lane & 31;
-    // J: load u (0..3) of wave w fills LDS rows 16w + 4u + lane/16 at position lane % 16,
+    // J: load u of wave w fills LDS rows 4 JL w + 4u + lane/16 at position lane % 16,
     // which holds piece (lane % 16) ^ (row % 16) of that row.  Addresses are a
     // wave-uniform base plus 32-bit lane offsets (fewer registers than 64-bit pointers).
-    const uint16_t *Jw = Jb + (I0 + 16 * wave) * np;
-    uint32_t oJ[4];
+    const uint16_t *Jw = Jb + (I0 + 4 * JL * wave) * np;
+    uint32_t oJ[JL];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int r = 4 * u + (lane >> 4);         // row - 16 w, and row % 16 == r % 16
-        oJ[u] = (uint32_t)r * (uint32_t)np + 8u * (uint32_t)((lane & 15) ^ (r & 15));
+    for (int u = 0; u < JL; ++u) {
+        const int r = 4 * u + (lane >> 4);         // row - 4 JL w
+        oJ[u] = (uint32_t)r * (uint32_t)np +
+                8u * (uint32_t)((lane & 15) ^ ((4 * JL * wave + r) & 15));
     }
-    // spins: the load of wave w fills bytes 1024w + 16 lane of the 8 KiB block of the
-    // tile's replicas (64 bytes per replica, in replica order): row 16w + lane/4,
-    // position lane % 4, which holds piece (lane - row / 4) % 4
-    const uint32_t *Sw = s_cur + (R0 + 16 * wave) * 16;
-    const uint32_t oS = (uint32_t)(lane >> 2) * 16u +
-                        4u * (uint32_t)(((lane & 3) - ((lane >> 4) & 3)) & 3);
-    const int64_t sstride = tl.Rp * 16;            // u32 words between consecutive chunks
+    // spins: the load of wave w < SL fills the 16 bytes of replicas 64 w + lane (replicas
+    // past the padded ones repeat the last)
+    const bool loads_s = wave < TL::SL;
+    const uint32_t *Sw = s_cur + min(R0 + 64 * wave + lane, tl.Rp - 1) * 4;
+    const int64_t sstride = tl.Rp * 4;             // u32 words between consecutive chunks
     auto stage = [&](int kc, int st) {
         kc = kc < nchunk ? kc : nchunk - 1;        // past the end: reload the last chunk
-        uint8_t *dst = lds + st * STG;
+        uint8_t *dst = lds + st * TL::STG;
         const uint16_t *jc = Jw + (int64_t)kc * KC;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < JL; ++u)
             __builtin_amdgcn_global_load_lds(jc + oJ[u],
-                                             (lds_void *)(dst + (4 * wave + u) * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(Sw + (int64_t)kc * sstride + oS,
-                                         (lds_void *)(dst + JSTG + 1024 * wave), 16, 0, 0);
+                                             (lds_void *)(dst + (JL * wave + u) * 1024), 16, 0, 0);
+        if (loads_s)
+            __builtin_amdgcn_global_load_lds(Sw + (int64_t)kc * sstride,
+                                             (lds_void *)(dst + TL::JSTG + 1024 * wave), 16, 0, 0);
     };
 
-    const uint32_t sign_mask = __builtin_amdgcn_readfirstlane(0x80008000u) + 0u * lane;
+    uint32_t sign_mask = 0x80008000u;
+    asm volatile("" : "+v"(sign_mask));        // a VGPR whose value the compiler does not know
     f32x16 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -193,49 +211,81 @@ __device__ __forceinline__ void matrix_step(uint8_t *lds, const Tile &tl, int nc
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    // the products of chunk c from its stage
-    auto multiply = [&](int c) {
-        const uint8_t *src = lds + (c % NST) * STG;
-        // this lane's 4 pair words (k steps 4 kh .. 4 kh + 3 of its half) per replica
-        // fragment: piece 2 half + kh of the replica's 64 bytes
-        u32x4 sw[2];
+    // J fragments of one k step and this lane's 64 sign bits of a chunk per replica
+    // fragment, moved so that the byte of its half is the low byte of each 16 bits
+    auto read_j = [&](u32x4 (&bq)[2], int st, int qq) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int row = 64 * wr + 32 * i + l32;
-            const int pos = (2 * half + kh + (row >> 2)) & 3;
-            sw[i] = *reinterpret_cast<const u32x4 *>(src + JSTG + 64 * row + 16 * pos);
+        for (int j = 0; j < 2; ++j) {
+            const int row = 64 * wc + 32 * j + l32;
+            const int pos = (2 * (4 * kh + qq) + half) ^ (row & 15);
+            bq[j] = *reinterpret_cast<const u32x4 *>(lds + st * TL::STG + row * 256 + pos * 16);
         }
+    };
+    auto read_s = [&](u32x2 (&sw)[2], int st) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            sw[i] = *reinterpret_cast<const u32x2 *>(lds + st * TL::STG + TL::JSTG +
+                                                     16 * (64 * wr + 32 * i + l32) + 8 * kh);
+    };
+    // The products of a chunk.  The next k step's fragments (the next chunk's first ones and
+    // its signs in the last step) are read right after a step's first product, in an order
+    // fixed by scheduling barriers: the compiler would read them before their use and wait.
+    u32x4 bq[2][2];
+    u32x2 sw[2][2];
+    auto multiply = [&](int st, int st_next, u32x2 (&s_now)[2], u32x2 (&s_next)[2]) {
+        u32x2 w[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) w[i] = s_now[i] >> (u32x2){8u * half, 8u * half};
 #pragma unroll
         for (int qq = 0; qq < 4; ++qq) {
-            const int q = 4 * kh + qq;
-            u32x4 bq[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int row = 64 * wc + 32 * j + l32;
-                const int pos = (2 * q + half) ^ (row & 15);
-                bq[j] = *reinterpret_cast<const u32x4 *>(src + row * 256 + pos * 16);
-            }
-            bf16x8 a[2];
+            for (int i = 0; i < 2; ++i) {
+                const bf16x8 a = qq & 1 ? expand_spins<1>(w[i][qq >> 1], sign_mask)
+                                        : expand_spins<0>(w[i][qq >> 1], sign_mask);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = expand_spins(sw[i][qq], sign_mask);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 2; ++j) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        a[i], __builtin_bit_cast(bf16x8, bq[j]), acc[i][j], 0, 0, 0);
+                        a, __builtin_bit_cast(bf16x8, bq[qq & 1][j]), acc[i][j], 0, 0, 0);
+                    if (i == 0 && j == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (qq < 3) {
+                            read_j(bq[(qq + 1) & 1], st, qq + 1);
+                        } else {
+                            read_j(bq[0], st_next, 0);
+                            read_s(s_next, st_next);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
         }
     };
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s) stage(s, s);
-    for (int c = 0; c < nchunk; ++c) {
-        // this wave's loads of chunk c have landed (the NST-2 younger chunks may not);
+    // chunk 0 has landed in every wave; its first fragments
+    if (loads_s) wait_barrier<(NST - 2) * (JL + 1)>();
+    else wait_barrier<(NST - 2) * JL>();
+    read_j(bq[0], 0, 0);
+    read_s(sw[0], 0);
+    int st = 0, nx = NST - 1;                      // stages of chunk c and of chunk c + NST - 1
+    auto chunk = [&](int c, u32x2 (&s_now)[2], u32x2 (&s_next)[2]) {
+        // this wave's loads of chunk c + 1 have landed (the NST-3 younger chunks may not);
         // after the barrier every wave's have, and every wave is done with the stage of
         // chunk c-1, which is refilled next
-        wait_barrier<(NST - 2) * LOADS_PER_CHUNK>();
-        stage(c + NST - 1, (c + NST - 1) % NST);
-        multiply(c);
+        if (loads_s) wait_barrier<(NST - 3) * (JL + 1)>();
+        else wait_barrier<(NST - 3) * JL>();
+        stage(c + NST - 1, nx);
+        const int sn = st + 1 == NST ? 0 : st + 1;
+        multiply(st, sn, s_now, s_next);
+        st = sn;
+        nx = nx + 1 == NST ? 0 : nx + 1;
+    };
+    int c = 0;
+    for (; c + 2 <= nchunk; c += 2) {
+        chunk(c, sw[0], sw[1]);
+        chunk(c + 1, sw[1], sw[0]);
     }
+    if (c < nchunk) chunk(c, sw[0], sw[1]);
     wait_barrier<0>();     // the trailing (redundant) loads have landed in every wave and
                            // every stage read is done: the stages can take the sums
     // each k half stores its sums into its own buffer (the state waves add the two, first
@@ -254,10 +304,10 @@ __device__ __forceinline__ void matrix_step(uint8_t *lds, const Tile &tl, int nc
     wait_barrier<0>();      // partial sums stored
 }
 
-// ---- state waves: thread t (0..511) owns column t % 128 of rows 4e + t / 128 ---------
-// Row pointers are wave-uniform and advanced one row pair at a time through an opaque
-// step, so that the compiler computes each address when it is used instead of holding
-// all 64 in scalar registers.
+// ---- state waves: thread t (0..511) owns column t % BN of rows RS e + t / BN -----------
+// Addresses are the tile's uniform base plus one 32-bit lane offset that steps by rows
+// (256 rows of np <= 2^18 floats stay below 2^32 bytes).  Row pointers held in scalar
+// registers spilled: 22 scalar operations per row and 3 us more per step.
 template <typename P> __device__ __forceinline__ P *next_rows(P *p, int64_t stride) {
     P *q = p + stride;
     asm volatile("" : "+s"(q));
@@ -272,30 +322,45 @@ struct StateRegs {
 // Loads the tile's x, m and b, spread over the matrix waves' nchunk chunk barriers (a
 // few elements before each), so that this traffic shares the memory system with the
 // chunk loads instead of delaying the first chunks.  Rows past rlive are padding: they
-// are not read and take zeros.  Row pointers are wave-uniform, so that each load is a
-// scalar base plus the lane's column.  Executes nchunk barriers.  NTL: non-temporal loads
+// are not read and take zeros.  Executes nchunk barriers.  NTL: non-temporal loads
 // (the grouped batch step).
-template <bool NTL>
+template <class TL, bool NTL>
 __device__ __forceinline__ void state_load(StateRegs &st, const Tile &tl, int nchunk, int t) {
-    const int col = t & (BN - 1);
-    const int rsub = __builtin_amdgcn_readfirstlane(t >> 7);
+    constexpr int RS = TL::RS;
+    const int col = t & (TL::BN - 1);
+    const int rsub = __builtin_amdgcn_readfirstlane(t / TL::BN);
     const int per = (SR + nchunk - 1) / nchunk;
-    const float *xr = tl.x + (tl.R0 + rsub) * tl.np + tl.I0;
-    const float *mr = tl.m + (tl.R0 + rsub) * tl.np + tl.I0;
-    int passed = 0;
+    const char *xb = reinterpret_cast<const char *>(tl.x + tl.R0 * tl.np + tl.I0);
+    const char *mb = reinterpret_cast<const char *>(tl.m + tl.R0 * tl.np + tl.I0);
+    uint32_t o = 4u * ((uint32_t)rsub * (uint32_t)tl.np + (uint32_t)col);
+    const uint32_t step = 4u * RS * (uint32_t)tl.np;
+    auto get = [](const char *b, uint32_t off) {
+        const float *p = reinterpret_cast<const float *>(b + off);
+        return NTL ? __builtin_nontemporal_load(p) : *p;
+    };
+    int passed = 0, left = per;
+    auto rows = [&](auto full) {
 #pragma unroll
-    for (int e = 0; e < SR; ++e) {
-        if (e > 0 && e % per == 0 && passed < nchunk) {
-            barrier();
-            ++passed;
+        for (int e = 0; e < SR; ++e) {
+            if (left == 0 && passed < nchunk) {
+                barrier();
+                ++passed;
+                left = per;
+            }
+            --left;
+            // padding rows (uniform per wave) are not read: they start from zero each step
+            if (decltype(full)::value || tl.R0 + RS * e + rsub < tl.rlive) {
+                st.xv[e] = get(xb, o);
+                st.mv[e] = get(mb, o);
+            } else {
+                st.xv[e] = 0.0f;
+                st.mv[e] = 0.0f;
+            }
+            o += step;
         }
-        // padding rows (uniform per wave) are not read: they start from zero each step
-        const bool live = tl.R0 + 4 * e + rsub < tl.rlive;
-        st.xv[e] = live ? (NTL ? __builtin_nontemporal_load(&xr[col]) : xr[col]) : 0.0f;
-        st.mv[e] = live ? (NTL ? __builtin_nontemporal_load(&mr[col]) : mr[col]) : 0.0f;
-        xr = next_rows(xr, 4 * tl.np);
-        mr = next_rows(mr, 4 * tl.np);
-    }
+    };
+    if (tl.R0 + TL::BM <= tl.rlive) rows(std::true_type{});
+    else rows(std::false_type{});
     st.bi = tl.b[tl.I0 + col];
     for (; passed < nchunk; ++passed) barrier();   // the remaining chunks
 }
@@ -307,68 +372,58 @@ __device__ __forceinline__ void state_collect(StateRegs &st) {
     asm volatile("" ::"v"(st.bi));
 }
 
-// The PA update of the tile from the field sums in LDS, then the new spins as pair words.
+// The PA update of the tile from the field sums in LDS, then the new spins as sign bits.
 // Rows are taken in groups of 8 with no branch inside the loop (the field reads of a group
-// are issued together); lane 2g + ln keeps the ballot of row g of each group, and after
-// the loop lanes 0..15 turn them into 16-byte stores (the even (ln = 0) or odd (ln = 1)
-// bytes of their row).  With h_last the fields are stored by a second pass.  Executes no
-// barrier.
+// are issued together); lane e keeps the ballot of the wave's row e (64 variables: half a
+// chunk), and after the loop lanes 0..31 store them.  With h_last the fields are stored by a
+// second pass.  Executes no barrier.
+template <class TL>
 __device__ __forceinline__ void state_update(StateRegs &st, const Tile &tl, const float *hs,
                                              uint32_t *__restrict__ s_nxt,
-                                             float *__restrict__ h_last, int t, int wave,
-                                             int lane, float lt, float eta, float alpha) {
-    const int col = t & (BN - 1);
-    const int rsub = __builtin_amdgcn_readfirstlane(t >> 7);
-    {
-    const int u_mine = (lane >> 1) & 7;
-    uint64_t mine[SR / 8];
+                                             float *__restrict__ h_last, int t, int lane,
+                                             float lt, float eta, float alpha) {
+    constexpr int RS = TL::RS, HS = TL::HS, BM = TL::BM;
+    const int col = t & (TL::BN - 1);
+    const int rsub = __builtin_amdgcn_readfirstlane(t / TL::BN);
+    const int u_mine = lane & 7, g_mine = lane >> 3;
+    uint64_t mine = 0;
 #pragma unroll
     for (int g = 0; g < SR / 8; ++g) {
         float hv[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int k = (4 * (8 * g + u) + rsub) * HS + col;
+            const int k = (RS * (8 * g + u) + rsub) * HS + col;
             hv[u] = hs[k] + hs[BM * HS + k];          // first k half + second k half
         }
         uint64_t bal[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int e = 8 * g + u;
-            const bool live = tl.R0 + 4 * e + rsub < tl.rlive;      // uniform per wave
+            const bool live = tl.R0 + RS * e + rsub < tl.rlive;      // uniform per wave
             const float h = __fadd_rn(__fmul_rn(hv[u], tl.scale), st.bi);
             pa_update(h, lt, eta, alpha, st.xv[e], st.mv[e]);
             bal[u] = __ballot(live && st.xv[e] < 0.0f);
         }
-        mine[g] = bal[0];
+        uint64_t mg = bal[0];
 #pragma unroll
-        for (int k = 1; k < 8; ++k) mine[g] = u_mine == k ? bal[k] : mine[g];
+        for (int k = 1; k < 8; ++k) mg = u_mine == k ? bal[k] : mg;
+        mine = g_mine == g ? mg : mine;
     }
-    // this wave covers variables 64 c2 .. 64 c2 + 63 of the chunk: ballot byte k of a row
-    // is word 8 (k & 1) + 4 c2 + k / 2 of the replica's 16 pair words
-    if (lane < 16) {
-        const int c2 = (wave - MW) & 1;
-        const int ln = lane & 1;
-        uint32_t *wrow = s_nxt + ((tl.I0 / KC) * tl.Rp + tl.R0 + rsub) * 16 + 4 * c2 + 8 * ln;
-#pragma unroll
-        for (int g = 0; g < SR / 8; ++g) {
-            u32x4 wq;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                wq[k] = spin_pair((uint32_t)(mine[g] >> (8 * (2 * k + ln))) & 0xFFu);
-            *reinterpret_cast<u32x4 *>(wrow + 64 * (8 * g + u_mine)) = wq;
-        }
-    }
-    }
+    // this wave covers variables v0 .. v0 + 63 (half a chunk: two of its four words)
+    const int64_t v0 = tl.I0 + 64 * __builtin_amdgcn_readfirstlane((t & (TL::BN - 1)) >> 6);
+    const int64_t r = tl.R0 + RS * lane + rsub;
+    if (lane < SR && r < tl.Rp)
+        *reinterpret_cast<u32x2 *>(s_nxt + ((v0 / KC) * tl.Rp + r) * 4 + (v0 % KC) / 32) =
+            (u32x2){(uint32_t)mine, (uint32_t)(mine >> 32)};
     if (h_last) {
         float *hr = h_last + (tl.R0 + rsub) * tl.np + tl.I0;
 #pragma unroll
         for (int e = 0; e < SR; ++e) {
-            if (tl.R0 + 4 * e + rsub < tl.rlive)
-                hr[col] = __fadd_rn(__fmul_rn(hs[(4 * e + rsub) * HS + col] +
-                                                  hs[BM * HS + (4 * e + rsub) * HS + col],
-                                              tl.scale),
-                                    st.bi);
-            hr = next_rows(hr, 4 * tl.np);
+            if (tl.R0 + RS * e + rsub < tl.rlive) {
+                const int k = (RS * e + rsub) * HS + col;
+                hr[col] = __fadd_rn(__fmul_rn(hs[k] + hs[BM * HS + k], tl.scale), st.bi);
+            }
+            hr = next_rows(hr, RS * tl.np);
         }
     }
 }
@@ -376,30 +431,36 @@ __device__ __forceinline__ void state_update(StateRegs &st, const Tile &tl, cons
 // NT: non-temporal stores.  Measured: 1.6 % faster for the single-instance step; for the
 // grouped batch step (a batch's state, couplings and spins are more than the caches hold
 // between steps) non-temporal stores and loads (NTL in state_load) together 6 % faster.
-template <bool NT>
+template <class TL, bool NT>
 __device__ __forceinline__ void state_store(const StateRegs &st, const Tile &tl, int t) {
-    const int col = t & (BN - 1);
-    const int rsub = __builtin_amdgcn_readfirstlane(t >> 7);
-    float *xr = tl.x + (tl.R0 + rsub) * tl.np + tl.I0;
-    float *mr = tl.m + (tl.R0 + rsub) * tl.np + tl.I0;
+    constexpr int RS = TL::RS;
+    const int col = t & (TL::BN - 1);
+    const int rsub = __builtin_amdgcn_readfirstlane(t / TL::BN);
+    char *xb = reinterpret_cast<char *>(tl.x + tl.R0 * tl.np + tl.I0);
+    char *mb = reinterpret_cast<char *>(tl.m + tl.R0 * tl.np + tl.I0);
+    uint32_t o = 4u * ((uint32_t)rsub * (uint32_t)tl.np + (uint32_t)col);
+    const uint32_t step = 4u * RS * (uint32_t)tl.np;
+    auto put = [](char *b, uint32_t off, float v) {
+        float *p = reinterpret_cast<float *>(b + off);
+        if (NT) __builtin_nontemporal_store(v, p);
+        else *p = v;
+    };
+    auto rows = [&](auto full) {
 #pragma unroll
-    for (int e = 0; e < SR; ++e) {
-        if (tl.R0 + 4 * e + rsub < tl.rlive) {
-            if (NT) {
-                __builtin_nontemporal_store(st.xv[e], &xr[col]);
-                __builtin_nontemporal_store(st.mv[e], &mr[col]);
-            } else {
-                xr[col] = st.xv[e];
-                mr[col] = st.mv[e];
+        for (int e = 0; e < SR; ++e) {
+            if (decltype(full)::value || tl.R0 + RS * e + rsub < tl.rlive) {
+                put(xb, o, st.xv[e]);
+                put(mb, o, st.mv[e]);
             }
+            o += step;
         }
-        xr = next_rows(xr, 4 * tl.np);
-        mr = next_rows(mr, 4 * tl.np);
-    }
+    };
+    if (tl.R0 + TL::BM <= tl.rlive) rows(std::true_type{});
+    else rows(std::false_type{});
 }
 
 // One PA step of one BF16 tile: matrix and state waves side by side.
-template <bool NT, bool NTL = false>
+template <class TL, bool NT, bool NTL = false>
 __device__ __forceinline__ void mfma_tile_step(uint8_t *lds, const Tile &tl,
                                                const uint32_t *__restrict__ s_cur,
                                                uint32_t *__restrict__ s_nxt,
@@ -411,28 +472,165 @@ __device__ __forceinline__ void mfma_tile_step(uint8_t *lds, const Tile &tl,
     if (wave >= MW) {
         const int t = tid - MW * 64;
         StateRegs st;
-        state_load<NTL>(st, tl, nchunk, t);
+        barrier();                                     // chunk 0 landed
+        state_load<TL, NTL>(st, tl, nchunk, t);
         barrier();                                     // stages drained
         barrier();                                     // partial sums stored
         state_collect(st);
-        state_update(st, tl, reinterpret_cast<const float *>(lds), s_nxt, h_last, t, wave, lane,
-                     lt, eta, alpha);
-        state_store<NT>(st, tl, t);
+        state_update<TL>(st, tl, reinterpret_cast<const float *>(lds), s_nxt, h_last, t, lane, lt,
+                         eta, alpha);
+        state_store<TL, NT>(st, tl, t);
         return;
     }
-    matrix_step(lds, tl, nchunk, s_cur, wave, lane);
+    MatrixStep<TL>::run(lds, tl, nchunk, s_cur, wave, lane);
 }
 
+// Workgroup k of a launch runs on compute die k mod 8; the tiles go to the dies in
+// consecutive runs with the replicas fastest, so that the replica tiles of one block of
+// variables, which read the same rows of J, share a die's L2 whatever their number
+// (n = 3968, 31 blocks of 128: 37.4 us per step against 51.7 with one block after the other
+// round the dies).  False: no tile.
+__device__ __forceinline__ bool die_tile(int64_t gx, int64_t gy, int64_t &ix, int64_t &iy) {
+    const int64_t pos = (blockIdx.x & 7) * (int64_t)(gridDim.x >> 3) + (blockIdx.x >> 3);
+    ix = pos / gy;
+    iy = pos - ix * gy;
+    return ix < gx;
+}
+unsigned die_grid(int64_t gx, int64_t gy) { return (unsigned)((gx * gy + 7) / 8 * 8); }
+
+template <class TL>
 __global__ void __launch_bounds__(THREADS, 1) k_mfma_step(
     int64_t Rp, int64_t np, int64_t rlive, const uint16_t *__restrict__ Jb,
     const float *__restrict__ b, const CanonScalars *__restrict__ sc,
     const uint32_t *__restrict__ s_cur, uint32_t *__restrict__ s_nxt, float *__restrict__ x,
     float *__restrict__ m, float *__restrict__ h_last, int t, const float *__restrict__ lam,
     float eta, float alpha) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
-    const Tile tl{np, Rp, (int64_t)blockIdx.x * BN, (int64_t)blockIdx.y * BM, rlive, Jb, b,
-                  sc->scale, x, m};
-    mfma_tile_step<true>(lds, tl, s_cur, s_nxt, h_last, lam[t], eta, alpha);
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TL::LDS];
+    int64_t ix, iy;
+    if (!die_tile(np / TL::BN, (rlive + TL::BM - 1) / TL::BM, ix, iy)) return;
+    const Tile tl{np, Rp, ix * TL::BN, iy * TL::BM, rlive, Jb, b, sc->scale, x, m};
+    mfma_tile_step<TL, true>(lds, tl, s_cur, s_nxt, h_last, lam[t], eta, alpha);
+}
+
+// ---- small tiles: 32 variables x 32 FR replicas -------------------------------------------
+// The 128 x 128 tiles leave most compute units idle for smaller instances (n = 1001, R =
+// 200: 16 workgroups).  Here a workgroup is two waves, the two k halves of the big tile
+// (chunk steps 0..3 and 4..7), each with FR accumulators of 32 x 32 over the whole
+// reduction, so that every sum is formed in the big tile's order and its bits are the
+// same.  What bounds such a step is the latency of its loads, not their volume: J and
+// the sign bits go from global memory straight to registers (a lane's 64 bytes of a J row
+// and 8 of its replica's 16 bytes of signs per chunk), D chunks ahead, with no LDS and no
+// barrier in the loop.  At the end each wave hands half of its rows' sums to the other and
+// updates the other half of the rows.
+template <int FR, int D>
+__global__ void __launch_bounds__(128, 1) k_mfma_small(
+    int64_t Rp, int64_t np, int64_t rlive, const uint16_t *__restrict__ Jb,
+    const float *__restrict__ b, const CanonScalars *__restrict__ sc,
+    const uint32_t *__restrict__ s_cur, uint32_t *__restrict__ s_nxt, float *__restrict__ x,
+    float *__restrict__ m, float *__restrict__ h_last, int t, const float *__restrict__ lam,
+    float eta, float alpha) {
+    __shared__ float ex[FR][2][8][64];
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int kh = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t ix, iy;
+    if (!die_tile(np / 32, (rlive + 32 * FR - 1) / (32 * FR), ix, iy)) return;
+    const int64_t I0 = ix * 32, R0 = iy * (32 * FR);
+    const int nchunk = (int)(np / KC);
+    const uint16_t *Jr = Jb + (I0 + l32) * np + 64 * kh + 8 * half;
+    const uint32_t *Sr = s_cur + (R0 + l32) * 4 + 2 * kh;
+    // rows updated by this wave: sums 8 kh .. 8 kh + 7 of each lane
+    auto row = [&](int v) { return 8 * ((8 * kh + v) >> 2) + 4 * half + (v & 3); };
+    float xv[FR][8], mv[FR][8];
+#pragma unroll
+    for (int f = 0; f < FR; ++f)
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const int64_t k = min(R0 + 32 * f + row(v), rlive - 1) * np + I0 + l32;
+            xv[f][v] = x[k];
+            mv[f][v] = m[k];
+        }
+    const float bi = b[I0 + l32], lt = lam[t], scale = sc->scale;
+    u32x4 jq[D][4];
+    u32x2 sq[D][FR];
+    auto load = [&](int d, int c) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            jq[d][q] = *reinterpret_cast<const u32x4 *>(Jr + (int64_t)c * KC + 16 * q);
+#pragma unroll
+        for (int f = 0; f < FR; ++f)
+            sq[d][f] = *reinterpret_cast<const u32x2 *>(Sr + ((int64_t)c * Rp + 32 * f) * 4);
+    };
+    uint32_t sign_mask = 0x80008000u;
+    asm volatile("" : "+v"(sign_mask));        // a VGPR whose value the compiler does not know
+    f32x16 acc[FR];
+#pragma unroll
+    for (int f = 0; f < FR; ++f)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[f][v] = 0.0f;
+    auto multiply = [&](int d) {
+        u32x2 w[FR];
+#pragma unroll
+        for (int f = 0; f < FR; ++f) w[f] = sq[d][f] >> (u32x2){8u * half, 8u * half};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int f = 0; f < FR; ++f)
+                acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    q & 1 ? expand_spins<1>(w[f][q >> 1], sign_mask)
+                          : expand_spins<0>(w[f][q >> 1], sign_mask),
+                    __builtin_bit_cast(bf16x8, jq[d][q]), acc[f], 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, min(d, nchunk - 1));
+    int c = 0;
+    for (; c + 2 * D <= nchunk; c += D)
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            multiply(d);
+            load(d, c + D + d);
+        }
+    // the last D .. 2 D - 1 chunks (all of them where there are fewer)
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (c + d < nchunk) {
+            multiply(d);
+            if (c + D + d < nchunk) load(d, c + D + d);
+        }
+    c += D;
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+        if (c + d < nchunk) multiply(d);
+#pragma unroll
+    for (int f = 0; f < FR; ++f)
+#pragma unroll
+        for (int v = 0; v < 8; ++v) ex[f][1 - kh][v][lane] = kh ? acc[f][v] : acc[f][8 + v];
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < FR; ++f) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            // first k half + second k half
+            const float own = kh ? acc[f][8 + v] : acc[f][v], other = ex[f][kh][v][lane];
+            const int64_t r = R0 + 32 * f + row(v), k = r * np + I0 + l32;
+            const bool live = r < rlive;
+            const float h = __fadd_rn(__fmul_rn(own + other, scale), bi);
+            pa_update(h, lt, eta, alpha, xv[f][v], mv[f][v]);
+            if (live) {
+                x[k] = xv[f][v];
+                m[k] = mv[f][v];
+                if (h_last) h_last[k] = h;
+            }
+            const uint64_t bal = __ballot(live && xv[f][v] < 0.0f);
+            mine = lane == v ? (uint32_t)bal : lane == 8 + v ? (uint32_t)(bal >> 32) : mine;
+        }
+        // lane q < 16: the 32 sign bits of the row of sum q % 8 in lane half q / 8
+        if (lane < 16) {
+            const int vv = 8 * kh + (lane & 7);
+            const int64_t r = R0 + 32 * f + 8 * (vv >> 2) + 4 * (lane >> 3) + (vv & 3);
+            s_nxt[((I0 / KC) * Rp + r) * 4 + (I0 % KC) / 32] = mine;
+        }
+    }
 }
 
 // Many instances in one launch: block k runs tile k of the table.  Each tile points at
@@ -440,13 +638,13 @@ __global__ void __launch_bounds__(THREADS, 1) k_mfma_step(
 __global__ void __launch_bounds__(THREADS, 1) k_mfma_grouped(const MfmaTile *__restrict__ tiles,
                                                              int t, const float *__restrict__ lam,
                                                              float eta, float alpha) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[BfSquare::LDS];
     const MfmaTile mt = tiles[blockIdx.x];
     if (mt.np == 0) return;      // filler entry of the compute-die-ordered table
     const uint32_t *cur = (t & 1) ? mt.s1 : mt.s0;
     uint32_t *nxt = (t & 1) ? mt.s0 : mt.s1;
     const Tile tl{mt.np, mt.Rp, mt.I0, mt.R0, mt.rlive, mt.Jb, mt.b, mt.sc->scale, mt.x, mt.m};
-    mfma_tile_step<true, true>(lds, tl, cur, nxt, nullptr, lam[t], eta, alpha);
+    mfma_tile_step<BfSquare, true, true>(lds, tl, cur, nxt, nullptr, lam[t], eta, alpha);
 }
 
 // ---- int8 tiles of a batch: 64 replicas x 256 variables ---------------------------------
@@ -770,7 +968,7 @@ template <bool SPARSE>
 __global__ void __launch_bounds__(THREADS, 1) k_mfma_grouped8(const MfmaTile *__restrict__ tiles,
                                                               int t, const float *__restrict__ lam,
                                                               float eta, float alpha) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS8_BYTES];
     const MfmaTile mt = tiles[blockIdx.x];
     if (mt.np == 0) return;      // filler entry of the compute-die-ordered table
     const uint8_t *cur = reinterpret_cast<const uint8_t *>((t & 1) ? mt.s1 : mt.s0);
@@ -793,20 +991,24 @@ __global__ void __launch_bounds__(256) k_mfma_pack_i8(int64_t Rp, int64_t np,
     }
 }
 
-// Pair words of the signs of x (layout above): one thread per word.
+// Sign bits of x (layout above): one thread per word.
 __global__ void __launch_bounds__(256) k_mfma_pack(int64_t Rp, int64_t np,
                                                    const float *__restrict__ x,
                                                    uint32_t *__restrict__ sw) {
-    const int64_t total = Rp * (np / 8);
+    const int64_t total = Rp * (np / 32);
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total;
          k += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t kc = k / (Rp * 16), rem = k - kc * Rp * 16;
-        const int64_t r = rem / 16, wd = rem - r * 16;
-        const int64_t h = wd >> 3, q = wd & 7;
-        const float *xr = x + r * np + KC * kc + 16 * q + 8 * h;
-        uint32_t byte = 0;
-        for (int j = 0; j < 8; ++j) byte |= (xr[j] < 0.0f ? 1u : 0u) << j;
-        sw[k] = spin_pair(byte);
+        const int64_t kc = k / (Rp * 4), rem = k - kc * Rp * 4;
+        const int64_t r = rem / 4, wd = rem - r * 4;
+        const float4 *xr = reinterpret_cast<const float4 *>(x + r * np + KC * kc + 32 * wd);
+        uint32_t bits = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float4 v = xr[j];
+            bits |= (v.x < 0.0f ? 1u : 0u) << (4 * j) | (v.y < 0.0f ? 2u : 0u) << (4 * j) |
+                    (v.z < 0.0f ? 4u : 0u) << (4 * j) | (v.w < 0.0f ? 8u : 0u) << (4 * j);
+        }
+        sw[k] = bits;
     }
 }
 
@@ -950,22 +1152,67 @@ hipError_t launch_i8s_fill(const I8sTask *tasks, int32_t ntask, int64_t max_np,
 
 hipError_t launch_mfma_pack_spins(int64_t Rp, int64_t np, const float *x, uint32_t *sbits,
                                   hipStream_t st) {
-    int64_t total = Rp * (np / 8);
+    int64_t total = Rp * (np / 32);
     int64_t g = (total + 255) / 256;
     if (g > 65536) g = 65536;
     k_mfma_pack<<<(unsigned)g, 256, 0, st>>>(Rp, np, x, sbits);
     return hipGetLastError();
 }
 
+namespace {
+template <class TL> unsigned wide_grid(int64_t np, int64_t rlive) {
+    return die_grid(np / TL::BN, (rlive + TL::BM - 1) / TL::BM);
+}
+
+// Replicas (in 32s) of the small tiles an instance runs on, 0: the 16384-element tiles.  The
+// tile with the least estimated step: a fixed part plus, per chunk of 128 variables, the
+// time of the workgroups that share a compute unit (us, fitted to steps of 256 <= n <= 4096,
+// 64 <= R <= 1024 within 10 %).  Measured, us per step:
+//   n     R     32 x 32   32 x 64   32 x 128   16384-element
+//   256   256     5.6       7.1       9.2         8.3
+//   1001  200     6.1       8.4      11.7        12.8
+//   1001  1024   12.7      11.4      12.9        13.5
+//   2048  256    12.4      10.7      15.3        18.3
+//   2048  1024   38.8      27.9      20.7        20.1
+//   4096  128    20.5      15.5      21.1        31.0
+//   4096  256    35.3      23.7      22.3        28.4
+//   4096  512    69.7      45.0      30.8        29.5
+int small_tile_replicas(int64_t np, int64_t Rp, int64_t rlive) {
+    const double nc = (double)(np / KC);
+    auto rounds = [](int64_t tiles) { return (double)((tiles + 255) / 256); };
+    double best = 7.5 + 0.66 * nc *
+                  rounds(Rp % 256 == 0 ? (np / 64) * (Rp / 256) : (np / 128) * (Rp / 128));
+    int fr = 0;
+    const double fixed[3] = {4.2, 5.7, 9.0}, chunk[3] = {0.26, 0.30, 0.40};
+    for (int k = 0; k < 3; ++k) {
+        const int64_t br = 32 << k;
+        const double t = fixed[k] + chunk[k] * nc * rounds((np / 32) * ((rlive + br - 1) / br));
+        if (t < best) {
+            best = t;
+            fr = 1 << k;
+        }
+    }
+    return fr;
+}
+}  // namespace
+
 hipError_t launch_mfma_step(int64_t Rp, int64_t np, int64_t rlive, const uint16_t *Jb,
                             const float *b, const CanonScalars *sc, const uint32_t *s_cur,
                             uint32_t *s_nxt, float *x, float *m, float *h_last, int32_t t,
                             const float *lam, float eta, float alpha, hipStream_t st) {
-    if (Rp % BM || np % MF_NPAD || np <= 0 || rlive < 1 || rlive > Rp)
+    if (Rp % MF_BM || np % MF_NPAD || np <= 0 || rlive < 1 || rlive > Rp)
         return hipErrorInvalidValue;
-    dim3 grid((unsigned)(np / BN), (unsigned)(Rp / BM));
-    k_mfma_step<<<grid, THREADS, 0, st>>>(Rp, np, rlive, Jb, b, sc, s_cur, s_nxt, x, m, h_last,
-                                          t, lam, eta, alpha);
+    const int fr = small_tile_replicas(np, Rp, rlive);
+    const unsigned gs = die_grid(np / 32, (rlive + 32 * fr - 1) / (32 * std::max(fr, 1)));
+#define QPA_BF(KERNEL, GRID, N)                                                             \
+    KERNEL<<<GRID, N, 0, st>>>(Rp, np, rlive, Jb, b, sc, s_cur, s_nxt, x, m, h_last, t, lam, \
+                               eta, alpha)
+    if (fr == 1) QPA_BF((k_mfma_small<1, 8>), gs, 128);
+    else if (fr == 2) QPA_BF((k_mfma_small<2, 8>), gs, 128);
+    else if (fr == 4) QPA_BF((k_mfma_small<4, 6>), gs, 128);
+    else if (Rp % 256 == 0) QPA_BF(k_mfma_step<BfWide>, wide_grid<BfWide>(np, rlive), THREADS);
+    else QPA_BF(k_mfma_step<BfSquare>, wide_grid<BfSquare>(np, rlive), THREADS);
+#undef QPA_BF
     return hipGetLastError();
 }
 

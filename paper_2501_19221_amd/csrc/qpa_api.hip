@@ -199,7 +199,7 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     switch (pl.path) {
         case Path::DenseResident: sbytes = 0; break;
         case Path::DenseTiled: sbytes = sizeof(float) * Rp * n; break;
-        case Path::DenseMfma: sbytes = sizeof(uint32_t) * Rp * (np / 8); break;
+        case Path::DenseMfma: sbytes = sizeof(uint32_t) * Rp * (np / 32); break;
         case Path::Csr:
         case Path::CsrResident:
         case Path::CsrBinned:
@@ -948,7 +948,7 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
             ds.o_bfp = tk(sizeof(float) * (size_t)np);
             ds.o_x = tk(sizeof(float) * (size_t)(Rp * np));
             ds.o_m = tk(sizeof(float) * (size_t)(Rp * np));
-            // room for byte spins (int8 tiles), twice the pair words of BF16 tiles
+            // room for byte spins (int8 tiles), eight times the sign bits of BF16 tiles
             ds.o_s0 = tk((size_t)(Rp * np));
             ds.o_s1 = tk((size_t)(Rp * np));
             const int32_t it = (int32_t)((np / MF_BN) * (Rp / MF_BM));

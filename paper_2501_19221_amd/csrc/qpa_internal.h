@@ -181,9 +181,9 @@ hipError_t launch_dense_fp32_step(int64_t n, int64_t Rp, const float *J, const f
 hipError_t launch_sign_f32(int64_t count, const float *x, float *s, hipStream_t st);
 
 // BF16 matrix-core path.  Internal padded layout: x, m [Rp][np] FP32, Jb [np][np] bf16,
-// spins Rp * np / 8 uint32 "pair words" (see the step kernel), chunk-major.
-constexpr int MF_BM = 128;   // replicas per tile
-constexpr int MF_BN = 128;   // variables per tile
+// sign bits of the spins, Rp * np / 32 uint32 (see the step kernel), chunk-major.
+constexpr int MF_BM = 128;   // replicas per square tile; Rp is a multiple of this
+constexpr int MF_BN = 128;   // variables per square tile
 constexpr int MF_NPAD = 128; // np is a multiple of this (the reduction chunk)
 // Tiles of the grouped int8 step: 64 replicas x 256 variables (np a multiple of 256).
 constexpr int MF_BM8 = 64, MF_BN8 = 256;

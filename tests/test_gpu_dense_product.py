@@ -93,3 +93,25 @@ def test_dense_resident_widths(q, eng, n):
     for j in range(n):
         acc = acc + s[:, j:j + 1] * inst.dense[j][None, :]
     assert np.array_equal(host(h), acc + inst.lin[None, :])
+
+
+# BF16 matrix-core path, integer couplings (exact in BF16): tiles of 32 x 32 with one, several
+# and many chunks, of 32 x 64 and 32 x 128 replicas, of 256 x 64 and of 128 x 128, ragged in
+# both (sizes the choice by time assigns to them)
+@pytest.mark.parametrize("n,R", [(5, 3), (127, 33), (129, 70), (1000, 31), (1025, 130), (2000, 17),
+                                 (1001, 1000), (2040, 250), (4090, 250), (4090, 1000),
+                                 (4090, 1100)])
+def test_bf16_tiles(q, eng, n, R):
+    T, lam0, eta = 4, 30.0, 0.002
+    inst = gen.dense_int_ising(n, -10, 10, seed=n)
+    prob = q.Problem.from_instance(inst)
+    p = q.make_params(R, T, eta, 0.9, lam0, 0.1, 3, q.QPA_PREC_BF16)
+    say("bf16 n=%d R=%d" % (n, R))
+    out = eng.solve(prob, p, want_state=True)
+    x, m, s = host(out["x"]), host(out["m"]), host(out["spins"])
+    lam = orc.lambda_linear(T, lam0)
+    for r in sorted({0, R // 3, 2 * R // 3, R - 1}):
+        xr, mr = orc.pa_init(n, 1, 3, np.float32(0.1), r0=r)
+        orc.pa_steps_dense_int(inst.dense, inst.lin, xr, mr, 0, T, lam, eta, 0.9)
+        assert np.array_equal(x[r:r + 1], xr) and np.array_equal(m[r:r + 1], mr)
+        assert np.array_equal(s[r], np.where(xr[0] >= 0, 1, -1))
