@@ -569,91 +569,304 @@ __global__ void __launch_bounds__(256) k_export_spins_batch(const ScoreTask *__r
 // E = (H + K) / 2 with the canonical (J, b, K).
 constexpr int ER = 16;
 
-// Dense: thread = replica.  A workgroup owns EROWS rows i and walks the columns in
-// chunks of 8.  For each row and chunk it builds the table of all 256 signed sums
-//   T_i[B] = sum_{k<8} J_{i,8c+k} (bit k of B ? -1 : +1)     (diagonal excluded)
-// (from two 16-entry half tables), after which replica r's row sum over the chunk is one
-// lookup T_i[B_r] with B_r its 8 sign bits there.  Per replica it accumulates
-//   sum_i s_i (J s)_i + 2 sum_i s_i b_i = 2 H(s)
-// over its rows; the tables are FP64 (exact for integer couplings, whose rows are
-// validated below 2^24).  Spins arrive bit-packed per replica (k_spin_rowbits).
-constexpr int EROWS = 16;
+// Dense: the products J s on the matrix cores, spins expanded from sign bits, row sums
+// weighted with the spins in registers.  2 H(s) = sum_i s_i (J s)_i + 2 sum_i b_i s_i, and
+// by symmetry a block of EROWS rows needs its own columns once and those past them
+// twice: half of the products.  Integer couplings use v_mfma_f32_32x32x2_f32, whose sums
+// are exact (every row's sum of |J| is validated below 2^24); float couplings use
+// v_mfma_f64_16x16x4_f64.  A wave owns a block of rows and 64 replicas (integer) or 32
+// (float); the four waves of a workgroup take neighbouring replicas and share the block's
+// rows in the cache.  Blocks t and T - 1 - t go together (n columns past the two) and
+// ESEG workgroups split the columns of both, so that all have the same work.  J is read down its
+// columns (it is symmetric), so that a wave's loads are contiguous, EDEP groups of 16
+// columns ahead.
+// What bounds it: the matrix rate for large R n^2 (147 TFLOP/s FP32, 33 FP64), the load
+// latency and the launch for small ones.  n = 1500, R = 1024, int32: 51 us against 356
+// with 256-entry tables of signed sums per row and 8 columns in LDS; n = 4096, R = 1024,
+// float: 390 us against 850; n = 512, R = 256, float: 16 us against 93.
+constexpr int EROWS = 32, ESEG = 4, EDEP = 3;
 
+// words[i / 64][r], bit i % 64 set <=> spin i of replica r is -1 (replicas fastest: a wave reads
+// its replicas' words of a column together); one wave per replica and 4 words
 __global__ void __launch_bounds__(256) k_spin_rowbits(int64_t n, int64_t R, int64_t nw,
                                                       const int8_t *__restrict__ s,
                                                       uint64_t *__restrict__ bits) {
-    // one wave per replica; bit i%64 of word i/64 set <=> spin i is -1
     const int lane = threadIdx.x & 63;
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (r >= R) return;
-    for (int64_t w = 0; w < nw; ++w) {
-        const int64_t i = 64 * w + lane;
-        const uint64_t word = __ballot(i < n && s[r * n + i] < 0);
-        if (lane == 0) bits[r * nw + w] = word;
+    const int64_t nq = (nw + 3) / 4;
+    for (int64_t item = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; item < R * nq;
+         item += ((int64_t)gridDim.x * blockDim.x) >> 6) {
+        const int64_t r = item / nq, w0 = 4 * (item - r * nq);
+        int8_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = 64 * (w0 + u) + lane;
+            v[u] = i < n ? s[r * n + i] : (int8_t)1;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t word = __ballot(v[u] < 0);
+            if (lane == 0 && w0 + u < nw) bits[(w0 + u) * R + r] = word;
+        }
     }
 }
 
+typedef float ed_f16 __attribute__((ext_vector_type(16)));
+typedef double ed_d4 __attribute__((ext_vector_type(4)));
+
+// Part 0 or 1 of a workgroup: its row block (first row i0) and its share of that block's
+// columns (share 0 also takes the block's own columns and the field).  False: no part 1.
+__device__ __forceinline__ bool ed_block(int64_t n, int part, int &seg, int64_t &i0) {
+    const int64_t T = (n + EROWS - 1) / EROWS, p = blockIdx.x / ESEG, t = part ? T - 1 - p : p;
+    seg = (blockIdx.x + 2 * part) % ESEG;
+    i0 = t * EROWS;
+    return part == 0 || t > p;
+}
+
+// Columns [k0, k1) of segment seg of the columns past the block at i0.
+__device__ __forceinline__ void ed_range(int64_t n, int64_t i0, int seg, int64_t &k0, int64_t &k1) {
+    const int64_t a = i0 + EROWS, len = a < n ? (n - a + 15) / 16 : 0;
+    k0 = a + len * seg / ESEG * 16;
+    k1 = min(n, a + len * (seg + 1) / ESEG * 16);
+}
+
+// Integer couplings: a wave's 32 rows x 64 replicas.
 template <typename TQ>
-__global__ void __launch_bounds__(1024) k_energy_dense(int64_t n, int64_t nw,
-                                                       const TQ *__restrict__ Q,
-                                                       const int64_t *__restrict__ b_i64,
-                                                       const double *__restrict__ b_f64,
-                                                       const uint64_t *__restrict__ bits,
-                                                       int64_t R, double *__restrict__ partial) {
-    __shared__ double T[EROWS][256];
-    __shared__ double N[EROWS][2][16];
-    const int t = threadIdx.x;
-    const int64_t i0 = (int64_t)blockIdx.x * EROWS;
-    for (int64_t r0 = 0; r0 < R; r0 += 1024) {
-        const int64_t r = r0 + t;
-        const bool live = r < R;
-        const uint64_t *br = bits + (live ? r : 0) * nw;
-        double h[EROWS];
+__global__ void __launch_bounds__(256) k_energy_dense_int(int64_t n,
+                                                          const TQ *__restrict__ Q,
+                                                          const int64_t *__restrict__ b_i64,
+                                                          const uint64_t *__restrict__ bits,
+                                                          int64_t R, int64_t r_first,
+                                                          double *__restrict__ partial) {
+    const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
+    const int64_t rb = r_first + (int64_t)blockIdx.y * 256 + 64 * (threadIdx.x >> 6);
+    if (rb >= R) return;
+    const uint16_t *br[2];
 #pragma unroll
-        for (int k = 0; k < EROWS; ++k) h[k] = 0.0;
-        uint64_t word = 0;
-        for (int64_t c = 0; c < n; c += 8) {
-            if (t < EROWS * 32) {                 // half tables: 4 columns each
-                const int row = t >> 5, half = (t >> 4) & 1, e = t & 15;
-                const int64_t i = i0 + row;
-                double v = 0.0;
-                if (i < n) {
+    for (int f = 0; f < 2; ++f)
+        br[f] = reinterpret_cast<const uint16_t *>(bits + min(rb + 32 * f + l32, R - 1));
+    double tot[2] = {0.0, 0.0};
+    for (int part = 0; part < 2; ++part) {
+    int seg;
+    int64_t i0;
+    if (!ed_block(n, part, seg, i0)) break;
+    const int64_t i = i0 + l32, kl = (n - 1) / 16 * 16;      // kl: the last group of columns
+    uint32_t o[2][8];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int64_t j = c + 4 * half + k;
-                        const double q = (j < n && j != i) ? (double)Q[i * n + j] : 0.0;
-                        v += ((e >> k) & 1) ? -q : q;
-                    }
-                }
-                N[row][half][e] = v;
+    for (int e = 0; e < 8; ++e) {
+        o[0][e] = (uint32_t)((2 * e + h) * n + min(i, n - 1));
+        o[1][e] = (uint32_t)(min(2 * e + h, (int)(n - 1 - kl)) * n + min(i, n - 1));
+    }
+    ed_f16 acc[2];
+    auto clear = [&]() {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[f][v] = 0.0f;
+    };
+    // 16 columns from k (a multiple of 16): the lane's 8 couplings and its replicas' signs.
+    // Loads stay where they are written: the compiler would sink them to their use.
+    TQ q[EDEP][8];
+    uint32_t w[EDEP][2];
+    auto load = [&](int d, int64_t k) {
+        const bool last = k >= kl;                   // uniform; past the end: the last group
+        const int64_t kc = last ? kl : k;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[d][e] = (Q + kc * n)[last ? o[1][e] : o[0][e]];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) w[d][f] = (br[f] + (kc >> 6) * R * 4)[(kc >> 4) & 3];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int d, int64_t k, int64_t k1, auto diag) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int64_t j = k + 2 * e + h;
+            const bool use = j < k1 && !(decltype(diag)::value && j == i);
+            const float a = use ? (float)q[d][e] : 0.0f;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const uint32_t sg = (w[d][f] >> h) << (31 - 2 * e);
+                acc[f] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                    a, __uint_as_float((sg & 0x80000000u) | 0x3F800000u), acc[f], 0, 0, 0);
             }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < EROWS / 4; ++u) {
-                const int idx = t + 1024 * u, row = idx >> 8, e = idx & 255;
-                T[row][e] = N[row][0][e & 15] + N[row][1][e >> 4];
-            }
-            __syncthreads();
-            if ((c & 63) == 0 && live) word = br[c >> 6];
-            const int B = (int)((word >> (c & 63)) & 0xFFu);
-#pragma unroll
-            for (int k = 0; k < EROWS; ++k) h[k] += T[k][B];
         }
-        if (live) {
-            double acc = 0.0;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // this lane's rows of sum v: 8 (v / 4) + 4 h + v % 4
+    int32_t e2[2] = {0, 0};
+    auto weigh = [&](int f, auto &&val) {
+        const uint32_t sw = reinterpret_cast<const uint32_t *>(br[f])[i0 / 64 * R * 2 + i0 / 32 % 2];
+        int32_t t = 0;
 #pragma unroll
-            for (int k = 0; k < EROWS; ++k) {
-                const int64_t i = i0 + k;
-                if (i < n) {
-                    const bool neg = (br[i >> 6] >> (i & 63)) & 1u;
-                    const double bi = b_i64 ? (double)b_i64[i] : b_f64[i];
-                    const double term = h[k] + 2.0 * bi;
-                    acc += neg ? -term : term;
-                }
-            }
-            partial[(int64_t)blockIdx.x * R + r] = acc;
+        for (int v = 0; v < 16; ++v) {
+            const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+            const int32_t x = i0 + row < n ? val(v, row) : 0;
+            t += ((sw >> row) & 1u) ? -x : x;
         }
-        __syncthreads();
+        return t;
+    };
+    if (seg == 0) {
+        // the block's own columns, once, and the field
+        clear();
+        for (int64_t k = i0; k < min(i0 + EROWS, n); k += 16) {
+            load(0, k);
+            multiply(0, k, n, std::true_type{});
+        }
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+            e2[f] = weigh(f, [&](int v, int row) {
+                return (int32_t)acc[f][v] + 2 * (int32_t)b_i64[min(i0 + row, n - 1)];
+            });
+    }
+    clear();
+    int64_t k, k1;
+    ed_range(n, i0, seg, k, k1);
+    if (k < k1) {
+#pragma unroll
+        for (int d = 0; d < EDEP; ++d) load(d, k + 16 * d);
+        for (; k < k1; k += 16 * EDEP)
+#pragma unroll
+            for (int d = 0; d < EDEP; ++d) {
+                multiply(d, k + 16 * d, k1, std::false_type{});
+                load(d, k + 16 * (d + EDEP));
+            }
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        // at most 16 rows of 2 * 2^24 + 2^24 + 2 * 2^24: below 2^31
+        const int32_t t = e2[f] + 2 * weigh(f, [&](int v, int) { return (int32_t)acc[f][v]; });
+        tot[f] += (double)t + (double)__shfl_xor(t, 32);
+    }
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        const int64_t r = rb + 32 * f + l32;
+        if (h == 0 && r < R) partial[(int64_t)blockIdx.x * R + r] = tot[f];
+    }
+}
+
+// Float couplings or fields: a wave's 32 rows x 32 replicas in FP64.
+template <typename TQ>
+__global__ void __launch_bounds__(256) k_energy_dense_f64(int64_t n,
+                                                          const TQ *__restrict__ Q,
+                                                          const double *__restrict__ b_f64,
+                                                          const uint64_t *__restrict__ bits,
+                                                          int64_t R, int64_t r_first,
+                                                          double *__restrict__ partial) {
+    const int lane = threadIdx.x & 63, kq = lane >> 4, l16 = lane & 15;
+    const int64_t rb = r_first + (int64_t)blockIdx.y * 128 + 32 * (threadIdx.x >> 6);
+    if (rb >= R) return;
+    const uint16_t *br[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        br[f] = reinterpret_cast<const uint16_t *>(bits + min(rb + 16 * f + l16, R - 1));
+    }
+    double tot[2] = {0.0, 0.0};
+    for (int part = 0; part < 2; ++part) {
+    int seg;
+    int64_t i0;
+    if (!ed_block(n, part, seg, i0)) break;
+    const int64_t kl = (n - 1) / 16 * 16;                    // the last group of columns
+    uint32_t o[2][2][4];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t i = min(i0 + 16 * f + l16, n - 1);
+            o[0][f][e] = (uint32_t)((4 * e + kq) * n + i);
+            o[1][f][e] = (uint32_t)(min(4 * e + kq, (int)(n - 1 - kl)) * n + i);
+        }
+    ed_d4 acc[2][2];
+    auto clear = [&]() {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) acc[f][g] = (ed_d4){0.0, 0.0, 0.0, 0.0};
+    };
+    TQ q[EDEP][2][4];
+    uint32_t w[EDEP][2];
+    auto load = [&](int d, int64_t k) {
+        const bool last = k >= kl;
+        const int64_t kc = last ? kl : k;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[d][f][e] = (Q + kc * n)[last ? o[1][f][e] : o[0][f][e]];
+            w[d][f] = (br[f] + (kc >> 6) * R * 4)[(kc >> 4) & 3];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int d, int64_t k, int64_t k1, auto diag) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t j = k + 4 * e + kq;
+            double a[2], s[2];
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const bool use = j < k1 && !(decltype(diag)::value && j == i0 + 16 * f + l16);
+                a[f] = use ? (double)q[d][f][e] : 0.0;
+                const uint32_t sg = (w[d][f] >> kq) << (31 - 4 * e);
+                s[f] = __hiloint2double((int)((sg & 0x80000000u) | 0x3FF00000u), 0);
+            }
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+                    acc[f][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[f], s[g], acc[f][g], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // this lane's rows of sum v of row fragment f: 16 f + 4 v + kq
+    auto weigh = [&](int g, auto &&val) {
+        const uint32_t sw = reinterpret_cast<const uint32_t *>(br[g])[i0 / 64 * R * 2 + i0 / 32 % 2];
+        double t = 0.0;
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * f + 4 * v + kq;
+                const double x = i0 + row < n ? val(f, v, row) : 0.0;
+                t += ((sw >> row) & 1u) ? -x : x;
+            }
+        return t;
+    };
+    double e2[2] = {0.0, 0.0};
+    if (seg == 0) {
+        clear();
+        for (int64_t k = i0; k < min(i0 + EROWS, n); k += 16) {
+            load(0, k);
+            multiply(0, k, n, std::true_type{});
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+            e2[g] = weigh(g, [&](int f, int v, int row) {
+                return acc[f][g][v] + 2.0 * b_f64[min(i0 + row, n - 1)];
+            });
+    }
+    clear();
+    int64_t k, k1;
+    ed_range(n, i0, seg, k, k1);
+    if (k < k1) {
+#pragma unroll
+        for (int d = 0; d < EDEP; ++d) load(d, k + 16 * d);
+        for (; k < k1; k += 16 * EDEP)
+#pragma unroll
+            for (int d = 0; d < EDEP; ++d) {
+                multiply(d, k + 16 * d, k1, std::false_type{});
+                load(d, k + 16 * (d + EDEP));
+            }
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        double t = e2[g] + 2.0 * weigh(g, [&](int f, int v, int) { return acc[f][g][v]; });
+        t += __shfl_xor(t, 16);
+        t += __shfl_xor(t, 32);
+        tot[g] += t;
+    }
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const int64_t r = rb + 16 * g + l16;
+        if (kq == 0 && r < R) partial[(int64_t)blockIdx.x * R + r] = tot[g];
     }
 }
 
@@ -1153,7 +1366,8 @@ bool csr_rows_by_wave(const qpa_problem &p) {
 }
 
 int64_t energy_partial_blocks(const qpa_problem &p) {
-    if (p.format == QPA_FMT_DENSE) return (p.n + 15) / 16;
+    if (p.format == QPA_FMT_DENSE)
+        return ((p.n + EROWS - 1) / EROWS + 1) / 2 * ESEG;      // pairs of row blocks
     if (csr_rows_by_wave(p)) return (p.n + 3) / 4;
     return (p.n + 255) / 256;
 }
@@ -1172,12 +1386,25 @@ hipError_t launch_energy(const qpa_problem &p, const int64_t *b_i64, const doubl
     hipError_t e;
     if (p.format == QPA_FMT_DENSE) {
         const int64_t nw = (n + 63) / 64;
-        k_spin_rowbits<<<(unsigned)((R + 3) / 4), 256, 0, st>>>(n, R, nw, spins, words);
+        const int64_t nq = (nw + 3) / 4;
+        k_spin_rowbits<<<grid1(R * nq, 4), 256, 0, st>>>(n, R, nw, spins, words);
         e = dispatch_q(p.coupling_dtype, [&](auto tag) {
             using T = decltype(tag);
             const T *Q = static_cast<const T *>(p.dense);
-            k_energy_dense<T><<<(unsigned)nblk, 1024, 0, st>>>(n, nw, Q, is_int ? b_i64 : nullptr,
-                                                               b_f64, words, R, partial);
+            // replicas in grid rows, at most 2^15 of them a launch
+            const int64_t per = std::is_integral<T>::value && is_int ? 256 : 128;
+            for (int64_t r0 = 0; r0 < R; r0 += per << 15) {
+                const dim3 grid((unsigned)nblk,
+                                (unsigned)std::min<int64_t>((R - r0 + per - 1) / per, 1 << 15));
+                if constexpr (std::is_integral<T>::value) {
+                    if (is_int) {
+                        k_energy_dense_int<T><<<grid, 256, 0, st>>>(n, Q, b_i64, words, R, r0,
+                                                                    partial);
+                        continue;
+                    }
+                }
+                k_energy_dense_f64<T><<<grid, 256, 0, st>>>(n, Q, b_f64, words, R, r0, partial);
+            }
             return hipGetLastError();
         });
     } else {

@@ -194,7 +194,6 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_Jb = pl.path == Path::DenseMfma ? take(sizeof(uint16_t) * np * np) : 0;
     pl.o_x = state ? take(sizeof(float) * Rp * np) : 0;
     pl.o_m = state ? take(sizeof(float) * Rp * np) : 0;
-    pl.o_h = state ? take(sizeof(float) * Rp * np) : 0;
     size_t sbytes = 0;
     switch (pl.path) {
         case Path::DenseResident: sbytes = 0; break;
@@ -209,6 +208,9 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     if (!state) sbytes = 0;
     pl.o_s0 = sbytes ? take(sbytes) : 0;
     pl.o_s1 = sbytes ? take(sbytes) : 0;
+    // the last step's fields share their place with the scoring scratch: qpa_steps asks for
+    // fields and does not score
+    pl.o_h = off;
     pl.o_part = take(sizeof(double) * (size_t)pl.eblk * R);
     pl.o_ei = take(sizeof(int64_t) * R);
     pl.o_ed = take(sizeof(double) * R);
@@ -216,6 +218,7 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_best = take(sizeof(int32_t) * 4);
     pl.o_words = p.format == QPA_FMT_DENSE
                      ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64)) : 0;
+    if (state) off = std::max(off, pl.o_h + align_up(sizeof(float) * Rp * np));
     if (pl.bin_ok) {
         const size_t nnz = (size_t)std::max<int64_t>(p.nnz, 0), M = (size_t)pl.bg.M;
         pl.o_boff = take(sizeof(int32_t) * (M + 1));

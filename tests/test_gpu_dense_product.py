@@ -115,3 +115,39 @@ def test_bf16_tiles(q, eng, n, R):
         orc.pa_steps_dense_int(inst.dense, inst.lin, xr, mr, 0, T, lam, eta, 0.9)
         assert np.array_equal(x[r:r + 1], xr) and np.array_equal(m[r:r + 1], mr)
         assert np.array_equal(s[r], np.where(xr[0] >= 0, 1, -1))
+
+
+# Dense energies on the matrix cores: blocks of 32 rows (partial last ones), both column
+# segments empty or short, replica groups of 64 and 32 with a rest.  Integer energies are
+# exact; float ones are FP64 sums of n^2 terms in another order than the oracle's (error
+# below n^2 2^-53 of the sum of magnitudes)
+@pytest.mark.parametrize("n,R", [(1, 1), (31, 5), (32, 64), (33, 65), (64, 33), (65, 300), (129, 257),
+                                 (500, 70)])
+@pytest.mark.parametrize("kind", ["int_qubo", "int_ising", "float_ising", "int8_float_field"])
+def test_dense_energies(q, eng, n, R, kind):
+    import torch
+    rng = np.random.default_rng(n + R)
+    if kind == "int_qubo":
+        inst = gen.dense_int_qubo(n, -10, 10, seed=n)
+    elif kind == "int_ising":
+        inst = gen.dense_int_ising(n, -1000, 1000, seed=n)
+    else:
+        inst = gen.sk_ising(n, 0.1, seed=n)
+        if kind == "int8_float_field":
+            inst.dense = gen.dense_int_ising(n, -9, 9, seed=n).dense.astype(np.int8)
+    s = (2 * rng.integers(0, 2, size=(R, n)) - 1).astype(np.int8)
+    say("energies %s n=%d R=%d" % (kind, n, R))
+    p = q.make_params(R, 0, 0.1, 0.8, 1.0)
+    e, ei, best = eng.energy(q.Problem.from_instance(inst), p, torch.from_numpy(s).cuda())
+    e = host(e)
+    if kind == "int_qubo":
+        ref = np.array([orc.qubo_energy_int(inst.dense, inst.lin, (v > 0).astype(np.int8)) for v in s])
+    else:
+        D, b, S = inst.dense.astype(np.float64), inst.lin.astype(np.float64), s.astype(np.float64)
+        ref = 0.5 * ((S @ D) * S).sum(1) + S @ b
+    if kind.startswith("int_"):
+        assert np.array_equal(host(ei), ref.astype(np.int64)) and np.array_equal(e, ref)
+    else:
+        bound = (np.abs(D).sum() + np.abs(b).sum()) * n * n * 2.0 ** -52
+        assert np.max(np.abs(e - ref)) <= bound
+    assert int(host(best)[0]) == int(np.argmin(e))
