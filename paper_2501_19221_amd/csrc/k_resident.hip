@@ -23,7 +23,11 @@
 // entry and replica pair.  The total is A_0 + 2^16 A_1 exactly, whatever the signs of the
 // partial sums.  The cached entries are padded with zero weights, so the integer walk has
 // no per-entry branch.
+// Rows whose sum of |w| stays below 2^8 (k_csr_resident8, such as +-1 graphs) pack four
+// replicas a word: see there.
 #include "qpa_internal.h"
+
+#include <type_traits>
 
 namespace qpa {
 namespace {
@@ -284,6 +288,253 @@ __global__ void __launch_bounds__(RT) k_csr_resident(
     }
 }
 
+// ---- rows with sum of |w| below 2^8: four replicas per 32-bit word ---------------------------
+// The kernel above is bound by its vector instructions (about 25 per update at n = 2048,
+// G = 4, 6 entries a row).  Here a variable's spins are one word with a 0 / 1 byte per
+// replica, read as it is (no table), and with A as above (now below 2^8) one packed
+// v_pk_mad_u16 by the weight in both halves adds an entry for four replicas: each half
+// holds A_0 + 2^8 A_1 modulo 2^16, exact at the end whatever the partial sums.  Then per
+// update: v_cvt_f32_ubyte and one fused multiply-add for the field (sum |w| + b - 2 A, all
+// exact integers below 2^24), the seven operations of the definition, and 1.25 to gather the
+// four signs (byte permutes of the sign bytes; a -0.0 would count as negative there, so
+// the state's -0.0 are loaded as +0.0, and x + m' never makes one).  CACHE entries of each
+// row are in registers; waves whose rows hold at most 6 skip the rest.
+// The second spin buffer lies at a constant offset, so that both copies of the step share
+// their address registers; the schedule is loaded 64 steps at a time and broadcast.  n = 2048,
+// R = 1024, 6 entries a row: 0.845 us a step against 1.66 for the kernel above; n = 512:
+// 0.33 against 0.59; n = 4000, 3 entries a row: 1.43 against 2.23.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pk_mad(uint32_t w2, uint32_t s, uint32_t acc) {
+    const u16x2 r = __builtin_bit_cast(u16x2, w2) * __builtin_bit_cast(u16x2, s) +
+                    __builtin_bit_cast(u16x2, acc);
+    return __builtin_bit_cast(uint32_t, r);
+}
+
+// bit 0 of byte g <- sign bit of x[g]
+__device__ __forceinline__ uint32_t sign_bytes(const float *x, int count) {
+    auto u = [&](int g) { return g < count ? __float_as_uint(x[g]) : 0u; };
+    // byte 3 of two words each, then the two pairs
+    const uint32_t a = __builtin_amdgcn_perm(u(1), u(0), 0x0C0C0703u);
+    if (count <= 2) return (a >> 7) & 0x0101u;
+    const uint32_t b = __builtin_amdgcn_perm(u(3), u(2), 0x07030C0Cu);
+    return ((a | b) >> 7) & 0x01010101u;
+}
+
+// the second spin buffer's LDS address: a constant, so that both are offsets of one address
+constexpr int RES8_BUF = 32 * 1024;
+constexpr size_t res8_lds(int64_t n, int64_t nnz, int G) {
+    return RES8_BUF + (size_t)n * 4 * (size_t)((G + 3) / 4) + sizeof(int32_t) * (size_t)(n + 1) +
+           6 * (size_t)nnz + 16;
+}
+constexpr bool res8_fits(int64_t n, int64_t nnz, int G) {
+    return n * 4 * ((G + 3) / 4) <= RES8_BUF && res8_lds(n, nnz, G) <= RES_MAX_LDS;
+}
+
+// LDS: spins [n][NW] uint32 | at RES8_BUF the second spins | rp [n+1] int32 | w [nnz] int32 |
+//      col [nnz] uint16
+template <int G, int VPT>
+__global__ void __launch_bounds__(RT) k_csr_resident8(
+    int32_t n, int32_t nnz, int64_t R, int64_t Rp, const int32_t *__restrict__ rp_g,
+    const void *__restrict__ col_g, int32_t col_dt, const void *__restrict__ w_g, int32_t w_dt,
+    int32_t skip_diag, const float *__restrict__ b, float *__restrict__ x,
+    float *__restrict__ m, float *__restrict__ h_last, int32_t t0, int32_t t1,
+    const float *__restrict__ lam, float eta, float alpha) {
+    constexpr int NW = (G + 3) / 4;          // spin words per variable
+    constexpr int GW = G < 4 ? G : 4;        // replicas per word
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    uint32_t *sp = reinterpret_cast<uint32_t *>(lds);
+    int32_t *rp = reinterpret_cast<int32_t *>(sp + RES8_BUF / 4 + (size_t)n * NW);
+    int32_t *wi = rp + (n + 1);
+    uint16_t *col = reinterpret_cast<uint16_t *>(wi + nnz);
+    const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;   // VPT * nt >= n
+    const int64_t r0 = (int64_t)blockIdx.x * G;
+
+    for (int32_t k = tid; k <= n; k += nt) rp[k] = rp_g[k];
+    for (int32_t k = tid; k < nnz; k += nt) {
+        col[k] = (uint16_t)(col_dt == QPA_I16 ? (int32_t) static_cast<const int16_t *>(col_g)[k]
+                                              : static_cast<const int32_t *>(col_g)[k]);
+        wi[k] = ld_as<int32_t>(w_g, w_dt, k);
+    }
+
+    constexpr int CACHE = (16 / VPT) < 8 ? (16 / VPT) : 8;
+    int32_t cj[VPT][CACHE];      // LDS word of a cached entry's spins
+    uint32_t cw[VPT][CACHE];     // its weight in both halves
+    int32_t crest[VPT], cend[VPT];
+    uint32_t cneg[VPT];          // sum over w < 0 of |w|, in each byte lane's place
+    float hb[VPT];               // sum of |w| plus the field
+    float xs[VPT][G], ms[VPT][G];
+    int most = 0;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * nt;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            xs[u][g] = 0.0f;
+            ms[u][g] = 0.0f;
+            if (i < n && r0 + g < R) {
+                xs[u][g] = __fadd_rn(x[(int64_t)i * Rp + r0 + g], 0.0f);
+                ms[u][g] = m[(int64_t)i * Rp + r0 + g];
+            }
+        }
+        if (i < n)
+#pragma unroll
+            for (int p = 0; p < NW; ++p) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int g = 0; g < GW; ++g) word |= (xs[u][4 * p + g] < 0.0f ? 1u : 0u) << (8 * g);
+                sp[(size_t)i * NW + p] = word;
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * nt;
+        int32_t cnt = 0, k = 0, k1 = 0, sum = 0;
+        if (i < n) {
+            k = rp[i];
+            k1 = rp[i + 1];
+        }
+#pragma unroll
+        for (int c = 0; c < CACHE; ++c) {
+            cj[u][c] = 0;
+            cw[u][c] = 0u;
+        }
+        cneg[u] = 0u;
+        for (int32_t kk = k; kk < k1; ++kk) {
+            if (skip_diag && col[kk] == i) continue;
+            const int32_t a = wi[kk] < 0 ? -wi[kk] : wi[kk];
+            sum += a;
+            if (wi[kk] < 0) cneg[u] += (uint32_t)a * 0x01010101u;
+        }
+        hb[u] = i < n ? __fadd_rn((float)sum, b[i]) : 0.0f;
+        for (; k < k1 && cnt < CACHE; ++k) {
+            const int32_t j = col[k];
+            if (skip_diag && j == i) continue;
+#pragma unroll
+            for (int c = 0; c < CACHE; ++c)
+                if (c == cnt) {
+                    cj[u][c] = j * NW;
+                    cw[u][c] = ((uint32_t)wi[k] & 0xFFFFu) * 0x10001u;
+                }
+            ++cnt;
+        }
+        crest[u] = k;
+        cend[u] = k1;
+        most = max(most, cnt);
+    }
+    bool longer = false;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) longer = longer || crest[u] < cend[u];
+    const bool few = __ballot(most > 6) == 0, rest = __ballot(longer) != 0;   // per wave
+
+    // one step from buffer CUR into the other; NC entries of each row from the registers
+    auto step = [&](auto nc, auto cur, auto keep, float lt) {
+        constexpr int NC = decltype(nc)::value, CUR = decltype(cur)::value;
+        const uint32_t *s_now = sp + CUR * (RES8_BUF / 4);
+        uint32_t *s_nxt = sp + (CUR ^ 1) * (RES8_BUF / 4);
+        uint32_t acc[VPT][NW], s[VPT][NC][NW];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int u = 0; u < VPT; ++u)
+#pragma unroll
+                for (int p = 0; p < NW; ++p) s[u][c][p] = s_now[cj[u][c] + p];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int u = 0; u < VPT; ++u)
+#pragma unroll
+                for (int p = 0; p < NW; ++p)
+                    acc[u][p] = pk_mad(cw[u][c], s[u][c][p], c == 0 ? cneg[u] : acc[u][p]);
+        if (rest) {
+#pragma unroll
+            for (int u = 0; u < VPT; ++u)
+                for (int32_t k = crest[u]; k < cend[u]; ++k) {
+                    const int32_t j = col[k];
+                    if (skip_diag && j == tid + u * nt) continue;
+                    const uint32_t w2 = ((uint32_t)wi[k] & 0xFFFFu) * 0x10001u;
+#pragma unroll
+                    for (int p = 0; p < NW; ++p)
+                        acc[u][p] = pk_mad(w2, s_now[j * NW + p], acc[u][p]);
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int32_t i = tid + u * nt;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float a = (float)((acc[u][g >> 2] >> (8 * (g & 3))) & 0xFFu);
+                const float h = __fmaf_rn(-2.0f, a, hb[u]);
+                const float gr = __fadd_rn(__fmul_rn(lt, xs[u][g]), h);
+                const float mn = __fsub_rn(__fmul_rn(alpha, ms[u][g]), __fmul_rn(eta, gr));
+                ms[u][g] = mn;
+                // fmin(1, fmax(-1, y)), also for a NaN (-1)
+                xs[u][g] = __builtin_amdgcn_fmed3f(__fadd_rn(xs[u][g], mn), -1.0f, 1.0f);
+                if (decltype(keep)::value && i < n && r0 + g < R)
+                    h_last[(int64_t)i * Rp + r0 + g] = h;
+            }
+            if (i < n)
+#pragma unroll
+                for (int p = 0; p < NW; ++p)
+                    s_nxt[(size_t)i * NW + p] = sign_bytes(&xs[u][4 * p], GW);
+        }
+        __syncthreads();
+    };
+    auto run = [&](auto nc) {
+        std::integral_constant<int, 0> b0;
+        std::integral_constant<int, 1> b1;
+        const int32_t te = h_last ? t1 - 1 : t1;      // steps that keep no field
+        int32_t t = t0;
+        for (; t < te; t += 64) {                     // the schedule 64 steps at a time
+            const float lv = t + lane < t1 ? lam[t + lane] : 0.0f;
+            auto l = [&](int k) {
+                return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv), k));
+            };
+            const int cnt = min(64, te - t);
+            int k = 0;
+            for (; k + 2 <= cnt; k += 2) {
+                step(nc, b0, std::false_type{}, l(k));
+                step(nc, b1, std::false_type{}, l(k + 1));
+            }
+            if (k < cnt) step(nc, b0, std::false_type{}, l(k));    // only the last 64 steps
+        }
+        if (h_last) {
+            if ((te - t0) & 1) step(nc, b1, std::true_type{}, lam[te]);
+            else step(nc, b0, std::true_type{}, lam[te]);
+        }
+    };
+    if (few) run(std::integral_constant<int, CACHE < 6 ? CACHE : 6>{});
+    else run(std::integral_constant<int, CACHE>{});
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * nt;
+        if (i >= n) continue;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (r0 + g < R) {
+                x[(int64_t)i * Rp + r0 + g] = xs[u][g];
+                m[(int64_t)i * Rp + r0 + g] = ms[u][g];
+            }
+    }
+}
+
+template <int G, int VPT>
+hipError_t launch_res8(const CsrView &c, int64_t R, int64_t Rp, const float *b, float *x, float *m,
+                       float *h_last, int32_t t0, int32_t t1, const float *lam, float eta,
+                       float alpha, hipStream_t st) {
+    const size_t lds = res8_lds(c.n, c.nnz, G);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_csr_resident8<G, VPT>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipGetLastError();
+    // no more waves than the variables need: a second block then fits beside a small one
+    const unsigned nt = 64u * (unsigned)((c.n + 64 * VPT - 1) / (64 * VPT));
+    k_csr_resident8<G, VPT><<<(unsigned)((R + G - 1) / G), nt, lds, st>>>(
+        (int32_t)c.n, (int32_t)c.nnz, R, Rp, c.rp, c.col, c.col_dt, c.w, c.w_dt,
+        c.skip_diag ? 1 : 0, b, x, m, h_last, t0, t1, lam, eta, alpha);
+    return hipGetLastError();
+}
+
 template <int G, int VPT, bool INT, bool SW>
 hipError_t launch_one(const CsrView &c, int64_t R, int64_t Rp, const float *b, float *x,
                       float *m, float *h_last, int32_t t0, int32_t t1, const float *lam,
@@ -301,10 +552,15 @@ hipError_t launch_one(const CsrView &c, int64_t R, int64_t Rp, const float *b, f
 }
 
 template <int G, int VPT>
-hipError_t launch_g_v(const CsrView &c, int64_t R, int64_t Rp, bool is_int, bool small_w,
+hipError_t launch_g_v(const CsrView &c, int64_t R, int64_t Rp, bool is_int, double max_row,
                       const float *b, float *x, float *m, float *h_last, int32_t t0, int32_t t1,
                       const float *lam, float eta, float alpha, size_t lds, hipStream_t st) {
-    if (is_int && small_w)
+    // max_row bounds every row's sum of |w|.  The byte form is the faster one at every size
+    // and group measured (1.2x to 2x); its LDS (two spin words a variable, the second at a
+    // fixed offset) may not fit where the 16-bit form's bits do.
+    if (is_int && max_row < 256.0 && res8_fits(c.n, c.nnz, G))
+        return launch_res8<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
+    if (is_int && max_row < 65536.0)
         return launch_one<G, VPT, true, true>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta,
                                               alpha, lds, st);
     if (is_int)
@@ -340,7 +596,7 @@ int csr_resident_group(int64_t n, int64_t R, int cus) {
 }
 
 hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, bool is_int,
-                               bool small_w, const float *b, float *x, float *m, float *h_last,
+                               double max_row, const float *b, float *x, float *m, float *h_last,
                                int32_t t0, int32_t t1, const float *lam, float eta, float alpha,
                                hipStream_t st) {
     if (t1 <= t0) return hipSuccess;
@@ -350,7 +606,7 @@ hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, b
     if (v * G > 16) return hipErrorInvalidValue;
 #define QPA_RES_CASE(GG, VV)                                                                   \
     if (G == GG && v == VV)                                                                    \
-        return launch_g_v<GG, VV>(c, R, Rp, is_int, small_w, b, x, m, h_last, t0, t1, lam, eta, \
+        return launch_g_v<GG, VV>(c, R, Rp, is_int, max_row, b, x, m, h_last, t0, t1, lam, eta, \
                                   alpha, lds, st);
     QPA_RES_CASE(8, 1)
     QPA_RES_CASE(8, 2)
