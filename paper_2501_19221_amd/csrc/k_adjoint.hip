@@ -19,8 +19,8 @@
 // global rows [row0_k, row0_k + n_k).  Replicas r >= R are padding: held at zero and left
 // out of every sum.
 // Products with J: CSR couplings through row launches over blocks of 64 rows, the input
-// vector staged through LDS (a wave = four rows and 64 replicas, lane = replica, each
-// row's entries walked in order); dense FP32 couplings through the matrix-core
+// vector staged through LDS (a wave = four rows and 64 replicas, sixteen lanes a row, four
+// replicas a lane, each row's entries walked in order); dense FP32 couplings through the matrix-core
 // product shared with the SBM step, with the element work in its epilogue.  Both add one fused multiply-add
 // per term in ascending column order.
 // Inner products are accumulated in FP64 per thread, reduced per workgroup in a fixed
@@ -82,49 +82,83 @@ __device__ __forceinline__ double rel_group_sum(double v, double *sh, int nw) {
     return s;
 }
 
-// Element work of one launch; `acc` is the product (J v)_i when the mode has one.
-template <int MODE>
-__device__ __forceinline__ void rel_element(const RelArgs &a, int64_t idx, bool live, float acc,
-                                            float bi, double &s0, double &s1, double &s2) {
-    if (MODE == REL_FWD) {
-        float x = 0.0f, m = 0.0f;
-        if (live) {
-            x = a.xi[idx];
-            m = a.mi[idx];
-            rel_fwd_point(acc, bi, a.lam[a.t_f], a.eta, a.alpha, x, m);
+// N consecutive floats as one access (N = 1 or 4, 4-float aligned).
+template <int N> struct RelVec {
+    float v[N];
+    __device__ __forceinline__ void load(const float *p) {
+        if constexpr (N == 4) {
+            const float4 q = *reinterpret_cast<const float4 *>(p);
+            v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+        } else {
+            v[0] = *p;
         }
-        a.xo[idx] = x;
-        a.mo[idx] = m;
-        if (a.fo) a.fo[idx] = live ? acc : 0.0f;
-    } else if (MODE == REL_LOSS) {
-        float xb = 0.0f;
-        if (live) {
-            const double x = a.xi[idx], f = acc, b = bi;
-            s0 += 0.5 * x * f + b * x;
-            xb = (float)(a.scale * (f + b));
+    }
+    __device__ __forceinline__ void store(float *p) const {
+        if constexpr (N == 4) *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+        else *p = v[0];
+    }
+};
+
+// Element work of one launch on N consecutive replicas, the first `live` of them real;
+// `acc` is the product (J v)_i when the mode has one.
+template <int MODE, int N>
+__device__ __forceinline__ void rel_element(const RelArgs &a, int64_t idx, int live,
+                                            const float (&acc)[N], float bi, double &s0,
+                                            double &s1, double &s2) {
+    auto in = [&](const float *p) {
+        RelVec<N> v{};
+        if (live > 0) v.load(p + idx);
+        return v;
+    };
+    if constexpr (MODE == REL_FWD) {
+        RelVec<N> x = in(a.xi), m = in(a.mi), f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            f.v[k] = k < live ? acc[k] : 0.0f;
+            rel_fwd_point(acc[k], bi, a.lam[a.t_f], a.eta, a.alpha, x.v[k], m.v[k]);
+            if (k >= live) x.v[k] = m.v[k] = 0.0f;
         }
-        a.xbar[idx] = xb;
+        x.store(a.xo + idx);
+        m.store(a.mo + idx);
+        if (a.fo) f.store(a.fo + idx);
+    } else if constexpr (MODE == REL_LOSS) {
+        const RelVec<N> xi = in(a.xi);
+        RelVec<N> xb;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            xb.v[k] = 0.0f;
+            if (k < live) {
+                const double x = xi.v[k], f = acc[k], b = bi;
+                s0 += 0.5 * x * f + b * x;
+                xb.v[k] = (float)(a.scale * (f + b));
+            }
+        }
+        xb.store(a.xbar + idx);
     } else {
-        float xbar_next = 0.0f;
-        if (MODE == REL_A) {
-            xbar_next = a.xbar[idx];
+        RelVec<N> xn{}, mu_in = in(a.mu_in);
+        if constexpr (MODE == REL_A) {
+            xn.load(a.xbar + idx);
         } else {
             // B of the previous launch's step: xbar_t from ybar, mu_{t+1} and J mu_{t+1}
-            const float xb = live ? rel_b_point(a.yb[idx], a.mu_in[idx], acc, a.lam[a.t_f],
-                                                a.eta)
-                                  : 0.0f;
-            if (MODE == REL_B) {
-                a.xbar[idx] = xb;
+            const RelVec<N> yb = in(a.yb);
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                xn.v[k] = k < live ? rel_b_point(yb.v[k], mu_in.v[k], acc[k], a.lam[a.t_f], a.eta)
+                                   : 0.0f;
+            if constexpr (MODE == REL_B) {
+                xn.store(a.xbar + idx);
                 return;
             }
-            xbar_next = xb;
         }
-        float mu = 0.0f, yb = 0.0f;
-        if (live)
-            rel_a_point(a.sx[idx], a.sm[idx], a.sf[idx], bi, a.lam[a.t_a], a.eta, a.alpha,
-                        xbar_next, a.mu_in[idx], mu, yb, s0, s1, s2);
-        a.mu_out[idx] = mu;
-        a.yb[idx] = yb;
+        const RelVec<N> sx = in(a.sx), sm = in(a.sm), sf = in(a.sf);
+        RelVec<N> mu{}, yb{};
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (k < live)
+                rel_a_point(sx.v[k], sm.v[k], sf.v[k], bi, a.lam[a.t_a], a.eta, a.alpha,
+                            xn.v[k], mu_in.v[k], mu.v[k], yb.v[k], s0, s1, s2);
+        mu.store(a.mu_out + idx);
+        yb.store(a.yb + idx);
     }
 }
 
@@ -147,39 +181,64 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
     }
 }
 
-template <typename T> __device__ __forceinline__ float as_weight(T w) { return (float)w; }
-
 // Row launches: the CSR product with its input staged through LDS (the gather modes), and
 // the element-wise pass (REL_A) over every instance's rows with the same work items, so
 // that a step's partial sums are grouped alike whichever launch computes them.  Work item
 // = (block of 64 consecutive rows of one instance, 64-replica chunk c); a workgroup of 16
-// waves takes its items in the order below.  Wave w owns rows 4w .. 4w + 3 of the block
-// (lane = replica) and keeps their running sums; the input vector (x or mu of the
-// instance, the chunk's 64 replicas) goes through LDS 256 columns at a time (one buffer of
-// 64 KiB: a range is staged, then walked; the other workgroup on the compute unit walks
-// while this one stages), and each row walks its entries
-// whose column falls in the staged range, in ascending order, one fused multiply-add per
-// term (the order of the definition), while each staged value serves all 64 rows of the
-// block instead of one gather per entry.  A row's entries come in windows of 64 (lane k =
-// entry k past the row's cursor).  At the start of a range the number of each row's
-// entries in it is counted from the window at hand; the windows past them (all four rows)
-// are loaded into a second register set before any row is walked, so that they are in
-// flight during the walks, and they are converted only when the next range counts them.
-// The loads are issued without per-lane branches.
+// waves takes its items in the order below.  Sixteen lanes own a row, four replicas each,
+// so a wave owns four rows; the input vector (x or mu of the instance, the chunk's 64
+// replicas) goes through LDS 256 columns at a time (one buffer of 64 KiB: a range is
+// staged, then walked; the other workgroup on the compute unit walks while this one
+// stages), and each row walks its entries whose column falls in the staged range, in
+// ascending order, one fused multiply-add per term (the order of the definition), while
+// each staged value serves all 64 rows of the block instead of one gather per entry.
+// A row's entries come in windows of 64, 16 of them in a register across its lanes.  A step
+// of the walk broadcasts one entry's LDS offset and weight within the row's lanes as DPP
+// operands of the address addition and of the four multiply-adds, so a step serves an
+// entry of each of the wave's rows with one 16-byte read and five vector instructions.
+// Lanes whose row has no further entry in the range read a column of zeros with weight 0
+// (which changes no sum).  The windows past the range's entries are loaded before the walk.
+// 96 ER QUBOs of 100 to 2000 variables (p = 0.1, 13.4 million entries), 64 replicas: 115 us
+// a launch, against 230 with one row's entry per step (an address, a weight and a product
+// for every entry).  The 3.4 GB of staged values read at 128 bytes a clock take 46 us, the
+// vector instructions about 65; unequal items account for most of the rest.
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int GR_THREADS = 1024, GR_WAVES = GR_THREADS / 64, GR_RPW = 4;
 constexpr int GR_ROWS = GR_WAVES * GR_RPW;       // 64 rows per block
 constexpr int GR_CW = 256;                       // staged columns per range
+constexpr int GR_WIN = 4;                        // registers of 16 entries per row
 static_assert(GR_ROWS == 64, "blocks of 64 rows");
 
 typedef const __attribute__((address_space(1))) int32_t *gr_i32;
 
-// A row's window as loaded (raw column and weight of entry cursor + lane; lanes past the
-// row's end hold some stored entry of the instance); converted when it is used, so that
-// its loads stay in flight until then.
-template <typename TW, typename TI> struct GrWin {
-    TI j[GR_RPW];
-    TW w[GR_RPW];
+// A row's window as prepared for a range: LDS byte offsets and weights.
+struct GrWalk {
+    int32_t off[GR_WIN];
+    float w[GR_WIN];
+
+    // entry K of register Q of every row: lane K of each 16 broadcast within them
+    template <int K> static __device__ __forceinline__ int32_t bcast(int32_t v) {
+        return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true);
+    }
+    template <int K>
+    __device__ __forceinline__ void four(int q, const char *src, float (&acc)[4]) const {
+        const float4 v0 = *reinterpret_cast<const float4 *>(src + bcast<K>(off[q]));
+        const float4 v1 = *reinterpret_cast<const float4 *>(src + bcast<K + 1>(off[q]));
+        const float4 v2 = *reinterpret_cast<const float4 *>(src + bcast<K + 2>(off[q]));
+        const float4 v3 = *reinterpret_cast<const float4 *>(src + bcast<K + 3>(off[q]));
+        add<K>(q, v0, acc);
+        add<K + 1>(q, v1, acc);
+        add<K + 2>(q, v2, acc);
+        add<K + 3>(q, v3, acc);
+    }
+    template <int K>
+    __device__ __forceinline__ void add(int q, const float4 &v, float (&acc)[4]) const {
+        const float wk = __int_as_float(bcast<K>(__float_as_int(w[q])));
+        acc[0] = __fmaf_rn(wk, v.x, acc[0]);
+        acc[1] = __fmaf_rn(wk, v.y, acc[1]);
+        acc[2] = __fmaf_rn(wk, v.z, acc[2]);
+        acc[3] = __fmaf_rn(wk, v.w, acc[3]);
+    }
 };
 
 // Two workgroups per CU (64 KiB of LDS each, 8 waves per SIMD): the walks are bound by
@@ -193,12 +252,15 @@ __global__ void __launch_bounds__(GR_THREADS)
     constexpr bool GATHER = MODE != REL_A;
     typedef const __attribute__((address_space(1))) TW *gw_t;
     typedef const __attribute__((address_space(1))) TI *gi_t;
-    __shared__ __attribute__((aligned(16))) float vs[GATHER ? GR_CW * 64 : 1];
+    // the staged columns and one of zeros
+    __shared__ __attribute__((aligned(16))) float vs[GATHER ? (GR_CW + 1) * 64 : 1];
     __shared__ double sh[GR_WAVES];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rl = lane >> 4, ln = lane & 15;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     const int64_t total = blocks * C;
+    if (GATHER && threadIdx.x < 64) vs[GR_CW * 64 + threadIdx.x] = 0.0f;
     // items in chunks of P = (workgroups / 8) consecutive ones, chunk k on compute die
     // k mod 8 (workgroup b runs on die b mod 8): the items a die runs at a time are
     // neighbouring blocks, mostly of one instance, whose input vector its L2 then holds
@@ -219,11 +281,9 @@ __global__ void __launch_bounds__(GR_THREADS)
         // compiler knows, which would otherwise make it read them again)
         const RelInst &I = insts[lo];
         const int64_t n = I.n;
-        const int64_t i0 = (blk - I.blk0) * GR_ROWS + GR_RPW * wv;
-        float acc[GR_RPW];
-#pragma unroll
-        for (int u = 0; u < GR_RPW; ++u) acc[u] = 0.0f;
-        if (GATHER) {
+        const int64_t i = (blk - I.blk0) * GR_ROWS + GR_RPW * wv + rl;
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (GATHER) {
             const gr_i32 rp = (gr_i32)I.rp;
             const int32_t rp0 = rp[0];
             // (an instance without stored entries has nothing to gather: uniform per item)
@@ -251,216 +311,70 @@ __global__ void __launch_bounds__(GR_THREADS)
                             vq + o, (lds_void *)(vs + 4 * (1024 * u + 64 * wv)), 16, 0, 0);
                     }
                 };
-                int32_t kc[GR_RPW], ke[GR_RPW];
+                // the row's cursor and end, and its window as loaded (lanes past the row's
+                // end hold some stored entry of the instance)
+                int32_t kc = i < n ? rp[i] : rp0;
+                const int32_t ke = i < n ? rp[i + 1] : rp0;
+                const int32_t klast = max(ke - 1, rp0);
+                TI wj[GR_WIN];
+                TW ww[GR_WIN];
+                auto load = [&]() {
 #pragma unroll
-                for (int u = 0; u < GR_RPW; ++u) {
-                    const int64_t i = i0 + u;
-                    kc[u] = i < n ? rp[i] : rp0;
-                    ke[u] = i < n ? rp[i + 1] : rp0;
-                }
-                // row u's window from its cursor kc[u] (two loads, no branch)
-                auto load = [&](GrWin<TW, TI> &W, int u) {
-                    const int32_t kk = min(kc[u] + lane, max(ke[u] - 1, rp0));
-                    W.j[u] = col[kk];
-                    W.w[u] = w[kk];
-                };
-                // its entries as columns (past the row's end: one no range reaches) and
-                // weights (a stored QUBO diagonal is folded into b: weight 0 adds nothing)
-                auto cols = [&](const GrWin<TW, TI> &W, int u) {
-                    return kc[u] + lane < ke[u] ? (int32_t)W.j[u] : INT32_MAX;
-                };
-                auto weights = [&](const GrWin<TW, TI> &W, int u) {
-                    const float wf = as_weight(W.w[u]);
-                    return skip && (int64_t)W.j[u] == i0 + u ? 0.0f : wf;
-                };
-                auto walk = [&](int32_t jl, float wl, int u, int cnt, int32_t base,
-                                const float *src) {
-                    int e = 0;
-                    const int wi = __float_as_int(wl);
-                    for (; e + 4 <= cnt; e += 4) {
-                        const int32_t j0 = __builtin_amdgcn_readlane(jl, e) - base;
-                        const int32_t j1 = __builtin_amdgcn_readlane(jl, e + 1) - base;
-                        const int32_t j2 = __builtin_amdgcn_readlane(jl, e + 2) - base;
-                        const int32_t j3 = __builtin_amdgcn_readlane(jl, e + 3) - base;
-                        const float v0 = src[64 * j0], v1 = src[64 * j1];
-                        const float v2 = src[64 * j2], v3 = src[64 * j3];
-                        acc[u] = __fmaf_rn(__int_as_float(__builtin_amdgcn_readlane(wi, e)),
-                                           v0, acc[u]);
-                        acc[u] = __fmaf_rn(
-                            __int_as_float(__builtin_amdgcn_readlane(wi, e + 1)), v1, acc[u]);
-                        acc[u] = __fmaf_rn(
-                            __int_as_float(__builtin_amdgcn_readlane(wi, e + 2)), v2, acc[u]);
-                        acc[u] = __fmaf_rn(
-                            __int_as_float(__builtin_amdgcn_readlane(wi, e + 3)), v3, acc[u]);
-                    }
-                    for (; e < cnt; ++e) {
-                        const int32_t j = __builtin_amdgcn_readlane(jl, e) - base;
-                        acc[u] = __fmaf_rn(__int_as_float(__builtin_amdgcn_readlane(wi, e)),
-                                           src[64 * j], acc[u]);
+                    for (int q = 0; q < GR_WIN; ++q) {
+                        const int32_t kk = min(kc + 16 * q + ln, klast);
+                        wj[q] = col[kk];
+                        ww[q] = w[kk];
                     }
                 };
-                // Integer weights of 8 or 16 bits: the float of such a weight has its low 8
-                // bits zero, which then carry the entry's column within the staged range,
-                // so that one read of the window word gives both (the column on the scalar
-                // unit, the weight as it is).
-                constexpr bool PACK = std::is_integral<TW>::value && sizeof(TW) <= 2;
-                // Two forms of the word: 8-bit weights' floats have their low 16 bits zero
-                // too, which then carry the column's byte offset in the staged range as it is
-                // (one AND on the scalar unit instead of a shift and an AND); other 8- or
-                // 16-bit weights carry the column index in their low 8 bits.  W16 (a
-                // compile-time tag) selects the form.
-                auto pack = [&](int32_t jl, float wl, int32_t base, auto w16) {
-                    if (decltype(w16)::value)
-                        return (__float_as_int(wl) & (int32_t)0xFFFF0000) |
-                               (((jl - base) & 0xFF) << 8);
-                    return (__float_as_int(wl) & ~0xFF) | ((jl - base) & 0xFF);
-                };
-                auto offs = [](int32_t p, auto w16) -> int32_t {
-                    return decltype(w16)::value ? (p & 0xFF00) : ((p & 0xFF) << 8);
-                };
-                auto wgt = [](int32_t p, auto w16) -> float {
-                    return __int_as_float(decltype(w16)::value ? (p & (int32_t)0xFFFF0000)
-                                                               : (p & ~0xFF));
-                };
-                // the staged value of a word's column for this lane's replica
-                auto val = [&](const float *src, int32_t p, auto w16) {
-                    return *reinterpret_cast<const float *>(
-                        reinterpret_cast<const char *>(src) + offs(p, w16));
-                };
-                auto walkp = [&](int32_t pk, int u, int e, int cnt, const float *src, auto w16) {
-                    for (; e + 4 <= cnt; e += 4) {
-                        const int32_t p0 = __builtin_amdgcn_readlane(pk, e);
-                        const int32_t p1 = __builtin_amdgcn_readlane(pk, e + 1);
-                        const int32_t p2 = __builtin_amdgcn_readlane(pk, e + 2);
-                        const int32_t p3 = __builtin_amdgcn_readlane(pk, e + 3);
-                        const float v0 = val(src, p0, w16), v1 = val(src, p1, w16);
-                        const float v2 = val(src, p2, w16), v3 = val(src, p3, w16);
-                        acc[u] = __fmaf_rn(wgt(p0, w16), v0, acc[u]);
-                        acc[u] = __fmaf_rn(wgt(p1, w16), v1, acc[u]);
-                        acc[u] = __fmaf_rn(wgt(p2, w16), v2, acc[u]);
-                        acc[u] = __fmaf_rn(wgt(p3, w16), v3, acc[u]);
-                    }
-                    for (; e < cnt; ++e) {
-                        const int32_t p = __builtin_amdgcn_readlane(pk, e);
-                        acc[u] = __fmaf_rn(wgt(p, w16), val(src, p, w16), acc[u]);
-                    }
-                };
-                // rows u and u + 1 together over their common first entries (eight reads in
-                // flight, two independent sums), then each alone
-                auto walkp2 = [&](int32_t pa, int32_t pb, int u, int ca, int cb,
-                                  const float *src, auto w16) {
-                    const int cm = min(ca, cb);
-                    int e = 0;
-                    for (; e + 4 <= cm; e += 4) {
-                        int32_t p[8];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            p[k] = __builtin_amdgcn_readlane(pa, e + k);
-                            p[4 + k] = __builtin_amdgcn_readlane(pb, e + k);
-                        }
-                        float vv[8];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) vv[k] = val(src, p[k], w16);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            acc[u] = __fmaf_rn(wgt(p[k], w16), vv[k], acc[u]);
-                            acc[u + 1] = __fmaf_rn(wgt(p[4 + k], w16), vv[4 + k], acc[u + 1]);
-                        }
-                    }
-                    walkp(pa, u, e, ca, src, w16);
-                    walkp(pb, u + 1, e, cb, src, w16);
-                };
-                auto walk_any = [&](int32_t jl, float wl, int u, int cnt, int32_t base,
-                                    const float *src) {
-                    if (PACK) walkp(pack(jl, wl, base, std::false_type{}), u, 0, cnt, src,
-                                    std::false_type{});
-                    else walk(jl, wl, u, cnt, base, src);
-                };
+                load();
+                const char *src = reinterpret_cast<const char *>(vs) + 16 * ln;
                 const int nq = (int)((n + GR_CW - 1) / GR_CW);
-                GrWin<TW, TI> A, B;
-#pragma unroll
-                for (int u = 0; u < GR_RPW; ++u) load(A, u);
-                // range q: load Y (the windows past this range's entries of every row),
-                // then walk X (the windows at the cursors before)
-                auto range = [&](int q, GrWin<TW, TI> &X, GrWin<TW, TI> &Y) {
+                for (int q = 0; q < nq; ++q) {
                     // every wave is done with range q - 1, then the buffer takes range q
                     // and every wave's part has landed
                     if (q > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
                     stage(q);
                     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
                     const int32_t base = q * GR_CW, bound = base + GR_CW;
-                    int32_t jl[GR_RPW];
-                    float wl[GR_RPW];
-                    int cnt[GR_RPW];
+                    bool more;
+                    do {
+                        GrWalk W;
+                        int steps[GR_WIN];       // of the longest of the four rows
+                        int cnt = 0;
 #pragma unroll
-                    for (int u = 0; u < GR_RPW; ++u) {
-                        jl[u] = cols(X, u);
-                        wl[u] = weights(X, u);
-                        cnt[u] = __popcll(__ballot(jl[u] < bound));
-                    }
-                    const float *src = vs + lane;
-#pragma unroll
-                    for (int u = 0; u < GR_RPW; ++u) {
-                        kc[u] += cnt[u];
-                        load(Y, u);
-                    }
-                    if (PACK) {
-                        // the 16-bit form when every weight of the four windows fits it
-                        bool w16 = true;
-#pragma unroll
-                        for (int u = 0; u < GR_RPW; ++u)
-                            w16 = w16 && __ballot(kc[u] - cnt[u] + lane < ke[u] &&
-                                                  fabsf(wl[u]) > 255.0f) == 0;
-                        if (w16) {
-#pragma unroll
-                            for (int u = 0; u < GR_RPW; u += 2)
-                                walkp2(pack(jl[u], wl[u], base, std::true_type{}),
-                                       pack(jl[u + 1], wl[u + 1], base, std::true_type{}), u,
-                                       cnt[u], cnt[u + 1], src, std::true_type{});
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < GR_RPW; u += 2)
-                                walkp2(pack(jl[u], wl[u], base, std::false_type{}),
-                                       pack(jl[u + 1], wl[u + 1], base, std::false_type{}), u,
-                                       cnt[u], cnt[u + 1], src, std::false_type{});
+                        for (int r = 0; r < GR_WIN; ++r) {
+                            const int32_t j = (int32_t)wj[r];
+                            const bool in = kc + 16 * r + ln < ke && j < bound;
+                            const uint64_t bal = __ballot(in);
+                            const uint32_t l = (uint32_t)bal, h = (uint32_t)(bal >> 32);
+                            cnt += __popc(((rl & 2 ? h : l) >> (16 * (rl & 1))) & 0xFFFFu);
+                            steps[r] = __popc(((l | h) | ((l | h) >> 16)) & 0xFFFFu);
+                            W.off[r] = (in ? j - base : GR_CW) << 8;
+                            // (a stored QUBO diagonal is folded into b: weight 0)
+                            W.w[r] = in && !(skip && j == (int32_t)i) ? (float)ww[r] : 0.0f;
                         }
-                    }
+                        kc += cnt;
+                        more = __ballot(cnt == 16 * GR_WIN) != 0;
+                        load();
 #pragma unroll
-                    for (int u = 0; u < GR_RPW; ++u) {
-                        if (!PACK) walk_any(jl[u], wl[u], u, cnt[u], base, src);
-                        if (cnt[u] == 64) {
-                            // more of the row's entries in this range (rare): walk on from
-                            // Y, which starts at the cursor, and reload it after them
-                            for (;;) {
-                                const int32_t j2 = cols(Y, u);
-                                const int c2 = __popcll(__ballot(j2 < bound));
-                                walk_any(j2, weights(Y, u), u, c2, base, src);
-                                kc[u] += c2;
-                                load(Y, u);
-                                if (c2 < 64) break;
-                            }
+                        for (int r = 0; r < GR_WIN; ++r) {
+                            if (steps[r] == 0) break;
+                            W.four<0>(r, src, acc);
+                            if (steps[r] > 4) W.four<4>(r, src, acc);
+                            if (steps[r] > 8) W.four<8>(r, src, acc);
+                            if (steps[r] > 12) W.four<12>(r, src, acc);
                         }
-                    }
-                };
-                int q = 0;
-                for (; q + 2 <= nq; q += 2) {
-                    range(q, A, B);
-                    range(q + 1, B, A);
+                    } while (more);              // a row's window may end within the range
                 }
-                if (q < nq) range(q, A, B);
                 // every wave is done with the staging buffers before the next item loads
                 // them
                 __syncthreads();
             }
         }
-        const int64_t r = (int64_t)c * 64 + lane;
-#pragma unroll
-        for (int u = 0; u < GR_RPW; ++u) {
-            const int64_t i = i0 + u;
-            if (i < n)
-                rel_element<MODE>(a, (I.row0 + i) * a.Rp + r, r < a.R, acc[u], I.b[i], s0, s1,
-                                  s2);
-        }
+        const int r0 = c * 64 + 4 * ln;
+        if (i < n)
+            rel_element<MODE, 4>(a, (I.row0 + i) * a.Rp + r0, min(max(a.R - r0, 0), 4), acc,
+                                 I.b[i], s0, s1, s2);
     }
     rel_write_partials<MODE>(a, blockIdx.x, s0, s1, s2, sh, GR_WAVES);
 }
@@ -478,7 +392,8 @@ struct RelTileEpilogue {
     __device__ __forceinline__ Pre load(int64_t, int64_t) const { return Pre{}; }
     __device__ __forceinline__ void point(float acc, float bi, int64_t r, int64_t idx,
                                           const Pre &) {
-        rel_element<MODE>(a, idx, r < a.R, acc, bi, s0, s1, s2);
+        const float v[1] = {acc};
+        rel_element<MODE, 1>(a, idx, r < a.R ? 1 : 0, v, bi, s0, s1, s2);
     }
     __device__ __forceinline__ void finish() const {
         __shared__ double sh[8];
