@@ -198,10 +198,11 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
 // entry of each of the wave's rows with one 16-byte read and five vector instructions.
 // Lanes whose row has no further entry in the range read a column of zeros with weight 0
 // (which changes no sum).  The windows past the range's entries are loaded before the walk.
-// 96 ER QUBOs of 100 to 2000 variables (p = 0.1, 13.4 million entries), 64 replicas: 115 us
+// 96 ER QUBOs of 100 to 2000 variables (p = 0.1, 13.4 million entries), 64 replicas: 95 us
 // a launch, against 230 with one row's entry per step (an address, a weight and a product
-// for every entry).  The 3.4 GB of staged values read at 128 bytes a clock take 46 us, the
-// vector instructions about 65; unequal items account for most of the rest.
+// for every entry) and items in the given order.  The 3.4 GB of staged values read at 128
+// bytes a clock take 46 us, the padded entries and the staging bring that to 67, and the
+// vector instructions alone take about 65.
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int GR_THREADS = 1024, GR_WAVES = GR_THREADS / 64, GR_RPW = 4;
 constexpr int GR_ROWS = GR_WAVES * GR_RPW;       // 64 rows per block
@@ -261,14 +262,18 @@ __global__ void __launch_bounds__(GR_THREADS)
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     const int64_t total = blocks * C;
     if (GATHER && threadIdx.x < 64) vs[GR_CW * 64 + threadIdx.x] = 0.0f;
-    // items in chunks of P = (workgroups / 8) consecutive ones, chunk k on compute die
-    // k mod 8 (workgroup b runs on die b mod 8): the items a die runs at a time are
+    // items in chunks of P = (workgroups / 8) consecutive ones, eight chunks a round, one
+    // per compute die (workgroup b runs on die b mod 8): the items a die runs at a time are
     // neighbouring blocks, mostly of one instance, whose input vector its L2 then holds
-    // for all of them instead of every die fetching every instance's
+    // for all of them instead of every die fetching every instance's.  The table's items
+    // come longest first, and every other round runs through them backwards, which evens
+    // out the workgroups' shares (96 ER QUBOs, n = 100 to 2000: 115 us a launch with the
+    // instances as given, 95 so).
     const int64_t P = gridDim.x >> 3;
-    const int64_t die = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    for (int64_t k = die; k * P + slot < total; k += 8) {
-        const int64_t it = k * P + slot;
+    const int64_t me = (blockIdx.x & 7) * P + (blockIdx.x >> 3);
+    for (int64_t round = 0; round * gridDim.x < total; ++round) {
+        const int64_t it = round * gridDim.x + (round & 1 ? gridDim.x - 1 - me : me);
+        if (it >= total) continue;
         const int64_t blk = it / C;
         const int c = (int)(it - blk * C);
         int lo = 0, hi = ninst - 1;

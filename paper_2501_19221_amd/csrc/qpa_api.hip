@@ -724,7 +724,8 @@ struct RelPlan {
         int64_t items, blocks;     // rows, and blocks of 64 rows (the gather's work items)
     };
     std::vector<Group> groups;     // CSR instances by (coupling, index) type
-    std::vector<int32_t> csr_order;   // instance indices, grouped
+    std::vector<int32_t> all_order;   // instance indices, longest row blocks first
+    std::vector<int32_t> csr_order;   // the CSR ones, grouped, in that order
     std::vector<int32_t> dense_slot;  // per instance: first tile slot (-1 for CSR)
     size_t o_tab_all = 0, o_tab_csr = 0, o_lam = 0, o_x0 = 0, o_x1 = 0, o_m = 0, o_ckpt = 0,
            o_seg = 0, o_xbar = 0, o_yb = 0, o_mu0 = 0, o_mu1 = 0, o_part = 0, o_ploss = 0,
@@ -770,7 +771,18 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     rp.C = (int32_t)(rp.Rp / 64);
     rp.k = k;
     rp.nseg = (int32_t)((a.steps + k - 1) / k);
-    // CSR instances grouped by (coupling, index) type, in index order within a group
+    // the instances whose 64-row blocks take longest first (the row launches share their
+    // items out in this order): 64 entries cost about as much as staging 10 columns
+    auto block_work = [&](int32_t q) {
+        const double n = (double)probs[q].n;
+        return n + (probs[q].format == QPA_FMT_CSR ? 6.4 * (double)probs[q].nnz / n : 0.0);
+    };
+    rp.all_order.resize((size_t)count);
+    for (int32_t q = 0; q < count; ++q) rp.all_order[q] = q;
+    std::stable_sort(rp.all_order.begin(), rp.all_order.end(), [&](int32_t x, int32_t y) {
+        return block_work(x) > block_work(y);
+    });
+    // CSR instances grouped by (coupling, index) type, in that order within a group
     for (int32_t q = 0; q < count; ++q) {
         if (probs[q].format != QPA_FMT_CSR) continue;
         const int32_t wdt = probs[q].coupling_dtype, idt = probs[q].index_dtype;
@@ -781,7 +793,7 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     int32_t slot = 0;
     for (auto &g : rp.groups) {
         g.first = (int32_t)rp.csr_order.size();
-        for (int32_t q = 0; q < count; ++q)
+        for (const int32_t q : rp.all_order)
             if (probs[q].format == QPA_FMT_CSR && probs[q].coupling_dtype == g.wdt &&
                 probs[q].index_dtype == g.idt) {
                 rp.csr_order.push_back(q);
@@ -1379,8 +1391,9 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     };
     std::vector<RelInst> tab_all(count), tab_csr(std::max<size_t>(rp.csr_order.size(), 1));
     int64_t blk_all = 0;
-    for (int32_t q = 0; q < count; ++q) {
-        tab_all[q] = inst_entry(q, rp.row0[q], blk_all);
+    for (int32_t e = 0; e < count; ++e) {
+        const int32_t q = rp.all_order[e];
+        tab_all[e] = inst_entry(q, rp.row0[q], blk_all);
         blk_all += (probs[q].n + 63) / 64;
     }
     for (const auto &g : rp.groups) {
