@@ -24,6 +24,8 @@
 // with the weight (low / high 16 bits of a uint32).
 #include "qpa_internal.h"
 
+#include <type_traits>
+
 namespace qpa {
 namespace {
 
@@ -194,7 +196,14 @@ __global__ void __launch_bounds__(256) k_bin_rowconst(int64_t n, const int32_t *
     crow[i] = (int32_t)c;
 }
 
-// Pass 1.  Grid (Nc, S): chunk c, share s of its entries.
+// Four consecutive entry records or spin bytes, in one access from any entry.
+typedef uint32_t rec4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t byte4 __attribute__((aligned(1)));
+
+// Pass 1.  Grid (Nc, S): chunk c, share s of its entries, four consecutive ones per lane.
+// An access that starts on one of the share's entries may run up to three entries past
+// them: reads stay within the workspace (other arrays follow), writes are exact.
+// n = 24 million, 72 million entries, G = 4: 81 us (99 with one entry per access).
 __global__ void __launch_bounds__(BT) k_bin_gather(int shiftG, int64_t nwords, int64_t Nb,
                                                    const int32_t *__restrict__ off,
                                                    const uint32_t *__restrict__ src,
@@ -216,29 +225,57 @@ __global__ void __launch_bounds__(BT) k_bin_gather(int shiftG, int64_t nwords, i
     __syncthreads();
     const int vsh = 6 - shiftG;
     const uint32_t vmask = (1u << vsh) - 1, gmask = (1u << (1 << shiftG)) - 1;
-    constexpr int U = 8;
-    for (int64_t p = a + threadIdx.x; p < e; p += (int64_t)U * BT) {
-        uint32_t r[U];
+    constexpr int U = 4;
+    for (int64_t p = a + 4 * threadIdx.x; p < e; p += (int64_t)4 * U * BT) {
+        rec4 r[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t q = p + (int64_t)u * BT;
-            r[u] = q < e ? src[q] : 0u;
+            const int64_t q = p + (int64_t)4 * u * BT;
+            r[u] = 0u;
+            if (q < e) r[u] = __builtin_nontemporal_load(reinterpret_cast<const rec4 *>(src + q));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t q = p + (int64_t)u * BT;
-            if (q < e) {
-                const uint64_t word = words[r[u] >> vsh];
-                bits[q] = (uint8_t)((word >> ((r[u] & vmask) << shiftG)) & gmask);
+            const int64_t q = p + (int64_t)4 * u * BT;
+            uint32_t out = 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                // an entry past the share may belong to a chunk of any size
+                const uint32_t o = r[u][k] & ((uint32_t)CHUNK_WORDS << vsh) - 1u;
+                const uint64_t word = words[o >> vsh];
+                out |= ((uint32_t)(word >> ((o & vmask) << shiftG)) & gmask) << (8 * k);
+            }
+            if (q + 3 < e) {
+                *reinterpret_cast<byte4 *>(bits + q) = out;
+            } else {
+                for (int k = 0; k < 4; ++k)
+                    if (q + k < e) bits[q + k] = (uint8_t)(out >> (8 * k));
             }
         }
     }
 }
 
+// The L lanes of a word, from L bits: all ones in the lane of each set bit.
+template <int L> __device__ __forceinline__ uint32_t lane_masks(uint32_t b) {
+    if (L == 4) {
+        const uint32_t s = __umul24(b, 0x00204081u) & 0x01010101u;
+        return (s << 8) - s;
+    }
+    const uint32_t s = (b | (b << 15)) & 0x00010001u;
+    return (s << 16) - s;
+}
+
 // Pass 2.  One workgroup per bin of B = BIN_WORDS L / G rows; dynamic LDS holds the run
-// starts and prefix lengths of the bin's Nc runs (2 (Nc + 1) int32), so that two
-// workgroups share a compute unit and one's loads overlap the other's arithmetic.  For
-// L > 1 a table in LDS spreads a (flipped) spin byte into the G / L words of its lanes.
+// starts and lengths of the bin's Nc runs (2 (Nc + 1) int32), so that two workgroups share
+// a compute unit and one's loads overlap the other's arithmetic.  A wave takes pieces of
+// up to 256 consecutive entries of one run, four per lane, and finds a piece's run by
+// comparing 64 runs' piece counts at once (one LDS read; its pieces only grow).  The
+// update takes four consecutive (row, replica) pairs per lane.
+// n = 24 million, 3 entries a row, G = 4: 360 us (439 with one entry and one pair per access
+// and a search of the run per entry), of which the 1.6 GB of the update alone are 311 and
+// the entries alone 94: the two workgroups of a compute unit overlap little, as they run
+// the same phases at the same time.  Non-temporal entry loads (here and in pass 1) leave
+// the last-level cache to the spin bytes: 446 us a step against 473.
 template <int L>
 __global__ void __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) k_bin_update(
     int64_t n, int shiftG, int64_t Nb, int64_t Nc, int64_t nwords,
@@ -247,124 +284,178 @@ __global__ void __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(8))) k_
     uint64_t *__restrict__ s_nxt, float *__restrict__ x, float *__restrict__ m,
     float *__restrict__ h_last, int t, const float *__restrict__ lam, float eta, float alpha) {
     constexpr int LW = 32 / L;                          // lane width in bits
-    constexpr uint32_t LMASK = L == 1 ? 0xffffffffu : (1u << LW) - 1;
     constexpr int SUMS = BIN_WORDS * L;                 // (row, replica) sums of a bin
-    __shared__ uint32_t acc[BIN_WORDS];
-    __shared__ uint32_t spread[L > 1 ? 256 * 8 / L : 1];
+    __shared__ __attribute__((aligned(16))) uint32_t acc[BIN_WORDS];
     __shared__ int32_t wsum[BT / 64];
     extern __shared__ int32_t runs[];
     int32_t *st = runs;               // start of the run of chunk c
-    int32_t *pre = runs + Nc + 1;     // entries of the bin before chunk c's run
+    // pieces of the bin before chunk c's run, times 256, plus the run's length - 1 mod 256
+    // (at most 2^23 + Nc pieces)
+    uint32_t *pre = reinterpret_cast<uint32_t *>(runs + Nc + 1);
     const int64_t bin = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = 1 << shiftG;
     const int WPE = G / L;            // words of one entry (L <= G)
     const uint32_t gmask = (1u << G) - 1;
-    for (int q = tid; q < BIN_WORDS; q += BT) acc[q] = 0u;
-    if (L > 1)
-        for (int e = tid; e < 256 * WPE; e += BT) {
-            const uint32_t byte = (uint32_t)(e / WPE), k = (uint32_t)(e % WPE);
-            uint32_t v = 0u;
-            for (int l = 0; l < L; ++l) v |= ((byte >> (k * L + l)) & 1u) << (LW * l);
-            spread[e] = v;
-        }
     // run of chunk c in this bin: [off[c*Nb + bin], off[c*Nb + bin + 1])
-    int32_t v[2];
+    int32_t v[2], last[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int64_t c = 2 * tid + u;
-        v[u] = 0;
+        v[u] = last[u] = 0;
         if (c < Nc) {
             const int32_t a0 = off[c * Nb + bin];
             st[c] = a0;
-            v[u] = off[c * Nb + bin + 1] - a0;
+            const int32_t len = off[c * Nb + bin + 1] - a0;
+            v[u] = (len + 255) >> 8;
+            last[u] = (len + 255) & 255;
         }
     }
+    for (int q = 4 * tid; q < BIN_WORDS; q += 4 * BT)
+        *reinterpret_cast<uint4 *>(acc + q) = make_uint4(0u, 0u, 0u, 0u);
     const int32_t total = block_scan_excl<2>(v, wsum);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
-        if (2 * tid + u < Nc) pre[2 * tid + u] = v[u];
-    if (tid == 0) pre[Nc] = total;
+        if (2 * tid + u < Nc) pre[2 * tid + u] = ((uint32_t)v[u] << 8) | (uint32_t)last[u];
+    if (tid == 0) pre[Nc] = (uint32_t)total << 8;
     __syncthreads();
-    constexpr int U = 8;
-    for (int32_t e0 = tid; e0 < total; e0 += U * BT) {
-        uint32_t rec[U];
+    auto add = [&](uint32_t rec, uint32_t b) {
+        const int32_t wv = (int32_t)rec >> 16;
+        const uint32_t aw = (uint32_t)(wv < 0 ? -wv : wv);
+        const uint32_t fb = b ^ (wv < 0 ? gmask : 0u);            // b' of each replica
+        uint32_t *a = acc + ((rec & 0xffffu) << shiftG) / L;
+        if (L == 1) {
+            for (int r = 0; r < G; ++r)
+                if ((fb >> r) & 1u) atomicAdd(a + r, aw);
+        } else {
+            // |w| in every lane (below 2^LW, as the row's sum is)
+            const uint32_t rep = L == 4 ? __umul24(aw, 0x00010101u) | aw << 24 : aw | aw << 16;
+            for (int k = 0; k < WPE; ++k)
+                atomicAdd(a + k, rep & lane_masks<L>((fb >> (k * L)) & ((1u << L) - 1)));
+        }
+    };
+    int32_t c0 = 0;                   // a chunk whose run does not begin after the piece
+    constexpr int U = 2;
+    for (int32_t k0 = wave; k0 < total; k0 += U * (BT / 64)) {
+        rec4 rec[U];
         uint32_t bv[U];
+        int nv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int32_t e = e0 + u * BT;
-            rec[u] = 0;
-            bv[u] = 0;
-            if (e < total) {
-                // chunk of entry e: largest c with pre[c] <= e (pre[Nc] = total > e)
-                int32_t lo = 0, hi = (int32_t)Nc;
-                while (hi - lo > 1) {
-                    const int32_t mid = (lo + hi) >> 1;
-                    if (pre[mid] <= e) lo = mid;
-                    else hi = mid;
-                }
-                const int64_t p = (int64_t)st[lo] + (e - pre[lo]);
-                rec[u] = drec[p];
-                bv[u] = bits[p];
+            const int32_t k = k0 + u * (BT / 64);
+            nv[u] = 0;
+            rec[u] = 0u;
+            bv[u] = 0u;
+            if (k >= total) continue;
+            // the run of piece k: the last chunk c with pre[c] <= k (pre[Nc] = total > k)
+            uint32_t pl;
+            int adv;
+            for (;;) {
+                const int32_t c = c0 + lane;
+                pl = c <= (int32_t)Nc ? pre[c] : UINT32_MAX;
+                adv = __popcll(__ballot((pl >> 8) <= (uint32_t)k)) - 1;
+                if (adv < 63) break;
+                c0 += 63;
+            }
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int32_t)pl, adv);
+            const uint32_t next = (uint32_t)__builtin_amdgcn_readlane((int32_t)pl, adv + 1);
+            c0 += adv;
+            const int32_t cnt = (uint32_t)k + 1u == next >> 8 ? (int32_t)(first & 255u) + 1 : 256;
+            nv[u] = cnt - 4 * lane;
+            if (nv[u] > 0) {
+                const int64_t p = (int64_t)st[c0] + 256 * (int64_t)((uint32_t)k - (first >> 8)) + 4 * lane;
+                rec[u] = __builtin_nontemporal_load(reinterpret_cast<const rec4 *>(drec + p));
+                bv[u] = *reinterpret_cast<const byte4 *>(bits + p);
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (e0 + u * BT >= total) continue;
-            const int32_t wv = (int32_t)rec[u] >> 16;
-            const uint32_t aw = (uint32_t)(wv < 0 ? -wv : wv);
-            const uint32_t fb = bv[u] ^ (wv < 0 ? gmask : 0u);        // b' of each replica
-            uint32_t *a = acc + ((rec[u] & 0xffffu) << shiftG) / L;
-            if (L == 1) {
-                for (int r = 0; r < G; ++r)
-                    if ((fb >> r) & 1u) atomicAdd(a + r, aw);
-            } else {
-                for (int k = 0; k < WPE; ++k) atomicAdd(a + k, aw * spread[fb * WPE + k]);
-            }
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < nv[u]) add(rec[u][k], (bv[u] >> (8 * k)) & 0xffu);
     }
     __syncthreads();
-    // fused update of the bin's (row, replica) pairs; state index = row * G + replica.
-    // UQ pairs per thread per round: every load of a round is issued before its stores.
-    // x and m stream through once per step (gigabytes, far beyond the caches): their
-    // loads and stores are non-temporal, leaving the caches to the entry records.
-    constexpr int UQ = 4;
-    static_assert((BIN_WORDS / BT) % UQ == 0, "rounds must cover the bin exactly");
-    const int64_t q0 = bin * SUMS;
+    // fused update of the bin's (row, replica) pairs; state index = row * G + replica, four
+    // consecutive ones per lane, UQ times per round: every load of a round is issued before
+    // its stores.  x and m stream through once per step (gigabytes, far beyond the caches):
+    // their loads and stores are non-temporal, leaving the caches to the entry records.
+    constexpr int UQ = 2;
+    static_assert(SUMS % (4 * BT * UQ) == 0, "rounds must cover the bin exactly");
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const int64_t q0 = bin * SUMS, pairs = n << shiftG;
     const float lt = lam[t];
-    for (int qb = tid; qb < SUMS; qb += UQ * BT) {
-        float xv[UQ], mv[UQ];
-        int32_t cr[UQ];
-        bool live[UQ];
+    uint32_t *s32 = reinterpret_cast<uint32_t *>(s_nxt);
+    for (int qb = 4 * tid; qb < SUMS; qb += 4 * UQ * BT) {
+        f4 xv[UQ], mv[UQ];
+        int32_t cr[UQ][4];
 #pragma unroll
         for (int u = 0; u < UQ; ++u) {
-            const int64_t gi = q0 + qb + u * BT;
-            live[u] = (gi >> shiftG) < n;
+            const int64_t gi = q0 + qb + 4 * u * BT;
             xv[u] = mv[u] = 0.0f;
-            cr[u] = 0;
-            if (live[u]) {
-                xv[u] = __builtin_nontemporal_load(&x[gi]);
-                mv[u] = __builtin_nontemporal_load(&m[gi]);
-                cr[u] = crow[gi >> shiftG];
+            if (gi + 3 < pairs) {
+                xv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(x + gi));
+                mv[u] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(m + gi));
+                if (shiftG >= 2) {
+                    cr[u][0] = cr[u][1] = cr[u][2] = cr[u][3] = crow[gi >> shiftG];
+                } else if (shiftG == 1) {
+                    cr[u][0] = cr[u][1] = crow[gi >> 1];
+                    cr[u][2] = cr[u][3] = crow[(gi >> 1) + 1];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) cr[u][k] = crow[gi + k];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    cr[u][k] = 0;
+                    if (gi + k < pairs) {
+                        xv[u][k] = x[gi + k];
+                        mv[u][k] = m[gi + k];
+                        cr[u][k] = crow[(gi + k) >> shiftG];
+                    }
+                }
             }
         }
 #pragma unroll
         for (int u = 0; u < UQ; ++u) {
-            const int q = qb + u * BT;
+            const int q = qb + 4 * u * BT;
             const int64_t gi = q0 + q;
-            bool neg = false;
-            if (live[u]) {
-                const int32_t A = (int32_t)((acc[q / L] >> (LW * (q % L))) & LMASK);
-                const float h = (float)(cr[u] - 2 * A);
-                pa_update(h, lt, eta, alpha, xv[u], mv[u]);
-                __builtin_nontemporal_store(xv[u], &x[gi]);
-                __builtin_nontemporal_store(mv[u], &m[gi]);
-                if (h_last) h_last[gi] = h;
-                neg = xv[u] < 0.0f;
+            uint32_t neg = 0u;
+            f4 hv;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t wd = acc[(q + k) / L];
+                const int32_t A = (int32_t)(
+                    L == 1 ? wd : (wd >> (LW * (k % L))) & ((1u << (LW % 32)) - 1u));
+                hv[k] = (float)(cr[u][k] - 2 * A);
+                float xk = xv[u][k], mk = mv[u][k];
+                pa_update(hv[k], lt, eta, alpha, xk, mk);
+                xv[u][k] = xk;
+                mv[u][k] = mk;
+                neg |= (xk < 0.0f && gi + k < pairs ? 1u : 0u) << k;
             }
-            const uint64_t bal = __ballot(neg);
-            const int64_t wi = (gi - lane) >> 6;
-            if (lane == 0 && wi < nwords) s_nxt[wi] = bal;
+            if (gi + 3 < pairs) {
+                __builtin_nontemporal_store(xv[u], reinterpret_cast<f4 *>(x + gi));
+                __builtin_nontemporal_store(mv[u], reinterpret_cast<f4 *>(m + gi));
+                if (h_last) *reinterpret_cast<f4 *>(h_last + gi) = hv;
+            } else {
+                for (int k = 0; k < 4; ++k)
+                    if (gi + k < pairs) {
+                        x[gi + k] = xv[u][k];
+                        m[gi + k] = mv[u][k];
+                        if (h_last) h_last[gi + k] = hv[k];
+                    }
+            }
+            // the bits of eight lanes (32 pairs) in the first of them
+            auto from = [](uint32_t w, auto ctrl) {
+                return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, decltype(ctrl)::value, 0xf, 0xf,
+                                                          true);
+            };
+            neg |= from(neg, std::integral_constant<int, 0x101>{}) << 4;      // lane + 1
+            neg |= from(neg, std::integral_constant<int, 0x102>{}) << 8;      // lane + 2
+            neg |= from(neg, std::integral_constant<int, 0x104>{}) << 16;     // lane + 4
+            if ((lane & 7) == 0 && (gi >> 6) < nwords) s32[gi >> 5] = neg;
         }
     }
 }
@@ -437,14 +528,24 @@ hipError_t launch_bin_build(const CsrView &c, const BinGeom &g, const int64_t *b
     return c.col_dt == QPA_I16 ? byi((int16_t)0) : byi((int32_t)0);
 }
 
-hipError_t launch_bin_step(const BinGeom &g, int64_t n, int64_t nwords, const int32_t *off,
+hipError_t launch_bin_step(const BinGeom &g, int64_t n, int64_t nnz, int64_t nwords, const int32_t *off,
                            const uint32_t *src, const uint32_t *drec, uint8_t *bits,
                            const int32_t *crow, const uint64_t *s_cur, uint64_t *s_nxt, float *x,
                            float *m, float *h_last, int32_t t, const float *lam, float eta,
                            float alpha, int cus, hipStream_t st) {
-    int64_t S = (4 * (int64_t)cus + g.Nc - 1) / g.Nc;
-    if (S < 1) S = 1;
-    if (S > 64) S = 64;
+    // shares of a chunk's entries: the count with the least work per compute unit, one
+    // workgroup each at a time, where every share also loads the chunk's 128 KiB of words
+    // (an entry moves 5 bytes)
+    const double fixed = 131072.0 * (double)g.Nc / (5.0 * (double)(nnz > 0 ? nnz : 1));
+    int64_t S = 1;
+    double best = 0.0;
+    for (int64_t q = 1; q <= 64; ++q) {
+        const double work = (double)((g.Nc * q + cus - 1) / cus) * (1.0 / (double)q + fixed);
+        if (q == 1 || work < best) {
+            best = work;
+            S = q;
+        }
+    }
     k_bin_gather<<<dim3((unsigned)g.Nc, (unsigned)S), BT, 0, st>>>(g.shiftG, nwords, g.Nb, off,
                                                                    src, s_cur, bits);
     hipError_t e = hipGetLastError();

@@ -601,7 +601,7 @@ qpa_status run_steps_inner(qpa_ctx *ctx, const qpa_problem &p, const qpa_params 
             const BinGeom g = bin_run_geometry(ctx, pl);
             launches = 2 * (int64_t)(t1 - t0);
             for (int32_t t = t0; t < t1; ++t) {
-                QPA_HIP(launch_bin_step(g, pl.n, pl.nwords, off, src, drec,
+                QPA_HIP(launch_bin_step(g, pl.n, p.nnz, pl.nwords, off, src, drec,
                                         at<uint8_t>(ws, pl.o_bbits), at<int32_t>(ws, pl.o_bcrow),
                                         s0, s1, x, m, (t == t1 - 1) ? h : nullptr, t, lam, a.eta,
                                         a.alpha, ctx->cus, st));
