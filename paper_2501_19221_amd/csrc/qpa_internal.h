@@ -313,13 +313,14 @@ struct BinGeom {
 bool bin_geometry(int64_t n, int G, int lanes, BinGeom &g);
 int64_t bin_scan_tiles(const BinGeom &g);
 // Entry order of the binned kernels: off (M + 1 int32: block offsets, off[M] = entries),
-// cur (M int32 scratch), tsum (bin_scan_tiles int32 scratch), src / drec (nnz uint32),
+// cnt (M int32 scratch), tsum (bin_scan_tiles int32 scratch), src / drec (nnz uint32),
 // crow (n int32: sum over the row of |w| plus the canonical integer field b_i64).
 hipError_t launch_bin_build(const CsrView &c, const BinGeom &g, const int64_t *b_i64,
-                            int32_t *off, int32_t *cur, int32_t *tsum, uint32_t *src,
+                            int32_t *off, int32_t *cnt, int32_t *tsum, uint32_t *src,
                             uint32_t *drec, int32_t *crow, hipStream_t st);
 // One PA step: s_cur -> bits (nnz bytes) -> fields, update, s_nxt.
-hipError_t launch_bin_step(const BinGeom &g, int64_t n, int64_t nnz, int64_t nwords, const int32_t *off,
+hipError_t launch_bin_step(const BinGeom &g, int64_t n, int64_t nnz, int64_t nwords,
+                           const int32_t *off,
                            const uint32_t *src, const uint32_t *drec, uint8_t *bits,
                            const int32_t *crow, const uint64_t *s_cur, uint64_t *s_nxt, float *x,
                            float *m, float *h_last, int32_t t, const float *lam, float eta,
