@@ -4,7 +4,7 @@
 //
 // 1. k_spec_pack: one wave per replica packs its int8 spins into 64-bit words (one
 //    ballot per 64 variables, bit set <=> spin -1) and folds the words into a 64-bit
-//    hash (sum over words of a SplitMix64-style finaliser of word + position).
+//    hash (sum over words of a SplitMix64-style finaliser of word + position), one word a lane.
 // 2. k_spec_select: one workgroup sorts (energy, hash, replica) with a bitonic network
 //    in LDS; equal (energy, hash) runs are groups.  A group whose members all equal its
 //    first member (compared word by word) is one state: its first member represents it
@@ -35,13 +35,30 @@ __global__ void __launch_bounds__(256) k_spec_pack(int64_t n, int32_t R, int64_t
     if (r >= R) return;
     const int8_t *s = spins + r * n;
     uint64_t h = 0;
-    for (int64_t w = 0; w < nw; ++w) {
-        const int64_t i = 64 * w + lane;
-        const bool neg = i < n && s[i] < 0;
-        const uint64_t word = __ballot(neg);
-        if (lane == 0) bits[r * nw + w] = word;
-        h += spec_mix(word + (uint64_t)(w + 1) * 0x9e3779b97f4a7c15ull);
+    // 64 words a round, word w0 + l in lane l, the spins of eight loaded together
+    constexpr int U = 8;
+    for (int64_t w0 = 0; w0 < nw; w0 += 64) {
+        const int cnt = (int)(nw - w0 < 64 ? nw - w0 : 64);
+        uint64_t word = 0;
+        for (int c = 0; c < cnt; c += U) {
+            int8_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = 64 * (w0 + c + u) + lane;
+                v[u] = i < n ? s[i] : (int8_t)0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t bal = __ballot(v[u] < 0);
+                word = lane == c + u ? bal : word;
+            }
+        }
+        if (lane < cnt) {
+            bits[r * nw + w0 + lane] = word;
+            h += spec_mix(word + (uint64_t)(w0 + lane + 1) * 0x9e3779b97f4a7c15ull);
+        }
     }
+    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o);
     if (lane == 0) hash[r] = no_hash ? 0ull : h;
 }
 
@@ -49,9 +66,17 @@ __device__ __forceinline__ bool spec_equal(const uint64_t *__restrict__ bits, in
                                            int32_t a, int32_t b) {
     if (a == b) return true;
     const uint64_t *x = bits + (int64_t)a * nw, *y = bits + (int64_t)b * nw;
-    for (int64_t w = 0; w < nw; ++w)
-        if (x[w] != y[w]) return false;
-    return true;
+    constexpr int U = 8;                   // words compared together
+    int64_t w = 0;
+    for (; w + U <= nw; w += U) {
+        uint64_t d = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) d |= x[w + u] ^ y[w + u];
+        if (d) return false;
+    }
+    uint64_t d = 0;
+    for (; w < nw; ++w) d |= x[w] ^ y[w];
+    return d == 0;
 }
 
 // order-preserving unsigned key of a double (-0 is folded into +0 first)
@@ -61,10 +86,35 @@ __device__ __forceinline__ uint64_t spec_ekey(double e) {
 }
 
 // Bitonic sort of RP (a power of two) entries by (ka, kb) ascending.  Live entries carry
-// distinct (ka, kb) pairs, so their order is unique; padding sorts last.
+// distinct (ka, kb) pairs, so their order is unique; padding sorts last.  Entries i and
+// i ^ stride of a stride below 64 belong to one wave, which exchanges them by lane without
+// a barrier: 10 of the 55 rounds of 1024 entries go through LDS.
 __device__ void spec_sort(int32_t RP, uint64_t *ka, uint64_t *kb) {
-    for (int32_t size = 2; size <= RP; size <<= 1) {
-        for (int32_t stride = size >> 1; stride > 0; stride >>= 1) {
+    // rounds of the given sizes with strides below 64, for the entries of this thread
+    auto lanes = [&](int32_t size0, int32_t size1) {
+        for (int32_t i0 = 0; i0 < RP; i0 += SPEC_THREADS) {
+            const int32_t i = i0 + (int32_t)threadIdx.x;
+            uint64_t a = i < RP ? ka[i] : ~0ull, b = i < RP ? kb[i] : ~0ull;
+            for (int32_t size = size0; size <= size1; size <<= 1)
+                for (int32_t stride = size < 64 ? size >> 1 : 32; stride > 0; stride >>= 1) {
+                    const uint64_t pa = __shfl_xor(a, stride), pb = __shfl_xor(b, stride);
+                    const bool less = pa < a || (pa == a && pb < b);     // the partner's
+                    const bool small = ((i & size) == 0) == ((i & stride) == 0);
+                    if (less == small) {
+                        a = pa;
+                        b = pb;
+                    }
+                }
+            if (i < RP) {
+                ka[i] = a;
+                kb[i] = b;
+            }
+        }
+        __syncthreads();
+    };
+    lanes(2, RP < 64 ? RP : 64);
+    for (int32_t size = 128; size <= RP; size <<= 1) {
+        for (int32_t stride = size >> 1; stride >= 64; stride >>= 1) {
             for (int32_t i = threadIdx.x; i < RP; i += SPEC_THREADS) {
                 const int32_t j = i ^ stride;
                 if (j <= i) continue;
@@ -81,6 +131,7 @@ __device__ void spec_sort(int32_t RP, uint64_t *ka, uint64_t *kb) {
             }
             __syncthreads();
         }
+        lanes(size, size);
     }
 }
 
@@ -117,23 +168,36 @@ __global__ void __launch_bounds__(SPEC_THREADS) k_spec_select(
     if (t == 0) ndist = 0;
     __syncthreads();
     spec_sort(RP, ek, kb);
-    for (int32_t i = t; i < R; i += SPEC_THREADS) {
-        const bool head = i == 0 || ek[i] != ek[i - 1] ||
-                          (kb[i] >> SPEC_IBITS) != (kb[i - 1] >> SPEC_IBITS);
-        gs[i] = head ? i : 0;
+    // group start = largest head position <= i: the prefix maximum within each wave's 64
+    // positions, then over the waves before (positions in order: pass, wave; R <= 4 passes)
+    constexpr int NW = SPEC_THREADS / 64;
+    __shared__ int32_t wmax[4 * NW];
+    const int lane = t & 63, wave = t >> 6;
+    if (t < 4 * NW) wmax[t] = 0;
+    __syncthreads();
+    for (int32_t i0 = 0; i0 < R; i0 += SPEC_THREADS) {
+        const int32_t i = i0 + t;
+        const bool head = i < R && i > 0 &&
+                          (ek[i] != ek[i - 1] ||
+                           (kb[i] >> SPEC_IBITS) != (kb[i - 1] >> SPEC_IBITS));
+        const uint64_t heads = __ballot(head) & (~0ull >> (63 - lane));
+        const int32_t g0 = heads ? i - lane + 63 - __builtin_clzll(heads) : 0;
+        if (i < R) gs[i] = g0;
+        if (lane == 63) wmax[i0 / 64 + wave] = g0;
     }
     __syncthreads();
-    // group start = largest head position <= i (prefix max; R <= 4 * SPEC_THREADS)
-    for (int32_t off = 1; off < R; off <<= 1) {
-        int32_t v[4];
-        int c = 0;
-        for (int32_t i = t; i < R; i += SPEC_THREADS, ++c)
-            v[c] = (i >= off && gs[i - off] > gs[i]) ? gs[i - off] : gs[i];
-        __syncthreads();
-        c = 0;
-        for (int32_t i = t; i < R; i += SPEC_THREADS, ++c) gs[i] = v[c];
-        __syncthreads();
+    if (t < 64) {
+        int32_t v = wmax[t];
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t y = __shfl_up(v, d);
+            if (lane >= d && y > v) v = y;
+        }
+        wmax[t] = v;
     }
+    __syncthreads();
+    for (int32_t i = t; i < R; i += SPEC_THREADS)
+        if (gs[i] == 0 && i >= 64) gs[i] = wmax[i / 64 - 1];
+    __syncthreads();
     for (int32_t i = t; i < R; i += SPEC_THREADS) atomicAdd(&gc[gs[i]], 1);
     __syncthreads();
     // groups whose members are not all equal to the first one (hash collisions)
