@@ -72,21 +72,22 @@ template <int BM_, int BN_, int NST_> struct BfTile {
 };
 typedef BfTile<256, 64, 7> BfWide;
 typedef BfTile<128, 128, 4> BfSquare;
-// Integer couplings with |J| <= 127 (exact in int8) run on tiles of 64 replicas x 256
+// Integer couplings with |J| <= 127 (exact in int8) run on tiles of 64 replicas x 128
 // variables (see the int8 section below): J rows of 128 bytes per chunk, spins one byte per
 // (replica, variable) (+1 = 0x01, -1 = 0xFF), chunk-major (128 bytes per replica and
 // chunk), v_mfma_i32_32x32x32_i8 with exact int32 sums.
-constexpr int BM8 = MF_BM8, BN8 = MF_BN8;    // 64 replicas x 256 variables
-constexpr int JSTG8 = BN8 * KC;              // 256 rows x 128 bytes
+constexpr int BM8 = MF_BM8, BN8 = MF_BN8;    // 64 replicas x 128 variables
+constexpr int JSTG8 = BN8 * KC;              // 128 rows x 128 bytes
 constexpr int SSTG8 = BM8 * KC;              // 64 replicas x 128 bytes
 constexpr int STG8 = JSTG8 + SSTG8;
-constexpr int NST8 = 4;
+constexpr int NST8 = 3;
 constexpr int HS8 = BN8 + 8;                 // row stride of the int8 handoff (int32)
-constexpr int SR8 = BM8 / 2;                 // rows per state thread of an int8 tile
+constexpr int SR8 = BM8 / 8;                 // rows of four columns per state thread
 constexpr int LDS8_BYTES = NST8 * STG8;
-static_assert(LDS8_BYTES <= 160 * 1024, "LDS of one workgroup");
+constexpr int MW8 = 4, THREADS8 = 512;       // 4 matrix waves + 4 state waves
+static_assert(LDS8_BYTES <= 80 * 1024, "LDS of two workgroups per compute unit");
 static_assert(2 * BM8 * HS8 * 4 <= LDS8_BYTES, "the int8 handoff's two partial-sum buffers");
-static_assert(BN8 % KC == 0 && BN8 / 16 == 16, "16 row groups of 16 per int8 tile");
+static_assert(BN8 == KC && BN8 / 16 == 2 * MW8, "two row groups of 16 per state wave");
 constexpr int THREADS = 1024;                // 8 matrix waves + 8 state waves
 constexpr int MW = 8;                        // matrix waves
 constexpr int SR = 32;                       // rows per state thread
@@ -647,32 +648,37 @@ __global__ void __launch_bounds__(THREADS, 1) k_mfma_grouped(const MfmaTile *__r
     mfma_tile_step<BfSquare, true, true>(lds, tl, cur, nxt, nullptr, lam[t], eta, alpha);
 }
 
-// ---- int8 tiles of a batch: 64 replicas x 256 variables ---------------------------------
-// For integer couplings with |J| <= 127 a workgroup owns 64 replicas (R0 .. R0 + 63) and
-// 256 variables (I0 .. I0 + 255) of an instance; every tile row is a replica (with 64
-// replicas per instance, as in the batch workload, no row is padding), and one tile does
-// the work of two 128 x 128 tiles with one set of fixed costs.  Per chunk of 128 reduction
-// variables a stage holds the 256 x 128 int8 block of J (rows of 128 bytes, the 16-byte
-// piece p of row r at position p ^ (r % 8)) and the 64 x 128 byte spins of the tile's
-// replicas (same layout); NST8 = 4 stages.
-//   * matrix waves: wave w takes columns 64 (w % 4) .. + 63 and k steps 2 (w / 4),
-//     2 (w / 4) + 1 of every chunk (32 each), 2 x 2 accumulators of 32 x 32
-//     (v_mfma_i32_32x32x32_i8); they load the spins of every stage (one 1 KiB direct
-//     load each: rows 8w .. 8w + 7) and, for dense rows, the couplings (four: rows
+// ---- int8 tiles of a batch: 64 replicas x 128 variables ---------------------------------
+// For integer couplings with |J| <= 127 a workgroup of 8 waves owns 64 replicas (R0 ..
+// R0 + 63) and 128 variables (I0 .. I0 + 127) of an instance; every tile row is a replica
+// (with 64 replicas per instance, as in the batch workload, no row is padding).  Two
+// workgroups share a compute unit, so that one's state (128 KiB read and written) moves
+// while the other multiplies.  Per chunk of 128 reduction variables a stage holds the 128 x
+// 128 int8 block of J (rows of 128 bytes, the 16-byte piece p of row r at position
+// p ^ (r % 8)) and the 64 x 128 byte spins of the tile's replicas (same layout); NST8 = 3
+// stages, 72 KiB.
+//   * matrix waves: wave w takes columns 64 (w % 2) .. + 63 and k steps 2 (w / 2),
+//     2 (w / 2) + 1 of every chunk (32 each), 2 x 2 accumulators of 32 x 32
+//     (v_mfma_i32_32x32x32_i8); they load the spins of every stage (two 1 KiB direct
+//     loads each: rows 16w .. 16w + 15) and, for dense rows, the couplings (four: rows
 //     32w .. 32w + 31);
-//   * state waves: thread t owns column t % 256 of rows 2e + t / 256 (32 rows); for
+//   * state waves: thread t owns columns 4 (t % 32) .. + 3 of rows 8e + t / 32 (8 rows); for
 //     entry-list tiles, state wave g also writes the couplings of row groups 2g and 2g + 1
 //     (16 rows each) of every stage: it clears their 2 KiB and stores each entry's weight
-//     byte at its position (entries of chunk c placed after the barrier of chunk c - 2
-//     into the stage of chunk c - 4, loaded three chunks ahead into three register sets
+//     byte at its position (entries of chunk c placed after the barrier of chunk c - 1
+//     into the stage of chunk c - 3, loaded three chunks ahead into three register sets
 //     used in turn; lanes past a block's end repeat its last entry, the same byte with the
 //     same value, so that no load or store sits behind a per-lane branch and each wait
 //     for a register set covers that set only).
 // After the reduction the two k halves' exact int32 partial sums go through two LDS
-// buffers (rows padded to 264 words), added by the state waves, which then run the PA
-// update and store x, m and the byte spins of their live rows (rows at or past rlive,
-// uniform per wave, are skipped).  Barriers per tile: nchunk + 2 in both roles.
-
+// buffers (rows padded to 136 words), added by the state waves, which then run the PA
+// update and store x, m and the byte spins of their live rows.  Barriers per tile:
+// nchunk + 2 in both roles.
+// What bounds it: a tile takes about 11 us for its state and 1.1 us per chunk with two on
+// a compute unit; the chunks are mostly LDS time (byte writes of the entries, reads of the
+// products).  512 ER QUBOs of 100 to 2000 variables (p = 0.1), 64 replicas: 205 us a step
+// against 240 with one workgroup of 64 x 256 (padding to 256) and single-word state
+// accesses; 1024 of 508 variables: 127 against 159.
 // The table's pointers are generic; these views make the offsets scalar loads (uniform,
 // read-only during the launch) and the entries global loads, which count on the
 // vector-memory counter only (generic loads also count on the counter that the LDS
@@ -693,13 +699,13 @@ __device__ __forceinline__ void matrix_tile8(uint8_t *lds, const Tile &tl, int n
                                              const uint8_t *__restrict__ s_cur, int wave,
                                              int lane) {
     const int64_t np = tl.np;
-    const int kh = wave >> 2, wc = wave & 3;
+    const int kh = wave >> 1, wc = wave & 1;
     const int half = lane >> 5, l32 = lane & 31;
     // wave-uniform bases plus 32-bit lane offsets (fewer registers than 64-bit pointers):
     // load u of the couplings fills rows 32w + 8u + lane / 8, that of the spins rows
-    // 8w + lane / 8, each at position lane % 8 (piece (lane % 8) ^ (row % 8))
+    // 16w + 8u + lane / 8, each at position lane % 8 (piece (lane % 8) ^ (row % 8))
     const uint8_t *Jw = reinterpret_cast<const uint8_t *>(tl.Jb) + (tl.I0 + 32 * wave) * np;
-    const uint8_t *Sw = s_cur + (tl.R0 + 8 * wave) * KC;
+    const uint8_t *Sw = s_cur + (tl.R0 + 16 * wave) * KC;
     const int r8 = lane >> 3;
     const uint32_t piece = (uint32_t)((lane & 7) ^ r8);
     uint32_t oJ[4];
@@ -717,10 +723,13 @@ __device__ __forceinline__ void matrix_tile8(uint8_t *lds, const Tile &tl, int n
                                                  (lds_void *)(dst + (4 * wave + u) * 1024), 16, 0,
                                                  0);
         }
-        __builtin_amdgcn_global_load_lds(Sw + (int64_t)kc * sstride + oS,
-                                         (lds_void *)(dst + JSTG8 + wave * 1024), 16, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            __builtin_amdgcn_global_load_lds(Sw + (int64_t)kc * sstride + 8 * u * KC + oS,
+                                             (lds_void *)(dst + JSTG8 + (2 * wave + u) * 1024),
+                                             16, 0, 0);
     };
-    constexpr int LOADS = SPARSE ? 1 : 5;          // per chunk and wave
+    constexpr int LOADS = SPARSE ? 2 : 6;          // per chunk and wave
     i32x16 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -780,24 +789,24 @@ struct EntryRegs {
     int32_t cnt;
 };
 
-// Row group gg (0..15) of the tile, chunk kc (past the last chunk: the last again).  The
-// block belongs to the 128-row tile I0 / 128 + gg / 8 of the entry-list layout.
+// Row group gg (0..7) of the tile, chunk kc (past the last chunk: the last again).  The
+// block belongs to the 128-row tile I0 / 128 of the entry-list layout.
 __device__ __forceinline__ void entries_load(EntryRegs &er, const Tile &tl, int kc, int nchunk,
                                              int gg, int lane) {
     kc = kc < nchunk ? kc : nchunk - 1;
-    const int64_t blk = ((tl.I0 / KC + (gg >> 3)) * (tl.np / KC) + kc) * 8 + (gg & 7);
+    const int64_t blk = (tl.I0 / KC * (tl.np / KC) + kc) * 8 + gg;
     const c_i32 *O = (const c_i32 *)tl.O;
     const int32_t beg = O[blk];
     er.cnt = O[blk + 1] - beg;
     // an empty block reads the word at its start, which lies inside the coupling buffer
     // (the entries end at least a quarter of the buffer before its end); it is not placed
-    // each block is read once per step and a batch's lists, state and spins are far more
-    // than the caches hold between steps: non-temporal loads
+    // (ordinary loads: the cache holds part of the lists from one step to the next, as the
+    // state, far more than it holds, goes past it)
     const g_u32 *src = (const g_u32 *)tl.E + beg;
     const int32_t last = max(er.cnt - 1, 0);
 #pragma unroll
     for (int j = 0; j < I8S_EPL; ++j)
-        er.e[j] = __builtin_nontemporal_load(&src[min(lane + 64 * j, last)]);
+        er.e[j] = src[min(lane + 64 * j, last)];
 }
 
 // Clears row group gg's 2 KiB of the stage and writes its entries there.  An entry's
@@ -830,34 +839,41 @@ __device__ __forceinline__ void pair_place(const EntryPair &p, uint8_t *stage, i
     entries_place(p.b, stage, 2 * g + 1, lane);
 }
 
+typedef float st4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const st4 g_st4;
+typedef __attribute__((address_space(1))) st4 g_st4w;
+typedef __attribute__((address_space(1))) uint32_t g_u32w;
+
+// State thread t: columns 4 (t % 32) .. + 3 of rows 8e + t / 32.
 struct StateRegs8 {
-    float xv[SR8], mv[SR8];
-    float bi;
+    st4 xv[SR8], mv[SR8];
+    st4 bi;
 };
 
-// x, m of rows 2e + t / 256, E0 <= e < E1, of this thread (rows at or past rlive are not
-// read).  The state of a batch step (all instances', with the couplings and spins far more
-// than the caches hold between steps) is read and written non-temporally.
+// x, m of rows 8e + t / 32, E0 <= e < E1, of this thread (eight rows at or past rlive are
+// not read; others past it read the last live row again, unused).  The state of a batch
+// step (all instances', with the couplings and spins far more than the caches hold between
+// steps) is read and written non-temporally.
 template <int E0, int E1>
 __device__ __forceinline__ void xm_load8(StateRegs8 &st, const Tile &tl, int t) {
-    const int col = t & (BN8 - 1);
-    const int rsub = __builtin_amdgcn_readfirstlane(t >> 8);
-    const g_f32 *xr = (const g_f32 *)tl.x + (tl.R0 + 2 * E0 + rsub) * tl.np + tl.I0;
-    const g_f32 *mr = (const g_f32 *)tl.m + (tl.R0 + 2 * E0 + rsub) * tl.np + tl.I0;
+    const int col = 4 * (t & 31), rsub = t >> 5;
+    const int64_t left = tl.rlive - tl.R0;             // live rows from the tile's first on
 #pragma unroll
     for (int e = E0; e < E1; ++e) {
-        const bool live = tl.R0 + 2 * e + rsub < tl.rlive;
-        st.xv[e] = live ? __builtin_nontemporal_load(&xr[col]) : 0.0f;
-        st.mv[e] = live ? __builtin_nontemporal_load(&mr[col]) : 0.0f;
-        xr = next_rows(xr, 2 * tl.np);
-        mr = next_rows(mr, 2 * tl.np);
+        st.xv[e] = st.mv[e] = 0.0f;
+        if (8 * e < left) {
+            const int row = 8 * e + rsub < left ? 8 * e + rsub : (int)left - 1;
+            const int64_t o = (tl.R0 + row) * tl.np + tl.I0 + col;
+            st.xv[e] = __builtin_nontemporal_load((const g_st4 *)((const g_f32 *)tl.x + o));
+            st.mv[e] = __builtin_nontemporal_load((const g_st4 *)((const g_f32 *)tl.m + o));
+        }
     }
 }
 
-// One chunk barrier of a placing state wave: then the entries held in p (chunk c + 2) go
+// One chunk barrier of a placing state wave: then the entries held in p (chunk c + 1) go
 // into the stage of chunk c - 2 (free since the barrier of chunk c - 1) and p is reloaded
 // with the chunk three further on.  Past the last chunk the reloaded last chunk is placed
-// again, into a stage that no later chunk of the loop uses (they take those of c + 1 at
+// again, into a stage that no later chunk of the loop uses (they take those of c at
 // most); the barrier after the loop waits for these stores.  No branch, so that the waits
 // for one register set cover that set only.
 __device__ __forceinline__ void place_step(EntryPair &p, const Tile &tl, int c, int nchunk,
@@ -873,33 +889,30 @@ __device__ __forceinline__ void place_step(EntryPair &p, const Tile &tl, int c, 
 template <bool SPARSE>
 __device__ __forceinline__ void state_load8(StateRegs8 &st, const Tile &tl, int nchunk, int t,
                                             uint8_t *lds, int g, int lane) {
-    static_assert(SR8 == 32 && NST8 == 4, "the load pattern below");
-    const int col = t & (BN8 - 1);
+    static_assert(SR8 == 8 && NST8 == 3, "the load pattern below");
+    const g_st4 *bias = (const g_st4 *)((const g_f32 *)tl.b + tl.I0 + 4 * (t & 31));
     if (!SPARSE) {
         xm_load8<0, SR8>(st, tl, t);
-        st.bi = ((const g_f32 *)tl.b)[tl.I0 + col];
+        st.bi = *bias;
         for (int c = 0; c < nchunk; ++c) barrier();
         return;
     }
-    // the prologue's two chunks (past the last chunk: the last again, into stages no chunk
-    // uses), then the next three chunks' entries; x and m follow in three groups after the
-    // first three chunks' entry loads, since loads complete in issue order and a wait for
-    // entries would otherwise wait for them
+    // the prologue's chunk, and the next three chunks' entries; x and m follow in three
+    // groups after the first three chunks' entry loads, since loads complete in issue order
+    // and a wait for entries would otherwise wait for them
     EntryPair p0, p1, p2;
-    pair_load(p0, tl, 0, nchunk, g, lane);
-    pair_load(p1, tl, 1, nchunk, g, lane);
-    pair_place(p0, lds, g, lane);
-    pair_place(p1, lds + STG8, g, lane);
-    pair_load(p0, tl, 2, nchunk, g, lane);
-    pair_load(p1, tl, 3, nchunk, g, lane);
-    pair_load(p2, tl, 4, nchunk, g, lane);
+    pair_load(p2, tl, 0, nchunk, g, lane);
+    pair_load(p0, tl, 1, nchunk, g, lane);
+    pair_load(p1, tl, 2, nchunk, g, lane);
+    pair_place(p2, lds, g, lane);
+    pair_load(p2, tl, 3, nchunk, g, lane);
     if (nchunk > 0) place_step(p0, tl, 0, nchunk, lds, g, lane);
-    xm_load8<0, 11>(st, tl, t);
+    xm_load8<0, 3>(st, tl, t);
     if (nchunk > 1) place_step(p1, tl, 1, nchunk, lds, g, lane);
-    xm_load8<11, 22>(st, tl, t);
+    xm_load8<3, 6>(st, tl, t);
     if (nchunk > 2) place_step(p2, tl, 2, nchunk, lds, g, lane);
-    xm_load8<22, 32>(st, tl, t);
-    st.bi = ((const g_f32 *)tl.b)[tl.I0 + col];
+    xm_load8<6, 8>(st, tl, t);
+    st.bi = *bias;
     int c = 3;
     for (; c + 3 <= nchunk; c += 3) {
         place_step(p0, tl, c, nchunk, lds, g, lane);
@@ -919,55 +932,56 @@ __device__ __forceinline__ void tile8_step(uint8_t *lds, const Tile &tl,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nchunk = (int)(tl.np / KC);
-    if (wave < MW) {
+    if (wave < MW8) {
         matrix_tile8<SPARSE>(lds, tl, nchunk, s_cur, wave, lane);
         return;
     }
-    const int t = tid - MW * 64;
-    const int col = t & (BN8 - 1);
-    const int rsub = __builtin_amdgcn_readfirstlane(t >> 8);
+    const int t = tid - MW8 * 64;
+    const int col = 4 * (t & 31), rsub = t >> 5;
     StateRegs8 st;
-    state_load8<SPARSE>(st, tl, nchunk, t, lds, wave - MW, lane);
+    state_load8<SPARSE>(st, tl, nchunk, t, lds, wave - MW8, lane);
     lds_barrier();                                     // stages drained (and written)
     barrier();                                         // partial sums stored
 #pragma unroll
     for (int e = 0; e < SR8; ++e) asm volatile("" ::"v"(st.xv[e]), "v"(st.mv[e]));
     asm volatile("" ::"v"(st.bi));
     // field = sum of the two k halves' int32 partials (exact), unscaled; rows at or past
-    // rlive (uniform per wave) are not read, not updated and their spins not written
+    // rlive are not updated and their spins not written
     const int32_t *h0 = reinterpret_cast<const int32_t *>(lds), *h1 = h0 + BM8 * HS8;
-    // spins as bytes: row r of chunk (I0 + col) / 128 at (chunk * Rp + r) * 128 + col % 128
-    g_u8w *srow = (g_u8w *)s_nxt + (((tl.I0 + col) / KC) * tl.Rp + tl.R0 + rsub) * KC +
-                  (col & (KC - 1));
-    g_f32w *xr = (g_f32w *)tl.x + (tl.R0 + rsub) * tl.np + tl.I0 + col;
-    g_f32w *mr = (g_f32w *)tl.m + (tl.R0 + rsub) * tl.np + tl.I0 + col;
+    const int64_t left = tl.rlive - tl.R0;
+    // spins as bytes: row r of chunk I0 / 128 at (chunk * Rp + r) * 128 + col
+    g_u8w *srow = (g_u8w *)s_nxt + (tl.I0 / KC * tl.Rp + tl.R0) * KC + col;
 #pragma unroll
-    for (int g = 0; g < SR8 / 8; ++g) {
-        if (tl.R0 + 2 * (8 * g) + rsub >= tl.rlive) continue;
-        int32_t hv[8];
+    for (int e = 0; e < SR8; ++e) {
+        const int row = 8 * e + rsub;
+        if (8 * e >= left) break;
+        const int k = row * HS8 + col;
+        const i32x4 ha = *reinterpret_cast<const i32x4 *>(h0 + k);
+        const i32x4 hb = *reinterpret_cast<const i32x4 *>(h1 + k);
+        uint32_t spins = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = (2 * (8 * g + u) + rsub) * HS8 + col;
-            hv[u] = h0[k] + h1[k];
+        for (int u = 0; u < 4; ++u) {
+            const float h = __fadd_rn((float)(ha[u] + hb[u]), st.bi[u]);
+            float xk = st.xv[e][u], mk = st.mv[e][u];
+            pa_update(h, lt, eta, alpha, xk, mk);
+            st.xv[e][u] = xk;
+            st.mv[e][u] = mk;
+            spins |= (xk < 0.0f ? 0xFFu : 0x01u) << (8 * u);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = 8 * g + u;
-            if (tl.R0 + 2 * e + rsub < tl.rlive) {
-                const float h = __fadd_rn((float)hv[u], st.bi);
-                pa_update(h, lt, eta, alpha, st.xv[e], st.mv[e]);
-                srow[(int64_t)2 * e * KC] = st.xv[e] < 0.0f ? (uint8_t)0xFF : (uint8_t)0x01;
-                __builtin_nontemporal_store(st.xv[e], &xr[(int64_t)2 * e * tl.np]);
-                __builtin_nontemporal_store(st.mv[e], &mr[(int64_t)2 * e * tl.np]);
-            }
+        if (row < left) {
+            const int64_t o = (tl.R0 + row) * tl.np + tl.I0 + col;
+            __builtin_nontemporal_store(st.xv[e], (g_st4w *)((g_f32w *)tl.x + o));
+            __builtin_nontemporal_store(st.mv[e], (g_st4w *)((g_f32w *)tl.m + o));
+            *(g_u32w *)(srow + row * KC) = spins;
         }
     }
 }
 
+// Many int8 instances in one launch (tiles as above).
 template <bool SPARSE>
-__global__ void __launch_bounds__(THREADS, 1) k_mfma_grouped8(const MfmaTile *__restrict__ tiles,
-                                                              int t, const float *__restrict__ lam,
-                                                              float eta, float alpha) {
+__global__ void __launch_bounds__(THREADS8) __attribute__((amdgpu_waves_per_eu(4)))
+    k_mfma_grouped8(const MfmaTile *__restrict__ tiles, int t, const float *__restrict__ lam,
+                    float eta, float alpha) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS8_BYTES];
     const MfmaTile mt = tiles[blockIdx.x];
     if (mt.np == 0) return;      // filler entry of the compute-die-ordered table
@@ -1221,9 +1235,9 @@ hipError_t launch_mfma_grouped(const MfmaTile *tiles, int32_t ntiles, int32_t t,
                                hipStream_t st) {
     if (ntiles <= 0) return hipSuccess;
     if (kind == GK_I8_SPARSE)
-        k_mfma_grouped8<true><<<(unsigned)ntiles, THREADS, 0, st>>>(tiles, t, lam, eta, alpha);
+        k_mfma_grouped8<true><<<(unsigned)ntiles, THREADS8, 0, st>>>(tiles, t, lam, eta, alpha);
     else if (kind == GK_I8)
-        k_mfma_grouped8<false><<<(unsigned)ntiles, THREADS, 0, st>>>(tiles, t, lam, eta, alpha);
+        k_mfma_grouped8<false><<<(unsigned)ntiles, THREADS8, 0, st>>>(tiles, t, lam, eta, alpha);
     else
         k_mfma_grouped<<<(unsigned)ntiles, THREADS, 0, st>>>(tiles, t, lam, eta, alpha);
     return hipGetLastError();

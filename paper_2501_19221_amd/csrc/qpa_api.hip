@@ -943,7 +943,7 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
         // device) or BF16 requested, and cheaper by the cost model
         DenseSlot ds;
         const bool exact_ok = pl.is_int || a.precision == QPA_PREC_BF16;
-        // np a multiple of the int8 tiles' 256 variables (BF16 tiles take 128)
+        // np a multiple of both kinds of tiles' 128 variables
         const int64_t np = round_up(probs[k].n, MF_BN8), Rp = round_up(a.replicas, MF_BM);
         const bool cheaper =
             dense_step_cost(ctx, np, a.replicas, likely_sparse_i8(probs[k], np) ? probs[k].nnz : -1) <
@@ -965,7 +965,9 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
             // room for byte spins (int8 tiles), eight times the sign bits of BF16 tiles
             ds.o_s0 = tk((size_t)(Rp * np));
             ds.o_s1 = tk((size_t)(Rp * np));
-            const int32_t it = (int32_t)((np / MF_BN) * (Rp / MF_BM));
+            const int32_t it = (int32_t)std::max(
+                (np / MF_BN) * (Rp / MF_BM),
+                (np / MF_BN8) * ((a.replicas + MF_BM8 - 1) / MF_BM8));
             bp.ntiles_max += it;
             bp.inst_tiles_max = std::max(bp.inst_tiles_max, it);
         }
@@ -1900,7 +1902,7 @@ qpa_status qpa_solve_batch(qpa_ctx *ctx, int32_t count, const qpa_problem *probl
         }
         std::vector<MfmaTile> &tv = itiles[k];
         // BF16: tiles of 128 replicas x 128 variables over the padded replicas; int8: 64 x
-        // 256 over the replicas up to R (a tile past them would hold padding only)
+        // 128 over the replicas up to R (a tile past them would hold padding only)
         const int64_t bm = i8 ? MF_BM8 : MF_BM, bn = i8 ? MF_BN8 : MF_BN;
         const int64_t nrb = i8 ? (R + MF_BM8 - 1) / MF_BM8 : ds.Rp / MF_BM;
         tv.reserve((size_t)nrb * (size_t)(ds.np / bn));
