@@ -26,6 +26,7 @@ struct CanonScalars {
     float inv_scale;      // 2^-e
     int32_t flags;        // validation bit mask
     int32_t exp2;         // e
+    int32_t skew;         // CSR: entries right of the diagonal less those left of it
     double max_row;       // max_i sum_j |J_ij| + |b_i|
     double max_abs;       // max |J_ij| (i != j)
 };
