@@ -604,7 +604,7 @@ def main():
         mp = measured_peaks(torch)
         res_peaks = mp
         ref = {"GB/s": mp["hbm_copy_GBps"], "TFLOP/s": mp["bf16_gemm_TFLOPs"]}.get(roof["unit"])
-        if ref is not None and roof["bound"] in ("hbm", "mfma"):
+        if ref is not None and (roof["bound"] == "hbm" or roof["peak"] == PEAK_BF16_TFLOPS):
             roof["frac_of_measured"] = roof["achieved"] / ref
     else:
         res_peaks = None

@@ -23,8 +23,9 @@
 // entry and replica pair.  The total is A_0 + 2^16 A_1 exactly, whatever the signs of the
 // partial sums.  The cached entries are padded with zero weights, so the integer walk has
 // no per-entry branch.
-// Rows whose sum of |w| stays below 2^8 (k_csr_resident8, such as +-1 graphs) pack four
-// replicas a word: see there.
+// This form, with one bit per spin, needs the least LDS.  Where they fit, rows whose sum of
+// |w| stays below 2^8 (such as +-1 graphs) take k_csr_resident8, four replicas a word, and
+// all others k_csr_residentf, spins as floats: see there.
 #include "qpa_internal.h"
 
 #include <type_traits>
@@ -535,6 +536,187 @@ hipError_t launch_res8(const CsrView &c, int64_t R, int64_t Rp, const float *b, 
     return hipGetLastError();
 }
 
+// ---- other rows: spins as floats ----------------------------------------------------------
+// The kernels with spin bits pick a bit and a weight's sign for every entry and replica or
+// pair of replicas.
+// Here a variable's spins are G floats +-1 in LDS: one read and one multiply-add per entry
+// and replica (w s is exact, so the sum is the definition's chain; an unused slot's
+// weight 0 changes no sum, which starts at +0.0 and so is never -0.0).  Two buffers, one
+// barrier a step; the state's -0.0 are loaded as +0.0 (a spin is x's sign bit) as above.
+// n = 2048, 6 entries a row, R = 1024: 1.14 us a step, float couplings 1.99 with spin bits,
+// integer ones (row sums from 2^8 to 2^16) 1.66; n = 512, R = 256: 0.26, 0.56 and 0.43.
+constexpr size_t resf_lds(int64_t n, int64_t nnz, int G) {
+    return 2 * (size_t)n * G * 4 + sizeof(int32_t) * (size_t)(n + 1) + 6 * (size_t)nnz + 16;
+}
+
+template <int G> __device__ __forceinline__ void resf_read(const float *p, float (&s)[G]) {
+    if constexpr (G % 4 == 0) {
+#pragma unroll
+        for (int g = 0; g < G; g += 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(p + g);
+            s[g] = v.x, s[g + 1] = v.y, s[g + 2] = v.z, s[g + 3] = v.w;
+        }
+    } else if constexpr (G == 2) {
+        const float2 v = *reinterpret_cast<const float2 *>(p);
+        s[0] = v.x, s[1] = v.y;
+    } else {
+        s[0] = *p;
+    }
+}
+
+// LDS: spins [2][n][G] float | rp [n+1] int32 | w [nnz] float | col [nnz] uint16
+template <int G, int VPT>
+__global__ void __launch_bounds__(RT) k_csr_residentf(
+    int32_t n, int32_t nnz, int64_t R, int64_t Rp, const int32_t *__restrict__ rp_g,
+    const void *__restrict__ col_g, int32_t col_dt, const void *__restrict__ w_g, int32_t w_dt,
+    int32_t skip_diag, const float *__restrict__ b, float *__restrict__ x,
+    float *__restrict__ m, float *__restrict__ h_last, int32_t t0, int32_t t1,
+    const float *__restrict__ lam, float eta, float alpha) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    float *sp = reinterpret_cast<float *>(lds);
+    int32_t *rp = reinterpret_cast<int32_t *>(sp + 2 * (size_t)n * G);
+    float *wf = reinterpret_cast<float *>(rp + (n + 1));
+    uint16_t *col = reinterpret_cast<uint16_t *>(wf + nnz);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t r0 = (int64_t)blockIdx.x * G;
+    for (int32_t k = tid; k <= n; k += RT) rp[k] = rp_g[k];
+    for (int32_t k = tid; k < nnz; k += RT) {
+        col[k] = (uint16_t)(col_dt == QPA_I16 ? (int32_t) static_cast<const int16_t *>(col_g)[k]
+                                              : static_cast<const int32_t *>(col_g)[k]);
+        wf[k] = ld_as<float>(w_g, w_dt, k);
+    }
+    // cached entries (at most 32 spins read together)
+    constexpr int CA = (16 / VPT) < 8 ? (16 / VPT) : 8;
+    constexpr int CACHE = CA * G > 32 ? 32 / G : CA;
+    int32_t cj[VPT][CACHE], crest[VPT], cend[VPT];
+    float cw[VPT][CACHE], bi[VPT], xs[VPT][G], ms[VPT][G];
+    auto sign = [](float v) {
+        return __uint_as_float((__float_as_uint(v) & 0x80000000u) | 0x3F800000u);
+    };
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * RT;
+        bi[u] = i < n ? b[i] : 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            xs[u][g] = 0.0f;
+            ms[u][g] = 0.0f;
+            if (i < n && r0 + g < R) {
+                xs[u][g] = __fadd_rn(x[(int64_t)i * Rp + r0 + g], 0.0f);
+                ms[u][g] = m[(int64_t)i * Rp + r0 + g];
+            }
+            if (i < n) sp[i * G + g] = xs[u][g] < 0.0f ? -1.0f : 1.0f;
+        }
+    }
+    __syncthreads();
+    bool longer = false;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * RT;
+        int32_t k = 0, k1 = 0, cnt = 0;
+        if (i < n) {
+            k = rp[i];
+            k1 = rp[i + 1];
+        }
+#pragma unroll
+        for (int c = 0; c < CACHE; ++c) {
+            cj[u][c] = 0;
+            cw[u][c] = 0.0f;
+        }
+        for (; k < k1 && cnt < CACHE; ++k) {
+            const int32_t j = col[k];
+            if (skip_diag && j == i) continue;
+#pragma unroll
+            for (int c = 0; c < CACHE; ++c)
+                if (c == cnt) {
+                    cj[u][c] = j * G;
+                    cw[u][c] = wf[k];
+                }
+            ++cnt;
+        }
+        crest[u] = k;
+        cend[u] = k1;
+        longer = longer || k < k1;
+    }
+    const bool rest = __ballot(longer) != 0;       // per wave
+    int cur = 0;
+    auto step = [&](auto keep, float lt) {
+        const float *now = sp + (size_t)cur * n * G;
+        float *nxt = sp + (size_t)(cur ^ 1) * n * G;
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int32_t i = tid + u * RT;
+            if (i >= n) continue;
+            float sv[CACHE][G], acc[G];
+#pragma unroll
+            for (int c = 0; c < CACHE; ++c) resf_read<G>(now + cj[u][c], sv[c]);
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = 0.0f;
+#pragma unroll
+            for (int c = 0; c < CACHE; ++c)
+#pragma unroll
+                for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(cw[u][c], sv[c][g], acc[g]);
+            if (rest)
+                for (int32_t k = crest[u]; k < cend[u]; ++k) {
+                    const int32_t j = col[k];
+                    if (skip_diag && j == i) continue;
+                    float s[G];
+                    resf_read<G>(now + j * G, s);
+#pragma unroll
+                    for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(wf[k], s[g], acc[g]);
+                }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float h = __fadd_rn(acc[g], bi[u]);
+                const float gr = __fadd_rn(__fmul_rn(lt, xs[u][g]), h);
+                const float mn = __fsub_rn(__fmul_rn(alpha, ms[u][g]), __fmul_rn(eta, gr));
+                ms[u][g] = mn;
+                // fmin(1, fmax(-1, y)), also for a NaN (-1)
+                xs[u][g] = __builtin_amdgcn_fmed3f(__fadd_rn(xs[u][g], mn), -1.0f, 1.0f);
+                if (decltype(keep)::value && r0 + g < R) h_last[(int64_t)i * Rp + r0 + g] = h;
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) nxt[i * G + g] = sign(xs[u][g]);
+        }
+        __syncthreads();
+        cur ^= 1;
+    };
+    const int32_t te = h_last ? t1 - 1 : t1;       // steps that keep no field
+    for (int32_t t = t0; t < te; t += 64) {        // the schedule 64 steps at a time
+        const float lv = t + lane < t1 ? lam[t + lane] : 0.0f;
+        const int cnt = min(64, te - t);
+        for (int k = 0; k < cnt; ++k)
+            step(std::false_type{},
+                 __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv), k)));
+    }
+    if (h_last) step(std::true_type{}, lam[te]);
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * RT;
+        if (i >= n) continue;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (r0 + g < R) {
+                x[(int64_t)i * Rp + r0 + g] = xs[u][g];
+                m[(int64_t)i * Rp + r0 + g] = ms[u][g];
+            }
+    }
+}
+
+template <int G, int VPT>
+hipError_t launch_resf(const CsrView &c, int64_t R, int64_t Rp, const float *b, float *x, float *m,
+                       float *h_last, int32_t t0, int32_t t1, const float *lam, float eta,
+                       float alpha, hipStream_t st) {
+    const size_t lds = resf_lds(c.n, c.nnz, G);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_csr_residentf<G, VPT>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipGetLastError();
+    k_csr_residentf<G, VPT><<<(unsigned)((R + G - 1) / G), RT, lds, st>>>(
+        (int32_t)c.n, (int32_t)c.nnz, R, Rp, c.rp, c.col, c.col_dt, c.w, c.w_dt,
+        c.skip_diag ? 1 : 0, b, x, m, h_last, t0, t1, lam, eta, alpha);
+    return hipGetLastError();
+}
+
 template <int G, int VPT, bool INT, bool SW>
 hipError_t launch_one(const CsrView &c, int64_t R, int64_t Rp, const float *b, float *x,
                       float *m, float *h_last, int32_t t0, int32_t t1, const float *lam,
@@ -555,11 +737,15 @@ template <int G, int VPT>
 hipError_t launch_g_v(const CsrView &c, int64_t R, int64_t Rp, bool is_int, double max_row,
                       const float *b, float *x, float *m, float *h_last, int32_t t0, int32_t t1,
                       const float *lam, float eta, float alpha, size_t lds, hipStream_t st) {
-    // max_row bounds every row's sum of |w|.  The byte form is the faster one at every size
-    // and group measured (1.2x to 2x); its LDS (two spin words a variable, the second at a
+    // max_row bounds every row's sum of |w|.  The byte form is the fastest at every size and
+    // group measured (1.2x to 2x over spin bits, 1.3x over float spins); its LDS (two spin words a variable, the second at a
     // fixed offset) may not fit where the 16-bit form's bits do.
     if (is_int && max_row < 256.0 && res8_fits(c.n, c.nnz, G))
         return launch_res8<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
+    // other rows: spins as floats, exact for integers too (every row sum is below 2^24); the
+    // kernels with spin bits are slower (1.4x to 2.3x) and serve what does not fit in LDS so
+    if (resf_lds(c.n, c.nnz, G) <= RES_MAX_LDS)
+        return launch_resf<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
     if (is_int && max_row < 65536.0)
         return launch_one<G, VPT, true, true>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta,
                                               alpha, lds, st);
