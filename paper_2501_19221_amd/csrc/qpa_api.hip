@@ -1036,7 +1036,10 @@ SbmPlan make_sbm_plan(const qpa_problem &p, const qpa_sbm_params &s, int cus = 2
         off += align_up(bytes);
         return o;
     };
-    const size_t RN = (size_t)sp.Rp * (size_t)p.n;
+    // a dense instance's buffers have room for whole tiles of 128 replicas, whatever tiles the
+    // step takes (the size the entry point has always asked for); rows are Rp floats
+    const int64_t room = p.format == QPA_FMT_DENSE ? round_up(sp.Rp, 128) : sp.Rp;
+    const size_t RN = (size_t)room * (size_t)p.n;
     sp.o_q0 = take(sizeof(float) * RN);
     sp.o_q1 = take(sizeof(float) * RN);
     sp.o_p = take(sizeof(float) * RN);
