@@ -319,7 +319,7 @@ qpa_status qpa_relaxed_grad_batch(qpa_ctx *ctx, int32_t count, const qpa_problem
 /* Step kernels, as named by the profiling calls and qpa_batch_paths. */
 typedef enum {
     QPA_PATH_ALL = -1,           /* qpa_profile_read_path: every kernel           */
-    QPA_PATH_DENSE_RESIDENT = 0, /* FP32 couplings held in LDS, all steps at once */
+    QPA_PATH_DENSE_RESIDENT = 0, /* FP32 couplings held on chip, all steps at once */
     QPA_PATH_DENSE_TILED = 1,    /* FP32 couplings streamed, one launch per step  */
     QPA_PATH_DENSE_MFMA = 2,     /* BF16 matrix-core step, one launch per step    */
     QPA_PATH_CSR = 3,            /* sparse step, one launch per step              */

@@ -1542,8 +1542,9 @@ bool csr_rows_by_wave(const qpa_problem &p) {
 }
 
 int64_t energy_partial_blocks(const qpa_problem &p) {
-    if (p.format == QPA_FMT_DENSE)
-        return ((p.n + EROWS - 1) / EROWS + 1) / 2 * ESEG;      // pairs of row blocks
+    if (p.format == QPA_FMT_DENSE)               // pairs of row blocks; a lone block has no
+        return p.n <= EROWS ? 1                  // columns past it to split
+                            : ((p.n + EROWS - 1) / EROWS + 1) / 2 * ESEG;
     if (csr_rows_by_wave(p)) return (p.n + 3) / 4;
     // more blocks than fill the chip add only to the last reduction, one wave a replica
     // (n = 24 million: 93750 blocks took 0.55 ms)

@@ -164,7 +164,7 @@ hipError_t launch_finalize_argmin_batch(const ScoreTask *tasks, int32_t ntask, i
                                         hipStream_t st);
 
 // ---- dense PA steps ------------------------------------------------------------------
-// Small instances: couplings in LDS, all steps of a replica block in one launch.
+// Small instances: couplings in registers, all steps of a replica in one launch.
 bool dense_resident_fits(int64_t n);
 hipError_t launch_dense_resident(int64_t n, int64_t R, const float *J, const float *b,
                                  float *x, float *m, float *h_last, int32_t t0, int32_t t1,
@@ -285,8 +285,8 @@ constexpr size_t RES_MAX_LDS = 160 * 1024;
 size_t csr_resident_lds(int64_t n, int64_t nnz);
 // G for R replicas on `cus` compute units, 0 when the instance does not fit the kernel.
 int csr_resident_group(int64_t n, int64_t R, int cus);
-// max_row (integer couplings only): a bound of every row's sum of |w|; below 2^8 or 2^16 the
-// field sums of four or two replicas share a word.
+// max_row (integer couplings only): a bound of every row's sum of |w|; below 2^8 (or, where the
+// float spins do not fit in LDS, 2^16) the field sums of four (two) replicas share a word.
 hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, bool is_int,
                                double max_row, const float *b, float *x, float *m, float *h_last,
                                int32_t t0, int32_t t1, const float *lam, float eta, float alpha,
