@@ -369,8 +369,8 @@ qpa_status upload_schedule(qpa_ctx *ctx, const qpa_params &a, float *d_lam, hipS
     return QPA_OK;
 }
 
-// Canonicalise + validate; synchronises the stream to read the validation flags.
-qpa_status canonicalise(qpa_ctx *ctx, const qpa_problem &p, const Plan &pl, void *ws,
+// The canonicalising launches of one instance.
+qpa_status canon_launch(qpa_ctx *ctx, const qpa_problem &p, const Plan &pl, void *ws,
                         hipStream_t st) {
     CanonScalars *sc = at<CanonScalars>(ws, pl.o_sc);
     float *bf = at<float>(ws, pl.o_bf);
@@ -387,9 +387,12 @@ qpa_status canonicalise(qpa_ctx *ctx, const qpa_problem &p, const Plan &pl, void
                                  at<double>(ws, pl.o_rabs), at<double>(ws, pl.o_rmax),
                                  at<double>(ws, pl.o_rk), at<double>(ws, pl.o_cpart), sc, st));
     }
-    QPA_HIP(hipMemcpyAsync(ctx->host_sc, sc, sizeof(CanonScalars), hipMemcpyDeviceToHost, st));
-    QPA_HIP(hipStreamSynchronize(st));
-    const int32_t f = ctx->host_sc->flags;
+    return QPA_OK;
+}
+
+// The status of an instance's canonical scalars.
+qpa_status canon_check(qpa_ctx *ctx, const qpa_problem &p, const CanonScalars &sc) {
+    const int32_t f = sc.flags;
     if (f & FLAG_SHAPE)
         return fail(ctx, QPA_E_SHAPE, "CSR row pointers or column indices are inconsistent");
     if (f & FLAG_UNSORTED)
@@ -400,9 +403,85 @@ qpa_status canonicalise(qpa_ctx *ctx, const qpa_problem &p, const Plan &pl, void
                                          : "couplings not symmetric");
     if (f & FLAG_RANGE)
         return fail(ctx, QPA_E_RANGE,
-                    "integer row bound max_i sum_j |J_ij| + |b_i| = %.0f >= 2^24",
-                    ctx->host_sc->max_row);
+                    "integer row bound max_i sum_j |J_ij| + |b_i| = %.0f >= 2^24", sc.max_row);
     return QPA_OK;
+}
+
+// Canonicalise + validate; synchronises the stream to read the validation flags.
+qpa_status canonicalise(qpa_ctx *ctx, const qpa_problem &p, const Plan &pl, void *ws,
+                        hipStream_t st) {
+    const qpa_status s = canon_launch(ctx, p, pl, ws, st);
+    if (s != QPA_OK) return s;
+    QPA_HIP(hipMemcpyAsync(ctx->host_sc, at<CanonScalars>(ws, pl.o_sc), sizeof(CanonScalars),
+                           hipMemcpyDeviceToHost, st));
+    QPA_HIP(hipStreamSynchronize(st));
+    return canon_check(ctx, p, *ctx->host_sc);
+}
+
+// Canonicalisation of a batch's integer instances on the wave-per-row pass with a one-launch
+// finalisation: a table for batched launches (once per coupling / index type pair), each
+// instance also writing its scalars to scall[k].  The others are left to the caller.
+struct CanonTables {
+    struct Group {
+        qpa_dtype w, i;
+        int32_t first, count;
+        int64_t max_n;
+    };
+    std::vector<CanonTask> tasks;
+    std::vector<Group> groups;
+    std::vector<char> batched;
+
+    hipError_t launch(const CanonTask *dev, hipStream_t st) const {
+        hipError_t e = hipSuccess;
+        for (const Group &g : groups)
+            if (e == hipSuccess)
+                e = launch_canon_batch(dev + g.first, g.count, g.w, g.i, g.max_n, st);
+        return e;
+    }
+};
+
+CanonTables canon_tables(int32_t count, const qpa_problem *problems,
+                         const std::vector<Plan> &inst, const std::vector<size_t> &base, char *ws,
+                         CanonScalars *scall) {
+    CanonTables ct;
+    ct.batched.assign((size_t)count, 0);
+    for (qpa_dtype wt : {QPA_I8, QPA_I16, QPA_I32})
+        for (qpa_dtype xt : {QPA_I16, QPA_I32}) {
+            CanonTables::Group g{wt, xt, (int32_t)ct.tasks.size(), 0, 0};
+            for (int32_t k = 0; k < count; ++k) {
+                const qpa_problem &p = problems[k];
+                if (p.coupling_dtype != wt || p.index_dtype != xt || !csr_rows_by_wave(p) ||
+                    p.n > CANON_ROWS_PER_PART)
+                    continue;
+                const Plan &pl = inst[k];
+                char *iw = ws + base[k];
+                CanonTask t{};
+                t.rp = p.row_ptr;
+                t.col = p.col;
+                t.w = p.weights;
+                t.lin = p.linear;
+                t.lin_dt = p.linear_dtype;
+                t.is_qubo = p.kind == QPA_KIND_QUBO ? 1 : 0;
+                t.is_int = dtype_is_int(p.coupling_dtype) &&
+                           (p.linear == nullptr || dtype_is_int(p.linear_dtype));
+                t.n = p.n;
+                t.nnz = p.nnz;
+                t.b_f32 = at<float>(iw, pl.o_bf);
+                t.b_i64 = at<int64_t>(iw, pl.o_bi);
+                t.b_f64 = at<double>(iw, pl.o_bd);
+                t.row_abs = at<double>(iw, pl.o_rabs);
+                t.row_max = at<double>(iw, pl.o_rmax);
+                t.row_k = at<double>(iw, pl.o_rk);
+                t.sc = at<CanonScalars>(iw, pl.o_sc);
+                t.mirror = scall + k;
+                ct.tasks.push_back(t);
+                ct.batched[k] = 1;
+                ++g.count;
+                g.max_n = std::max(g.max_n, p.n);
+            }
+            if (g.count) ct.groups.push_back(g);
+        }
+    return ct;
 }
 
 hipError_t take_event(qpa_ctx *ctx, hipEvent_t *ev) {
@@ -1370,11 +1449,50 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     float *lam = at<float>(ws, rp.o_lam);
     s = upload_schedule(ctx, *params, lam, st);
     if (s != QPA_OK) return s;
-    for (int32_t q = 0; q < count; ++q) {
-        s = canonicalise(ctx, probs[q], rp.inst[q], at<char>(ws, rp.base[q]), st);
-        if (s != QPA_OK) {
-            std::string msg = "instance " + std::to_string(q) + ": " + ctx->err;
-            return fail(ctx, s, "%s", msg.c_str());
+    // every instance canonicalised, then one read-back of all scalars.  They and the table of
+    // the batched launches lie where x will be (rows * Rp floats, at least 256 bytes an
+    // instance; the state is written after the read-back).  96 ER QUBOs: 0.3 ms of launches
+    // and one wait against 3.3 with three launches, a read-back and a wait for each
+    // (gradient of 150 steps 47.7 -> 44.4 ms)
+    {
+        static_assert(sizeof(CanonScalars) + sizeof(CanonTask) <= 256, "room of one row");
+        CanonScalars *scall = at<CanonScalars>(ws, rp.o_x0);
+        CanonTask *dtab = reinterpret_cast<CanonTask *>(scall + count);
+        const CanonTables ct = canon_tables(count, probs, rp.inst, rp.base,
+                                            static_cast<char *>(ws), scall);
+        const size_t cbytes = sizeof(CanonTask) * ct.tasks.size();
+        char *stage = nullptr;
+        s = host_stage(ctx, sizeof(CanonScalars) * (size_t)count + cbytes, &stage);
+        if (s != QPA_OK) return s;
+        CanonScalars *pinned = reinterpret_cast<CanonScalars *>(stage);
+        CanonTask *ptab = reinterpret_cast<CanonTask *>(pinned + count);
+        hipError_t e = hipSuccess;
+        if (!ct.tasks.empty()) {
+            std::copy(ct.tasks.begin(), ct.tasks.end(), ptab);
+            e = hipMemcpyAsync(dtab, ptab, cbytes, hipMemcpyHostToDevice, st);
+            if (e == hipSuccess) e = ct.launch(dtab, st);
+        }
+        for (int32_t q = 0; q < count && e == hipSuccess && s == QPA_OK; ++q) {
+            if (ct.batched[q]) continue;
+            char *iw = at<char>(ws, rp.base[q]);
+            s = canon_launch(ctx, probs[q], rp.inst[q], iw, st);
+            if (s == QPA_OK)
+                e = hipMemcpyAsync(scall + q, at<CanonScalars>(iw, rp.inst[q].o_sc),
+                                   sizeof(CanonScalars), hipMemcpyDeviceToDevice, st);
+        }
+        if (e == hipSuccess && s == QPA_OK)
+            e = hipMemcpyAsync(pinned, scall, sizeof(CanonScalars) * (size_t)count,
+                               hipMemcpyDeviceToHost, st);
+        const hipError_t e2 = hipStreamSynchronize(st);       // the staging block is idle again
+        if (s != QPA_OK) return s;
+        QPA_HIP(e);
+        QPA_HIP(e2);
+        for (int32_t q = 0; q < count; ++q) {
+            s = canon_check(ctx, probs[q], pinned[q]);
+            if (s != QPA_OK) {
+                std::string msg = "instance " + std::to_string(q) + ": " + ctx->err;
+                return fail(ctx, s, "%s", msg.c_str());
+            }
         }
     }
     // instance tables: every instance (element-wise pass) and the CSR ones by group
@@ -1756,52 +1874,8 @@ qpa_status qpa_solve_batch(qpa_ctx *ctx, int32_t count, const qpa_problem *probl
     // scalars into one array, then one read-back of that array
     std::vector<CanonScalars> hsc(count);
     CanonScalars *scall = reinterpret_cast<CanonScalars *>(ws + bp.o_scall);
-    // integer instances on the wave-per-row pass with a one-launch finalisation are
-    // canonicalised by batched launches from a table (once per coupling/index type pair)
-    struct CanonGroup {
-        qpa_dtype w, i;
-        int32_t first, count;
-        int64_t max_n;
-    };
-    std::vector<CanonTask> ctasks;
-    std::vector<CanonGroup> cgroups;
-    std::vector<char> canon_b(count, 0);
-    for (qpa_dtype wt : {QPA_I8, QPA_I16, QPA_I32})
-        for (qpa_dtype xt : {QPA_I16, QPA_I32}) {
-            CanonGroup g{wt, xt, (int32_t)ctasks.size(), 0, 0};
-            for (int32_t k = 0; k < count; ++k) {
-                const qpa_problem &p = problems[k];
-                if (p.coupling_dtype != wt || p.index_dtype != xt || !csr_rows_by_wave(p) ||
-                    p.n > CANON_ROWS_PER_PART)
-                    continue;
-                const Plan &pl = bp.inst[k];
-                char *iw = ws + bp.base[k];
-                CanonTask t{};
-                t.rp = p.row_ptr;
-                t.col = p.col;
-                t.w = p.weights;
-                t.lin = p.linear;
-                t.lin_dt = p.linear_dtype;
-                t.is_qubo = p.kind == QPA_KIND_QUBO ? 1 : 0;
-                t.is_int = dtype_is_int(p.coupling_dtype) &&
-                           (p.linear == nullptr || dtype_is_int(p.linear_dtype));
-                t.n = p.n;
-                t.nnz = p.nnz;
-                t.b_f32 = at<float>(iw, pl.o_bf);
-                t.b_i64 = at<int64_t>(iw, pl.o_bi);
-                t.b_f64 = at<double>(iw, pl.o_bd);
-                t.row_abs = at<double>(iw, pl.o_rabs);
-                t.row_max = at<double>(iw, pl.o_rmax);
-                t.row_k = at<double>(iw, pl.o_rk);
-                t.sc = at<CanonScalars>(iw, pl.o_sc);
-                t.mirror = scall + k;
-                ctasks.push_back(t);
-                canon_b[k] = 1;
-                ++g.count;
-                g.max_n = std::max(g.max_n, p.n);
-            }
-            if (g.count) cgroups.push_back(g);
-        }
+    const CanonTables ct = canon_tables(count, problems, bp.inst, bp.base, ws, scall);
+    const std::vector<CanonTask> &ctasks = ct.tasks;
     // one pinned block: the scalars' read-back, then the table
     const size_t cbytes = sizeof(CanonTask) * ctasks.size();
     char *stage = nullptr;
@@ -1816,14 +1890,12 @@ qpa_status qpa_solve_batch(qpa_ctx *ctx, int32_t count, const qpa_problem *probl
     if (!ctasks.empty()) {
         const CanonTask *dt = reinterpret_cast<const CanonTask *>(ws + bp.o_canon);
         hipError_t e = hipMemcpyAsync(ws + bp.o_canon, ptab, cbytes, hipMemcpyHostToDevice, st);
-        for (const CanonGroup &g : cgroups)
-            if (e == hipSuccess)
-                e = launch_canon_batch(dt + g.first, g.count, g.w, g.i, g.max_n, st);
+        if (e == hipSuccess) e = ct.launch(dt, st);
         if (e != hipSuccess)
             s = fail(ctx, QPA_E_DEVICE, "canonicalisation: %s", hipGetErrorString(e));
     }
     if (s == QPA_OK) s = aux_issue(ctx, count, "canonicalisation", [&](int32_t k, hipStream_t ak) {
-        if (canon_b[k]) return hipSuccess;
+        if (ct.batched[k]) return hipSuccess;
         const Plan &pl = bp.inst[k];
         void *iw = ws + bp.base[k];
         return launch_canon_csr(problems[k], at<float>(iw, pl.o_bf), at<int64_t>(iw, pl.o_bi),
