@@ -23,6 +23,18 @@ def eng():
 
 def _graph(n, dtype, seed):
     rng = np.random.default_rng(seed)
+    if n > 20000:                       # a circulant graph, i -- i + 1 and i -- i + 7
+        i = np.arange(n)
+        w1, w7 = rng.integers(-8, 9, n), rng.integers(-8, 9, n)
+        cols = np.stack([(i + 1) % n, (i - 1) % n, (i + 7) % n, (i - 7) % n], 1)
+        w = np.stack([w1, w1[(i - 1) % n], w7, w7[(i - 7) % n]], 1)
+        order = np.argsort(cols, 1)
+        cols, w = np.take_along_axis(cols, order, 1), np.take_along_axis(w, order, 1)
+        w = w.astype(dtype) if dtype != np.float32 else (w * 0.37).astype(np.float32)
+        return gen.Instance("ising", n, csr=gen.CSR(n, (4 * np.arange(n + 1)).astype(np.int32),
+                                                    cols.reshape(-1).astype(np.int32),
+                                                    w.reshape(-1)),
+                            lin=rng.integers(-3, 4, n).astype(dtype), meta={})
     a = {}
     for _ in range(2 * n):
         i, j = sorted(int(v) for v in rng.integers(0, n, 2))
@@ -42,8 +54,10 @@ def _graph(n, dtype, seed):
     return gen.Instance("ising", n, csr=gen.CSR(n, rp, col, w), lin=lin, meta={})
 
 
-@pytest.mark.parametrize("n", [1, 63, 1025, 4099])
-@pytest.mark.parametrize("R", [1, 4, 5, 17, 64, 130])
+# the last four have more than 2^20 elements, which take the turned tiles
+@pytest.mark.parametrize("n,R", [(n, R) for n in (1, 63, 1025, 4099)
+                                 for R in (1, 4, 5, 17, 64, 130)] +
+                         [(1_048_579, 1), (350_003, 3), (16_411, 65), (4_099, 257)])
 def test_initial_state_scored(eng, n, R):
     from paper_2501_19221_amd import qpa
     import torch
