@@ -217,7 +217,8 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_sp = take(sizeof(int8_t) * R * n);
     pl.o_best = take(sizeof(int32_t) * 4);
     pl.o_words = p.format == QPA_FMT_DENSE
-                     ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64)) : 0;
+                     ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64))
+                     : state && energy_packs_spins(p, pl.R) ? take(n) : 0;
     if (state) off = std::max(off, pl.o_h + align_up(sizeof(float) * Rp * np));
     if (pl.bin_ok) {
         const size_t nnz = (size_t)std::max<int64_t>(p.nnz, 0), M = (size_t)pl.bg.M;

@@ -110,6 +110,9 @@ hipError_t launch_export_spins(int64_t n, int64_t R, const float *x, int64_t ld_
 // Integer: e_i64[r] = objective (and e_f64 = (double)e_i64).  Float: e_f64 only.
 // words: scratch of R * ceil(n/64) uint64 (dense problems only).
 int64_t energy_partial_blocks(const qpa_problem &p);
+// True where launch_energy takes n bytes of `words` for the spins of a variable in one byte
+// (large sparse integer instances with at most 8 replicas; optional there).
+bool energy_packs_spins(const qpa_problem &p, int64_t R);
 // Integer CSR instances with many entries per row run their row scan and energies with
 // one wave per row.
 bool csr_rows_by_wave(const qpa_problem &p);

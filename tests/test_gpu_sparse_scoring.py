@@ -54,10 +54,13 @@ def _graph(n, dtype, seed):
     return gen.Instance("ising", n, csr=gen.CSR(n, rp, col, w), lin=lin, meta={})
 
 
-# the last four have more than 2^20 elements, which take the turned tiles
+# then more than 2^20 elements, which take the turned tiles; then more than 2^20 variables with
+# 2 to 8 replicas, whose spins are packed in bytes
 @pytest.mark.parametrize("n,R", [(n, R) for n in (1, 63, 1025, 4099)
                                  for R in (1, 4, 5, 17, 64, 130)] +
-                         [(1_048_579, 1), (350_003, 3), (16_411, 65), (4_099, 257)])
+                         [(1_048_579, 1), (350_003, 3), (16_411, 65), (4_099, 257)] +
+                         [(1_048_576, 2), (1_048_579, 4), (1_048_577, 5), (1_048_578, 8),
+                          (1_048_575, 8), (1_048_576, 9)])
 def test_initial_state_scored(eng, n, R):
     from paper_2501_19221_amd import qpa
     import torch
