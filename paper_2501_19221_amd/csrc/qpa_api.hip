@@ -968,10 +968,11 @@ std::vector<MfmaTile> by_compute_die(const std::vector<MfmaTile> &in) {
 // stored entry for integer couplings sparse enough for entry lists: at most a tenth of
 // the padded matrix is assumed here, the exact test runs on the device) and x, m.
 constexpr double SPARSE_ADDS_DEFAULT = 1.0e12, DENSE_BPS_DEFAULT = 3.0e12;
-// Variables are priced as if padded to 256, though the tiles pad them to 128.  The choice also
-// sets the size of the workspace that a caller has to bring: an instance that moves to tiles
-// needs their padded buffers besides its sparse ones (n = 513 with 8 entries a row, 8 replicas:
-// 2.1 MB against 0.5 MB), so only those move that are cheaper there by this margin.
+// Tiles have to be the cheaper path with the variables padded to 128, as the tiles pad them, and
+// to 256.  The choice also sets the size of the workspace that a caller has to bring: an
+// instance that moves to tiles needs their padded buffers besides its sparse ones (n = 513
+// with 8 entries a row, 8 replicas: 2.1 MB against 0.5 MB), so only those move that are
+// cheaper there by this margin.
 constexpr int64_t BATCH_PRICE_PAD = 256;
 static_assert(BATCH_PRICE_PAD % MF_BN8 == 0, "a price of whole tiles");
 double csr_step_work(int64_t nnz, int64_t R) { return (double)nnz * (double)R; }
@@ -1031,11 +1032,13 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
         const bool exact_ok = pl.is_int || a.precision == QPA_PREC_BF16;
         // np a multiple of both kinds of tiles' 128 variables
         const int64_t np = round_up(probs[k].n, MF_BN8), Rp = round_up(a.replicas, MF_BM);
-        const int64_t priced = round_up(probs[k].n, BATCH_PRICE_PAD);
+        auto cheaper_at = [&](int64_t pad) {
+            return dense_step_cost(ctx, pad, a.replicas,
+                                   likely_sparse_i8(probs[k], pad) ? probs[k].nnz : -1) <
+                   csr_step_cost(ctx, probs[k].nnz, a.replicas);
+        };
         const bool cheaper =
-            dense_step_cost(ctx, priced, a.replicas,
-                            likely_sparse_i8(probs[k], priced) ? probs[k].nnz : -1) <
-            csr_step_cost(ctx, probs[k].nnz, a.replicas);
+            cheaper_at(np) && cheaper_at(round_up(probs[k].n, BATCH_PRICE_PAD));
         const int32_t force = a.flags & (QPA_BATCH_SPARSE | QPA_BATCH_DENSE);
         if (exact_ok && force != QPA_BATCH_SPARSE && (cheaper || force == QPA_BATCH_DENSE)) {
             ds.cand = true;

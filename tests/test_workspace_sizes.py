@@ -47,6 +47,7 @@ def batch_size(q, probs, a):
     (513, 20, "QPA_I8", 2, 0, False, 1, 466944),
     (513, 8, "QPA_I8", 300, 0, False, 3, 6711552),
     (257, 20, "QPA_F32", 64, 0, True, 1, 269568),
+    (513, 100, "QPA_I8", 2, 0, False, 1, 462592),
     (38, 20, "QPA_I8", 16, 0, False, 3, 210944),
     (300, 100, "QPA_F32", 4, 0, True, 1, 287744),
     (100, 20, "QPA_I8", 64, 0, False, 1, 605952),
