@@ -113,7 +113,21 @@ struct Plan {
     size_t o_sc, o_cpart, o_lam, o_bf, o_bi, o_bd, o_rabs, o_rmax, o_rk, o_Jf, o_Jb, o_x, o_m, o_h,
         o_s0, o_s1, o_part, o_ei, o_ed, o_sp, o_best, o_words, o_boff, o_bcur, o_btsum,
         o_bsrc, o_bdrec, o_bbits, o_bcrow, total;
+    size_t keep;          // without state buffers: bytes before the scratch that a caller's own
+                          // buffers may share (below)
 };
+
+// The canonicalisation's row sums at byte `off`; returns their end.  They are dead once its
+// scalars have been read back, before any state is written.
+size_t place_row_sums(Plan &pl, size_t off) {
+    const size_t n = (size_t)pl.n;
+    pl.o_rabs = off;
+    pl.o_rmax = off + sizeof(double) * n;
+    pl.o_rk = off + sizeof(double) * 2 * n;
+    pl.o_cpart = off + sizeof(double) * 3 * n;
+    return pl.o_cpart +
+           (pl.n > CANON_ROWS_PER_PART ? sizeof(double) * 4 * (size_t)CANON_PARTS : 0);
+}
 
 // Spin words of the streamed layout above which the binned kernels run by default: the
 // per-row gather then misses the L2 on nearly every coupling.
@@ -185,15 +199,29 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_bf = take(sizeof(float) * np);
     pl.o_bi = take(sizeof(int64_t) * n);
     pl.o_bd = take(sizeof(double) * n);
-    pl.o_rabs = take(sizeof(double) * n);
-    pl.o_rmax = take(sizeof(double) * n);
-    pl.o_rk = take(sizeof(double) * n);
-    pl.o_cpart = take(sizeof(double) * 4 * (size_t)CANON_PARTS);
     pl.o_Jf = (pl.path == Path::DenseResident || pl.path == Path::DenseTiled)
                   ? take(sizeof(float) * n * (size_t)dense_ld(pl.n)) : 0;
     pl.o_Jb = pl.path == Path::DenseMfma ? take(sizeof(uint16_t) * np * np) : 0;
-    pl.o_x = state ? take(sizeof(float) * Rp * np) : 0;
-    pl.o_m = state ? take(sizeof(float) * Rp * np) : 0;
+    // from here on every buffer is written after the canonicalisation, whose scratch shares
+    // their place
+    if (!state) {
+        // a caller that keeps its own state scores when it no longer needs it (the spins have
+        // been exported): the partial sums may lie in the same place again
+        pl.o_ei = take(sizeof(int64_t) * R);
+        pl.o_ed = take(sizeof(double) * R);
+        pl.o_sp = take(sizeof(int8_t) * R * n);
+        pl.o_best = take(sizeof(int32_t) * 4);
+        pl.keep = off;
+        const size_t rows = align_up(place_row_sums(pl, off));
+        pl.o_part = take(sizeof(double) * (size_t)pl.eblk * R);
+        pl.o_words = p.format == QPA_FMT_DENSE
+                         ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64)) : 0;
+        pl.total = std::max(off, rows);
+        return pl;
+    }
+    const size_t rows = align_up(place_row_sums(pl, off));
+    pl.o_x = take(sizeof(float) * Rp * np);
+    pl.o_m = take(sizeof(float) * Rp * np);
     size_t sbytes = 0;
     switch (pl.path) {
         case Path::DenseResident: sbytes = 0; break;
@@ -205,7 +233,6 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
             sbytes = sizeof(uint64_t) * (size_t)(Rp / pl.Gs) * (size_t)pl.nwords;
             break;
     }
-    if (!state) sbytes = 0;
     pl.o_s0 = sbytes ? take(sbytes) : 0;
     pl.o_s1 = sbytes ? take(sbytes) : 0;
     // the last step's fields share their place with the scoring scratch: qpa_steps asks for
@@ -218,8 +245,8 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_best = take(sizeof(int32_t) * 4);
     pl.o_words = p.format == QPA_FMT_DENSE
                      ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64))
-                     : state && energy_packs_spins(p, pl.R) ? take(n) : 0;
-    if (state) off = std::max(off, pl.o_h + align_up(sizeof(float) * Rp * np));
+                     : energy_packs_spins(p, pl.R) ? take(n) : 0;
+    off = std::max(off, pl.o_h + align_up(sizeof(float) * Rp * np));
     if (pl.bin_ok) {
         const size_t nnz = (size_t)std::max<int64_t>(p.nnz, 0), M = (size_t)pl.bg.M;
         pl.o_boff = take(sizeof(int32_t) * (M + 1));
@@ -230,7 +257,7 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
         pl.o_bbits = take(nnz);
         pl.o_bcrow = take(sizeof(int32_t) * n);
     }
-    pl.total = off;
+    pl.total = std::max(off, rows);
     return pl;
 }
 
@@ -1086,8 +1113,11 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
     return QPA_OK;
 }
 
-// SBM workspace: the FP32 plan's canonical and scoring buffers (no PA state), then the
-// double-buffered positions, momenta, fields, c0 and the power method's vectors.
+// SBM workspace: the FP32 plan's canonical buffers and scoring outputs (no PA state), then the
+// double-buffered positions, momenta, fields, c0 and the power method's vectors.  The
+// canonicalisation's scratch (before them in time) and the partial sums of the energies
+// (after them) share their place, which is what keeps the size below the one that callers
+// were told when rows of J had no padding and the energies fewer partial sums.
 struct SbmPlan {
     Plan base;
     int64_t Rp, pblk;
@@ -1121,14 +1151,14 @@ SbmPlan make_sbm_plan(const qpa_problem &p, const qpa_sbm_params &s, int cus = 2
     sp.Rp = sbm_rpad(p, s.replicas);
     sp.pblk = pw_blocks(p);
     sp.Gres = (s.flags & QPA_SOLVE_STREAMED) ? 0 : sbm_resident_group(p, s.replicas, cus);
-    size_t off = sp.base.total;
+    size_t off = sp.base.keep;
     auto take = [&](size_t bytes) {
         size_t o = off;
         off += align_up(bytes);
         return o;
     };
     // a dense instance's buffers have room for whole tiles of 128 replicas, whatever tiles the
-    // step takes (the size the entry point has always asked for); rows are Rp floats
+    // step takes; rows are Rp floats
     const int64_t room = p.format == QPA_FMT_DENSE ? round_up(sp.Rp, 128) : sp.Rp;
     const size_t RN = (size_t)room * (size_t)p.n;
     sp.o_q0 = take(sizeof(float) * RN);
@@ -1141,7 +1171,7 @@ SbmPlan make_sbm_plan(const qpa_problem &p, const qpa_sbm_params &s, int cus = 2
     sp.o_pp = take(sizeof(double) * (size_t)sp.pblk);
     sp.o_nrm = take(sizeof(double) * 2);
     sp.o_atab = take(sizeof(float) * (size_t)std::max<int32_t>(s.steps, 1));
-    sp.total = off;
+    sp.total = std::max(off, sp.base.total);
     return sp;
 }
 

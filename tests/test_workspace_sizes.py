@@ -59,3 +59,41 @@ def test_batch(q, n, deg, couplings, R, flags, bf16, count, bound):
     a = q.make_params(R, 10, 0.1, 0.8, 4.0, flags=flags,
                       precision=q.QPA_PREC_BF16 if bf16 else q.QPA_PREC_FP32)
     assert batch_size(q, [problem(q, n, couplings, n * deg)] * count, a) <= bound
+
+
+# couplings, n, replicas: bytes.  Odd sizes, whose canonical rows are padded, and sizes whose
+# energies take the most partial sums
+@pytest.mark.parametrize("couplings,n,R,bound", [
+    ("QPA_F32", 117, 1, 97024),
+    ("QPA_I32", 65, 1, 58112),
+    ("QPA_I32", 129, 1, 439296),
+    ("QPA_F32", 209, 3, 755712),
+    ("QPA_I32", 1001, 200, 9542656),
+])
+def test_dense_solve(q, couplings, n, R, bound):
+    out = ctypes.c_size_t()
+    p = problem(q, n, couplings)
+    a = q.make_params(R, 100, 0.1, 0.8, 1.0)
+    assert q._lib.qpa_workspace_size(None, ctypes.byref(p), ctypes.byref(a),
+                                     ctypes.byref(out)) == q.QPA_OK
+    assert out.value <= bound
+
+
+@pytest.mark.parametrize("couplings,n,R,bound", [
+    ("QPA_I32", 1, 4096, 237568),
+    ("QPA_F32", 5, 1, 48384),
+    ("QPA_I32", 20, 256, 135680),
+    ("QPA_F32", 33, 4096, 2537472),
+    ("QPA_I32", 65, 257, 493312),
+    ("QPA_F32", 127, 31, 374272),
+    ("QPA_F32", 1001, 200, 8536576),
+    ("QPA_F32", 4096, 1024, 141338112),
+    ("QPA_F32", 5001, 2048, 280956416),
+])
+def test_dense_sbm(q, couplings, n, R, bound):
+    out = ctypes.c_size_t()
+    p = problem(q, n, couplings)
+    a = q.make_sbm_params(R, 10, 0.5)
+    assert q._lib.qpa_workspace_size_sbm(None, ctypes.byref(p), ctypes.byref(a),
+                                         ctypes.byref(out)) == q.QPA_OK
+    assert out.value <= bound
