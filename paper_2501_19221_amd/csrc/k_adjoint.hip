@@ -24,8 +24,8 @@
 // product shared with the SBM step, with the element work in its epilogue.  Both add one fused multiply-add
 // per term in ascending column order.
 // Inner products are accumulated in FP64 per thread, reduced per workgroup in a fixed
-// order and written to a per-step table of partial sums, which one last launch reduces in
-// a fixed order: results do not depend on the checkpoint interval or on timing.
+// order and written to a table of partial sums, whose rows (a step each) further launches
+// add up in a fixed order: results do not depend on the checkpoint interval or on timing.
 #include "fp32_tiled.h"
 #include <type_traits>
 
@@ -413,45 +413,44 @@ __global__ void __launch_bounds__(256) k_rel_fill(double *__restrict__ p, int64_
         p[q] = 0.0;
 }
 
-// Final reduction of the per-step partial tables, in a fixed order: thread t sums the
-// slots of steps t, t + 256, ... (d_lambda_t, and the step's d_eta and d_alpha terms,
-// which it leaves in the step's first slots), then thread 0 sums the steps in order.
-__global__ void __launch_bounds__(256) k_rel_finish(int32_t T, int32_t nblk,
-                                                    double *__restrict__ part_steps,
-                                                    const double *__restrict__ part_loss,
-                                                    double *__restrict__ loss,
-                                                    double *__restrict__ d_eta,
-                                                    double *__restrict__ d_alpha,
-                                                    double *__restrict__ d_lam) {
-    const bool grads = d_eta || d_alpha || d_lam;
-    if (grads)
-        for (int32_t t = threadIdx.x; t < T; t += blockDim.x) {
-            double *p = part_steps + (int64_t)t * 3 * nblk;
-            double e = 0.0, a = 0.0, l = 0.0;
-            for (int32_t k = 0; k < nblk; ++k) {
-                e += p[k];
-                a += p[nblk + k];
-                l += p[2 * nblk + k];
-            }
-            p[0] = e;
-            p[nblk] = a;
-            if (d_lam) d_lam[t] = l;
-        }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double L = 0.0;
-        for (int32_t k = 0; k < nblk; ++k) L += part_loss[k];
-        *loss = L;
-        if (grads) {
-            double e = 0.0, a = 0.0;
-            for (int32_t t = 0; t < T; ++t) {
-                e += part_steps[(int64_t)t * 3 * nblk];
-                a += part_steps[(int64_t)t * 3 * nblk + nblk];
-            }
-            if (d_eta) *d_eta = e;
-            if (d_alpha) *d_alpha = a;
-        }
+// Sums of partial rows: wave (kind, row) adds its nblk slots one after the other, 64 loaded
+// together, and clears them.  Kind 0: d_eta terms, 1: d_alpha, 2: d_lambda.
+__global__ void __launch_bounds__(64) k_rel_steps(int32_t t_first, int32_t nblk,
+                                                  double *__restrict__ part,
+                                                  double *__restrict__ steps, int32_t T,
+                                                  double *__restrict__ d_lam) {
+    const int32_t kind = blockIdx.x, t = t_first - (int32_t)blockIdx.y, lane = threadIdx.x;
+    double *p = part + ((int64_t)blockIdx.y * 3 + kind) * nblk;
+    auto load = [&](int32_t k) { return k + lane < nblk ? p[k + lane] : 0.0; };
+    double sum = 0.0, next = load(0);
+    for (int32_t k = 0; k < nblk; k += 64) {
+        const double v = next;
+        next = load(k + 64);
+        if (k + lane < nblk) p[k + lane] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 64; ++i)
+            sum += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
+                                    __builtin_amdgcn_readlane(__double2loint(v), i));
     }
+    if (lane != 0) return;
+    if (kind < 2) steps[(int64_t)kind * T + t] = sum;
+    else if (d_lam) d_lam[t] = sum;
+}
+
+// Final sums: the loss partials and the steps' terms, each in order.
+__global__ void __launch_bounds__(64) k_rel_finish(int32_t T, int32_t nblk,
+                                                   const double *__restrict__ steps,
+                                                   const double *__restrict__ part_loss,
+                                                   double *__restrict__ loss,
+                                                   double *__restrict__ d_eta,
+                                                   double *__restrict__ d_alpha) {
+    const double *p = threadIdx.x == 0 ? part_loss : steps + (threadIdx.x == 1 ? 0 : T);
+    double *out = threadIdx.x == 0 ? loss : threadIdx.x == 1 ? d_eta : d_alpha;
+    if (threadIdx.x > 2 || !out) return;
+    const int32_t n = threadIdx.x == 0 ? nblk : T;
+    double sum = 0.0;
+    for (int32_t k = 0; k < n; ++k) sum += p[k];
+    *out = sum;
 }
 
 template <typename F>
@@ -537,10 +536,16 @@ hipError_t launch_rel_fill(double *p, int64_t count, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_rel_finish(int32_t T, int32_t nblk, double *part_steps,
+hipError_t launch_rel_steps(int32_t t_first, int32_t rows, int32_t nblk, double *part,
+                            double *steps, int32_t T, double *d_lam, hipStream_t st) {
+    k_rel_steps<<<dim3(3, (unsigned)rows), 64, 0, st>>>(t_first, nblk, part, steps, T, d_lam);
+    return hipGetLastError();
+}
+
+hipError_t launch_rel_finish(int32_t T, int32_t nblk, const double *steps,
                              const double *part_loss, double *loss, double *d_eta,
-                             double *d_alpha, double *d_lam, hipStream_t st) {
-    k_rel_finish<<<1, 256, 0, st>>>(T, nblk, part_steps, part_loss, loss, d_eta, d_alpha, d_lam);
+                             double *d_alpha, hipStream_t st) {
+    k_rel_finish<<<1, 64, 0, st>>>(T, nblk, steps, part_loss, loss, d_eta, d_alpha);
     return hipGetLastError();
 }
 

@@ -138,8 +138,10 @@ constexpr int64_t BIN_AUTO_BYTES = (int64_t)4 << 20;
 // cus: compute units of the device (chooses the replica group of the resident sparse
 // kernel; the workspace size does not depend on it).
 // state = false: no PA state buffers (callers that keep their own, such as SBM).
+// scoring = false: only the canonical buffers (the relaxed gradient); the caller places the
+// canonicalisation's row sums.
 Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, int cus = 256,
-               bool state = true) {
+               bool state = true, bool scoring = true) {
     Plan pl{};
     pl.n = p.n;
     pl.R = a.replicas;
@@ -204,6 +206,10 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     pl.o_Jb = pl.path == Path::DenseMfma ? take(sizeof(uint16_t) * np * np) : 0;
     // from here on every buffer is written after the canonicalisation, whose scratch shares
     // their place
+    if (!scoring) {
+        pl.keep = pl.total = off;
+        return pl;
+    }
     if (!state) {
         // a caller that keeps its own state scores when it no longer needs it (the spins have
         // been exported): the partial sums may lie in the same place again
@@ -835,10 +841,18 @@ struct RelPlan {
     std::vector<int32_t> csr_order;   // the CSR ones, grouped, in that order
     std::vector<int32_t> dense_slot;  // per instance: first tile slot (-1 for CSR)
     size_t o_tab_all = 0, o_tab_csr = 0, o_lam = 0, o_x0 = 0, o_x1 = 0, o_m = 0, o_ckpt = 0,
-           o_seg = 0, o_xbar = 0, o_yb = 0, o_mu0 = 0, o_mu1 = 0, o_part = 0, o_ploss = 0,
-           total = 0;
+           o_seg = 0, o_xbar = 0, o_yb = 0, o_mu0 = 0, o_mu1 = 0, o_part = 0, o_steps = 0,
+           o_ploss = 0, total = 0;
     size_t vec_bytes() const { return sizeof(float) * (size_t)rows * (size_t)Rp; }
 };
+
+// Steps whose partial sums the reverse pass keeps before a launch adds them up.  A table of all
+// steps would be the largest buffer of a call of many steps on dense instances, which have a
+// slot for each of their 32 x 32 tiles (n = 5001, R = 4096, 500 steps: 240 MB).
+constexpr int32_t REL_RING = 32;
+// (64 replicas a row at least, and more than 1024 partial sums only for more rows than this)
+static_assert(3 * sizeof(double) + 4 * sizeof(double) * CANON_PARTS / CANON_ROWS_PER_PART <=
+                  64 * sizeof(float), "the row sums of an instance fit its rows");
 
 qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
                          const qpa_params &a, int32_t k, RelPlan &rp) {
@@ -868,7 +882,7 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
             return fail(ctx, s, "%s", msg.c_str());
         }
         // FP32 couplings: a dense instance gets its canonical FP32 matrix
-        const Plan pl = make_plan(probs[q], a32, 0, 256, false);
+        const Plan pl = make_plan(probs[q], a32, 0, 256, false, false);
         rp.inst[q] = pl;
         rp.base[q] = take(pl.total);
         rp.row0[q] = rp.rows;
@@ -934,7 +948,13 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     rp.o_yb = take(V);
     rp.o_mu0 = take(V);
     rp.o_mu1 = take(V);
-    rp.o_part = take(sizeof(double) * 3 * (size_t)rp.nblk * (size_t)std::max(a.steps, 1));
+    // each instance's row sums share the place of its rows of x1, which the steps write
+    for (int32_t q = 0; q < count; ++q)
+        place_row_sums(rp.inst[q], rp.o_x1 + sizeof(float) * (size_t)(rp.row0[q] * rp.Rp) -
+                                       rp.base[q]);
+    rp.o_part = take(sizeof(double) * 3 * (size_t)rp.nblk *
+                     (size_t)std::min(std::max(a.steps, 1), REL_RING));
+    rp.o_steps = take(sizeof(double) * 2 * (size_t)std::max(a.steps, 1));
     rp.o_ploss = take(sizeof(double) * (size_t)rp.nblk);
     rp.total = off;
     return QPA_OK;
@@ -1657,7 +1677,9 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         QPA_HIP(launch_init_state(probs[q].n, R, params->seed + (uint64_t)q, params->sigma0,
                                   X[0] + o, M + o, 1, Rp, Rp, probs[q].n, st));
     }
-    if (grads) QPA_HIP(launch_rel_fill(part, (int64_t)3 * rp.nblk * std::max(T, 1), st));
+    if (grads)
+        QPA_HIP(launch_rel_fill(part, (int64_t)3 * rp.nblk * std::min(std::max(T, 1), REL_RING),
+                                st));
     QPA_HIP(launch_rel_fill(ploss, rp.nblk, st));
     // forward pass, keeping (x, m) at the first step of every segment
     for (int32_t t = 0; t < T; ++t) {
@@ -1677,6 +1699,18 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         s = over_all(REL_MODE_LOSS, a);
         if (s != QPA_OK) return s;
     }
+    // step t of the reverse pass (T - 1, T - 2, ...) writes row (T - 1 - t) % REL_RING of the
+    // table; a full one is added up and cleared
+    double *steps = at<double>(ws, rp.o_steps);
+    auto ring_row = [&](int32_t t) {
+        return part + (size_t)3 * rp.nblk * (size_t)((T - 1 - t) % REL_RING);
+    };
+    auto step_done = [&](int32_t t) -> qpa_status {
+        const int32_t row = (T - 1 - t) % REL_RING;
+        if (row == REL_RING - 1 || t == 0)
+            QPA_HIP(launch_rel_steps(t + row, row + 1, rp.nblk, part, steps, T, d_lambda, st));
+        return QPA_OK;
+    };
     if (grads && T > 0) {
         QPA_HIP(hipMemsetAsync(MU[0], 0, V, st));    // mu_{T+1} = 0
         int cur = 0;
@@ -1700,10 +1734,12 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
                 a.mu_in = MU[cur];
                 a.mu_out = MU[cur ^ 1];
                 a.yb = yb;
-                a.part = part + (size_t)3 * rp.nblk * (size_t)(t1 - 1);
+                a.part = ring_row(t1 - 1);
                 a.slot0 = 0;
                 QPA_HIP(launch_rel_gather(REL_MODE_A, d_all, count, rp.blocks_all, rp.C, 0, 0,
                                           a, st));
+                s = step_done(t1 - 1);
+                if (s != QPA_OK) return s;
                 cur ^= 1;
             }
             for (int32_t t = t1 - 1; t > t0; --t) {    // B(t), then A(t - 1)
@@ -1716,8 +1752,9 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
                 a.mu_in = MU[cur];
                 a.mu_out = MU[cur ^ 1];
                 a.yb = yb;
-                a.part = part + (size_t)3 * rp.nblk * (size_t)(t - 1);
+                a.part = ring_row(t - 1);
                 s = over_all(REL_MODE_BA, a);
+                if (s == QPA_OK) s = step_done(t - 1);
                 if (s != QPA_OK) return s;
                 cur ^= 1;
             }
@@ -1732,8 +1769,8 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
             }
         }
     }
-    QPA_HIP(launch_rel_finish(T, rp.nblk, part, ploss, loss, grads ? d_eta : nullptr,
-                              grads ? d_alpha : nullptr, grads ? d_lambda : nullptr, st));
+    QPA_HIP(launch_rel_finish(T, rp.nblk, steps, ploss, loss, grads ? d_eta : nullptr,
+                              grads ? d_alpha : nullptr, st));
     return QPA_OK;
 }
 

@@ -384,11 +384,16 @@ hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, 
 hipError_t launch_rel_tiles(int32_t mode, int64_t n, const float *J, const float *b,
                             const RelArgs &a, hipStream_t st);
 hipError_t launch_rel_fill(double *p, int64_t count, hipStream_t st);
-// loss = sum of the loss partials; d_lam[t] (if non-NULL), d_eta, d_alpha from the
-// per-step tables [T][3][nblk] (overwritten), all in a fixed order.
-hipError_t launch_rel_finish(int32_t T, int32_t nblk, double *part_steps,
+// Sums of the partial table's rows 0 .. rows - 1 (steps t_first, t_first - 1, ...; [3][nblk] each),
+// every one in the order of its slots: the d_eta and d_alpha terms of step t to steps[t] and
+// steps[T + t], d_lam[t] where non-NULL.  The rows are left zero.
+hipError_t launch_rel_steps(int32_t t_first, int32_t rows, int32_t nblk, double *part,
+                            double *steps, int32_t T, double *d_lam, hipStream_t st);
+// loss = sum of the loss partials; d_eta and d_alpha (if non-NULL) = sums of their steps, all
+// in a fixed order.
+hipError_t launch_rel_finish(int32_t T, int32_t nblk, const double *steps,
                              const double *part_loss, double *loss, double *d_eta,
-                             double *d_alpha, double *d_lam, hipStream_t st);
+                             double *d_alpha, hipStream_t st);
 
 // ---- Simulated Bifurcation Machine (App. B) -----------------------------------------
 // State q, p [n][Rp] FP32 (replica fastest).  Rp: replicas padded to the dense product's 32

@@ -97,3 +97,21 @@ def test_dense_sbm(q, couplings, n, R, bound):
     assert q._lib.qpa_workspace_size_sbm(None, ctypes.byref(p), ctypes.byref(a),
                                          ctypes.byref(out)) == q.QPA_OK
     assert out.value <= bound
+
+
+# (couplings, n), replicas, steps, checkpoint interval: bytes
+@pytest.mark.parametrize("couplings,n,R,T,k,bound", [
+    ("QPA_F32", 1, 4096, 500, 50, 3892480),
+    ("QPA_I32", 1, 1, 1, 1, 45568),
+    ("QPA_F32", 5, 1, 5, 2, 94976),
+    ("QPA_I32", 33, 64, 100, 10, 1080832),
+    ("QPA_F32", 128, 128, 500, 1, 66621952),
+    ("QPA_F32", 300, 100, 20, 20, 11527424),
+    ("QPA_I32", 1001, 200, 100, 10, 66074112),
+    ("QPA_F32", 2048, 65, 500, 50, 206635264),
+    ("QPA_F32", 5001, 4096, 500, 50, 14897613312),
+])
+def test_relaxed_dense(q, couplings, n, R, T, k, bound):
+    p = problem(q, n, couplings)
+    a = q.make_params(R, T, 0.1, 0.8, 1.0)
+    assert q.qpa_workspace_size_relaxed(None, p, a, k) <= bound
