@@ -299,7 +299,7 @@ __global__ void __launch_bounds__(RT) k_csr_resident(
 // exact integers below 2^24), the seven operations of the definition, and 1.25 to gather the
 // four signs (byte permutes of the sign bytes; a -0.0 would count as negative there, so
 // the state's -0.0 are loaded as +0.0, and x + m' never makes one).  CACHE entries of each
-// row are in registers; waves whose rows hold at most 6 skip the rest.
+// row are in registers; workgroups whose rows hold at most 6 skip the rest.
 // The second spin buffer lies at a constant offset, so that both copies of the step share
 // their address registers; the schedule is loaded 64 steps at a time and broadcast.  n = 2048,
 // R = 1024, 6 entries a row: 0.845 us a step against 1.66 for the kernel above; n = 512:
@@ -333,7 +333,7 @@ constexpr bool res8_fits(int64_t n, int64_t nnz, int G) {
 }
 
 // LDS: spins [n][NW] uint32 | at RES8_BUF the second spins | rp [n+1] int32 | w [nnz] int32 |
-//      col [nnz] uint16
+//      col [nnz] uint16 | flag
 template <int G, int VPT>
 __global__ void __launch_bounds__(RT) k_csr_resident8(
     int32_t n, int32_t nnz, int64_t R, int64_t Rp, const int32_t *__restrict__ rp_g,
@@ -348,9 +348,11 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
     int32_t *rp = reinterpret_cast<int32_t *>(sp + RES8_BUF / 4 + (size_t)n * NW);
     int32_t *wi = rp + (n + 1);
     uint16_t *col = reinterpret_cast<uint16_t *>(wi + nnz);
+    int32_t *many = wi + nnz + (nnz + 1) / 2;       // past the columns, in the 16 spare bytes
     const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;   // VPT * nt >= n
     const int64_t r0 = (int64_t)blockIdx.x * G;
 
+    if (tid == 0) *many = 0;
     for (int32_t k = tid; k <= n; k += nt) rp[k] = rp_g[k];
     for (int32_t k = tid; k < nnz; k += nt) {
         col[k] = (uint16_t)(col_dt == QPA_I16 ? (int32_t) static_cast<const int16_t *>(col_g)[k]
@@ -427,7 +429,12 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
     bool longer = false;
 #pragma unroll
     for (int u = 0; u < VPT; ++u) longer = longer || crest[u] < cend[u];
-    const bool few = __ballot(most > 6) == 0, rest = __ballot(longer) != 0;   // per wave
+    const bool rest = __ballot(longer) != 0;       // per wave
+    // of the whole workgroup: the two step loops hold a barrier each, and all waves have to
+    // wait at the same one
+    if (most > 6) *many = 1;
+    __syncthreads();
+    const bool few = __builtin_amdgcn_readfirstlane(*many) == 0;
 
     // one step from buffer CUR into the other; NC entries of each row from the registers
     auto step = [&](auto nc, auto cur, auto keep, float lt) {
