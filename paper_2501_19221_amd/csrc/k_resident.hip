@@ -436,7 +436,11 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
     __syncthreads();
     const bool few = __builtin_amdgcn_readfirstlane(*many) == 0;
 
-    // one step from buffer CUR into the other; NC entries of each row from the registers
+    // one step from buffer CUR into the other; NC entries of each row from the registers, the
+    // others from LDS.  With one variable a thread, where a step waits for its longest row, they
+    // are read four at a time (n = 200, 20 entries a row, R = 64: 1.3 us a step against 2.65);
+    // with more, the code's registers cost the other rows as much.
+    constexpr int BATCH = 4;
     auto step = [&](auto nc, auto cur, auto keep, float lt) {
         constexpr int NC = decltype(nc)::value, CUR = decltype(cur)::value;
         const uint32_t *s_now = sp + CUR * (RES8_BUF / 4);
@@ -457,15 +461,44 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
                     acc[u][p] = pk_mad(cw[u][c], s[u][c][p], c == 0 ? cneg[u] : acc[u][p]);
         if (rest) {
 #pragma unroll
-            for (int u = 0; u < VPT; ++u)
-                for (int32_t k = crest[u]; k < cend[u]; ++k) {
-                    const int32_t j = col[k];
-                    if (skip_diag && j == tid + u * nt) continue;
-                    const uint32_t w2 = ((uint32_t)wi[k] & 0xFFFFu) * 0x10001u;
+            for (int u = 0; u < VPT; ++u) {
+                const int32_t i = tid + u * nt;
+                if constexpr (VPT == 1) {
+                    // BATCH entries' reads together; one past the row or on the diagonal
+                    // adds nothing
+                    for (int32_t k = crest[u]; k < cend[u]; k += BATCH) {
+                        int32_t j[BATCH];
+                        uint32_t w2[BATCH], sv[BATCH][NW];
 #pragma unroll
-                    for (int p = 0; p < NW; ++p)
-                        acc[u][p] = pk_mad(w2, s_now[j * NW + p], acc[u][p]);
+                        for (int d = 0; d < BATCH; ++d) {
+                            const int32_t kk = min(k + d, cend[u] - 1);
+                            j[d] = col[kk];
+                            w2[d] = ((uint32_t)wi[kk] & 0xFFFFu) * 0x10001u;
+                        }
+#pragma unroll
+                        for (int d = 0; d < BATCH; ++d) {
+                            const bool out = (k + d >= cend[u]) | (skip_diag & (j[d] == i));
+                            w2[d] &= (uint32_t)out - 1u;
+#pragma unroll
+                            for (int p = 0; p < NW; ++p) sv[d][p] = s_now[j[d] * NW + p];
+                        }
+#pragma unroll
+                        for (int d = 0; d < BATCH; ++d)
+#pragma unroll
+                            for (int p = 0; p < NW; ++p)
+                                acc[u][p] = pk_mad(w2[d], sv[d][p], acc[u][p]);
+                    }
+                } else {
+                    for (int32_t k = crest[u]; k < cend[u]; ++k) {
+                        const int32_t j = col[k];
+                        if (skip_diag && j == i) continue;
+                        const uint32_t w2 = ((uint32_t)wi[k] & 0xFFFFu) * 0x10001u;
+#pragma unroll
+                        for (int p = 0; p < NW; ++p)
+                            acc[u][p] = pk_mad(w2, s_now[j * NW + p], acc[u][p]);
+                    }
                 }
+            }
         }
 #pragma unroll
         for (int u = 0; u < VPT; ++u) {
