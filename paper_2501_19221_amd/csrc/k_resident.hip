@@ -23,9 +23,9 @@
 // entry and replica pair.  The total is A_0 + 2^16 A_1 exactly, whatever the signs of the
 // partial sums.  The cached entries are padded with zero weights, so the integer walk has
 // no per-entry branch.
-// This form, with one bit per spin, needs the least LDS.  Where they fit, rows whose sum of
-// |w| stays below 2^8 (such as +-1 graphs) take k_csr_resident8, four replicas a word, and
-// all others k_csr_residentf, spins as floats: see there.
+// This form, with one bit per spin, needs the least LDS and the fewest registers.  Rows whose
+// sum of |w| stays below 2^8 (such as +-1 graphs) can take k_csr_resident8, four replicas a
+// word, and all can take k_csr_residentf, spins as floats: the rule stands at res_form.
 #include "qpa_internal.h"
 
 #include <type_traits>
@@ -773,19 +773,56 @@ hipError_t launch_one(const CsrView &c, int64_t R, int64_t Rp, const float *b, f
     return hipGetLastError();
 }
 
+// The form of an instance.  All give the same bits (integer rows sum to less than 2^24).  What is
+// fastest depends on how the columns spread over the LDS banks too; the lines below are
+// drawn so that random graphs (n variables, d entries a row) and Chimera graphs are no
+// slower than with spin bits, the form that always fits.  us a step:
+//   * groups of at most 4 replicas have about one workgroup per compute unit: bytes or float
+//     spins where they fit, 0.6x to 0.9x the time of bits.  With four or more variables a
+//     thread the byte form spills registers, and float spins are faster (random, n = 3000,
+//     d = 3, R = 1024: bits 4.08, bytes 4.28, floats 3.57).
+//   * groups of 8, other rows than byte sums: two workgroups of 1024 threads share a compute
+//     unit if they use bits, one if they use float spins (registers).  Integer rows below
+//     2^16 take bits (random, n = 500, d = 6, R = 4096: 2.36 against 4.00; Chimera n = 512:
+//     1.48 and 1.99).  Float rows take bits where one variable a thread and more than one
+//     workgroup per compute unit meet (random 3.24 against 3.94, Chimera 1.86 and 2.00) and
+//     floats elsewhere (R = 2048: random 2.44 and 2.05, Chimera 1.30 and 1.05; n = 1152,
+//     R = 4096: Chimera 4.57 and 4.08).  Integer rows of 2^16 or more take floats (random,
+//     n = 1000, d = 8, R = 4096: 8.14 against 8.98).
+//   * groups of 8 in bytes: faster (n = 500, d = 6, R = 4096: 2.15) unless only bits leave room
+//     in LDS for a second workgroup and there is one (random, n = 1000, d = 6, R = 4096: 4.37
+//     against 4.75), or two variables a thread, whose byte form spills, hold very few
+//     entries (random, n = 1500, d = 3, R = 2048: 2.42 against 2.69; at d = 6 both 4.0;
+//     Chimera, n = 1152: 1.86 against 1.70).
+enum class ResForm { Bytes, Floats, Bits };
+
+template <int G, int VPT>
+ResForm res_form(const CsrView &c, int64_t R, bool is_int, double max_row, size_t lds, int cus) {
+    const bool queue = (R + G - 1) / G > cus;       // more workgroups than compute units
+    const bool floats = resf_lds(c.n, c.nnz, G) <= RES_MAX_LDS;
+    auto two = [](size_t bytes) { return 2 * bytes <= RES_MAX_LDS; };
+    if (is_int && max_row < 256.0 && res8_fits(c.n, c.nnz, G) && !(VPT >= 4 && floats)) {
+        const bool bits = G == 8 && (VPT == 2 ? c.nnz < 4 * c.n
+                                              : queue && two(lds) && !two(res8_lds(c.n, c.nnz, G)));
+        return bits ? ResForm::Bits : ResForm::Bytes;
+    }
+    if (!floats) return ResForm::Bits;
+    if (G < 8 || (is_int && max_row >= 65536.0)) return ResForm::Floats;
+    return is_int || (VPT == 1 && queue) ? ResForm::Bits : ResForm::Floats;
+}
+
 template <int G, int VPT>
 hipError_t launch_g_v(const CsrView &c, int64_t R, int64_t Rp, bool is_int, double max_row,
-                      const float *b, float *x, float *m, float *h_last, int32_t t0, int32_t t1,
-                      const float *lam, float eta, float alpha, size_t lds, hipStream_t st) {
-    // max_row bounds every row's sum of |w|.  The byte form is the fastest at every size and
-    // group measured (1.2x to 2x over spin bits, 1.3x over float spins); its LDS (two spin words a variable, the second at a
-    // fixed offset) may not fit where the 16-bit form's bits do.
-    if (is_int && max_row < 256.0 && res8_fits(c.n, c.nnz, G))
-        return launch_res8<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
-    // other rows: spins as floats, exact for integers too (every row sum is below 2^24); the
-    // kernels with spin bits are slower (1.4x to 2.3x) and serve what does not fit in LDS so
-    if (resf_lds(c.n, c.nnz, G) <= RES_MAX_LDS)
-        return launch_resf<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
+                      int cus, const float *b, float *x, float *m, float *h_last, int32_t t0,
+                      int32_t t1, const float *lam, float eta, float alpha, size_t lds,
+                      hipStream_t st) {
+    switch (res_form<G, VPT>(c, R, is_int, max_row, lds, cus)) {
+        case ResForm::Bytes:
+            return launch_res8<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
+        case ResForm::Floats:
+            return launch_resf<G, VPT>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta, alpha, st);
+        case ResForm::Bits: break;
+    }
     if (is_int && max_row < 65536.0)
         return launch_one<G, VPT, true, true>(c, R, Rp, b, x, m, h_last, t0, t1, lam, eta,
                                               alpha, lds, st);
@@ -822,9 +859,9 @@ int csr_resident_group(int64_t n, int64_t R, int cus) {
 }
 
 hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, bool is_int,
-                               double max_row, const float *b, float *x, float *m, float *h_last,
-                               int32_t t0, int32_t t1, const float *lam, float eta, float alpha,
-                               hipStream_t st) {
+                               double max_row, int cus, const float *b, float *x, float *m,
+                               float *h_last, int32_t t0, int32_t t1, const float *lam, float eta,
+                               float alpha, hipStream_t st) {
     if (t1 <= t0) return hipSuccess;
     const size_t lds = csr_resident_lds(c.n, c.nnz);
     if (lds > RES_MAX_LDS || c.n > RES_MAX_N || c.nnz > INT32_MAX) return hipErrorInvalidValue;
@@ -832,8 +869,8 @@ hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, b
     if (v * G > 16) return hipErrorInvalidValue;
 #define QPA_RES_CASE(GG, VV)                                                                   \
     if (G == GG && v == VV)                                                                    \
-        return launch_g_v<GG, VV>(c, R, Rp, is_int, max_row, b, x, m, h_last, t0, t1, lam, eta, \
-                                  alpha, lds, st);
+        return launch_g_v<GG, VV>(c, R, Rp, is_int, max_row, cus, b, x, m, h_last, t0, t1, lam, \
+                                  eta, alpha, lds, st);
     QPA_RES_CASE(8, 1)
     QPA_RES_CASE(8, 2)
     QPA_RES_CASE(4, 1)

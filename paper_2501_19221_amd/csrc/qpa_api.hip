@@ -701,8 +701,9 @@ qpa_status run_steps_inner(qpa_ctx *ctx, const qpa_problem &p, const qpa_params 
                       pl.is_qubo, p.nnz};
             // the canonical row bound (sum of |w| plus |b|, read back by canonicalise)
             // bounds every row's sum of |w|
-            QPA_HIP(launch_csr_resident(c, pl.G, pl.R, pl.Rp, pl.is_int, ctx->host_sc->max_row, bf,
-                                        x, m, h, t0, t1, lam, a.eta, a.alpha, st));
+            QPA_HIP(launch_csr_resident(c, pl.G, pl.R, pl.Rp, pl.is_int, ctx->host_sc->max_row,
+                                        ctx->cus, bf, x, m, h, t0, t1, lam, a.eta, a.alpha,
+                                        st));
             launches = 1;
             break;
         }

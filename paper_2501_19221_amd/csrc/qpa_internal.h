@@ -288,12 +288,12 @@ constexpr size_t RES_MAX_LDS = 160 * 1024;
 size_t csr_resident_lds(int64_t n, int64_t nnz);
 // G for R replicas on `cus` compute units, 0 when the instance does not fit the kernel.
 int csr_resident_group(int64_t n, int64_t R, int cus);
-// max_row (integer couplings only): a bound of every row's sum of |w|; below 2^8 (or, where the
-// float spins do not fit in LDS, 2^16) the field sums of four (two) replicas share a word.
+// max_row (integer couplings only): a bound of every row's sum of |w|; below 2^8 (2^16) the field
+// sums of four (two) replicas may share a word.
 hipError_t launch_csr_resident(const CsrView &c, int G, int64_t R, int64_t Rp, bool is_int,
-                               double max_row, const float *b, float *x, float *m, float *h_last,
-                               int32_t t0, int32_t t1, const float *lam, float eta, float alpha,
-                               hipStream_t st);
+                               double max_row, int cus, const float *b, float *x, float *m,
+                               float *h_last, int32_t t0, int32_t t1, const float *lam, float eta,
+                               float alpha, hipStream_t st);
 int csr_group_size(int64_t R);
 int64_t csr_words_per_group(int64_t n, int G);
 hipError_t launch_csr_pack_spins(int64_t n, int64_t Rp, int G, const float *x, uint64_t *sbits,
