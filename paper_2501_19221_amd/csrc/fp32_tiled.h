@@ -305,14 +305,18 @@ __global__ void __launch_bounds__(TL::THREADS) k_fp32_mfma_step(int64_t n, int64
 enum Fp32Tile : int { FP32_TILE_L, FP32_TILE_M, FP32_TILE_N, FP32_TILE_S };
 
 // The tile for an n x Rp product: the one whose workgroups, spread over the compute
-// units, finish first; among equals the largest (least traffic).
+// units, finish first; among equals the largest (least traffic).  An element of the smaller
+// tiles takes longer where they fill the chip: n = 4096, R = 4096 1014, 1078, 1242 and
+// 1298 us a step.  Counted alike, the smallest was taken for n = 209, R = 65536 (143 us, 109
+// with the largest) and n = 1500, R = 8192 (461 and 311).
 inline Fp32Tile fp32_tile_of(int64_t n, int64_t Rp) {
-    auto cost = [&](int64_t bi, int64_t br) {
+    auto cost = [&](int64_t bi, int64_t br, double element) {
         const int64_t tiles = ((n + bi - 1) / bi) * ((Rp + br - 1) / br);
-        return (tiles + 255) / 256 * (bi * br);
+        return (double)((tiles + 255) / 256 * (bi * br)) * element;
     };
     if (Rp > 32 * 65535) return FP32_TILE_L;        // grid y
-    const int64_t l = cost(128, 128), m = cost(64, 64), nn = cost(64, 32), s = cost(32, 32);
+    const double l = cost(128, 128, 1.0), m = cost(64, 64, 1.06), nn = cost(64, 32, 1.22),
+                 s = cost(32, 32, 1.28);
     if (l <= m && l <= nn && l <= s) return FP32_TILE_L;
     if (m <= nn && m <= s) return FP32_TILE_M;
     return nn <= s ? FP32_TILE_N : FP32_TILE_S;
