@@ -1180,8 +1180,12 @@ template <class TL> unsigned wide_grid(int64_t np, int64_t rlive) {
 
 // Replicas (in 32s) of the small tiles an instance runs on, 0: the 16384-element tiles.  The
 // tile with the least estimated step: a fixed part plus, per chunk of 128 variables, the
-// time of the workgroups that share a compute unit (us, fitted to steps of 256 <= n <= 4096,
-// 64 <= R <= 1024 within 10 %).  Measured, us per step:
+// time of the workgroups that share a compute unit, plus the state of those past the second,
+// which no longer overlaps.  The estimates are off by up to 30 % (the 16384-element tiles at
+// n = 4096, R = 1024: 28.6 for 38.5 us), all to the same side where it is close: over 276 sizes
+// (n = 100 to 6000, R = 1 to 16384) the tile taken is within 9 % of the fastest, 0.2 % on
+// average.  Without the last part it was up to 2.1 times the fastest where there are many
+// more replicas than variables.  Measured, us per step:
 //   n     R     32 x 32   32 x 64   32 x 128   16384-element
 //   256   256     5.6       7.1       9.2         8.3
 //   1001  200     6.1       8.4      11.7        12.8
@@ -1191,6 +1195,8 @@ template <class TL> unsigned wide_grid(int64_t np, int64_t rlive) {
 //   4096  128    20.5      15.5      21.1        31.0
 //   4096  256    35.3      23.7      22.3        28.4
 //   4096  512    69.7      45.0      30.8        29.5
+//   300   4096   21.1      18.6      13.0        11.1
+//   768   2048   20.3      19.9      14.5        13.2
 int small_tile_replicas(int64_t np, int64_t Rp, int64_t rlive) {
     const double nc = (double)(np / KC);
     auto rounds = [](int64_t tiles) { return (double)((tiles + 255) / 256); };
@@ -1198,9 +1204,11 @@ int small_tile_replicas(int64_t np, int64_t Rp, int64_t rlive) {
                   rounds(Rp % 256 == 0 ? (np / 64) * (Rp / 256) : (np / 128) * (Rp / 128));
     int fr = 0;
     const double fixed[3] = {4.2, 5.7, 9.0}, chunk[3] = {0.26, 0.30, 0.40};
+    const double state[3] = {2.0, 4.0, 2.0};
     for (int k = 0; k < 3; ++k) {
         const int64_t br = 32 << k;
-        const double t = fixed[k] + chunk[k] * nc * rounds((np / 32) * ((rlive + br - 1) / br));
+        const double r = rounds((np / 32) * ((rlive + br - 1) / br));
+        const double t = fixed[k] + chunk[k] * nc * r + state[k] * std::max(0.0, r - 2.0);
         if (t < best) {
             best = t;
             fr = 1 << k;
