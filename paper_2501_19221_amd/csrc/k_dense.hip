@@ -31,8 +31,9 @@ __device__ __forceinline__ float spin_of(float x) { return x >= 0.0f ? 1.0f : -1
 // variables sit in one register, the same in each row of 16 lanes, and the DPP operand
 // row_newbcast:j hands spin j of the row to every lane: one vector instruction per
 // term and nothing on the scalar unit.  The registers come from
-//   * n <= 64: the wave's own spins, its four rows of lanes copied across by
-//     v_permlane32_swap / v_permlane16_swap -- no LDS, no barrier;
+//   * n <= 64: the wave's own spins, the rows of lanes that hold any copied across by
+//     v_permlane32_swap / v_permlane16_swap -- no LDS, no barrier (with more waves than the
+//     chip holds these count: n = 12, R = 65536 3.25 us a step, 3.75 with all rows copied);
 //   * larger n: the replica's spins in LDS (two buffers), one barrier per step.
 // Terms j >= n are +0.0 (zero couplings, +1 spins): a sum that starts at +0.0 never becomes
 // -0.0 under round-to-nearest, so adding them changes no bit.  The schedule is read 64
@@ -124,7 +125,14 @@ __global__ void __launch_bounds__(NC <= 4 ? 64 : NC <= 8 ? 128 : 256, 1) k_dense
         for (int k = 0; k < te; ++k) {
             const float lt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv), k));
             float sv[ONE ? 4 : NC];
-            if constexpr (ONE) {
+            if constexpr (NC == 1) {
+                sv[0] = s;                           // the variables' own row
+            } else if constexpr (NC == 2) {
+                const auto h = __builtin_amdgcn_permlane16_swap(
+                    __float_as_uint(s), __float_as_uint(s), false, false);   // rows 0 0, 1 1
+                sv[0] = __uint_as_float(h[0]);
+                sv[1] = __uint_as_float(h[1]);
+            } else if constexpr (ONE) {
                 dr_rows(s, sv);
             } else {
 #pragma unroll
