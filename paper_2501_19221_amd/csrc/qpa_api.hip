@@ -833,6 +833,7 @@ struct RelPlan {
     // [0, nblk_all); a gather step writes each CSR group's blocks and then each dense
     // instance's tiles, [0, nblk_gather); nblk = the larger of the two
     int32_t nblk = 0, nblk_all = 0, nblk_gather = 0;
+    int32_t ring = 1;              // steps the table of partial sums has room for
     struct Group {
         int32_t wdt, idt, first, count, slot0;
         int64_t items, blocks;     // rows, and blocks of 64 rows (the gather's work items)
@@ -847,9 +848,10 @@ struct RelPlan {
     size_t vec_bytes() const { return sizeof(float) * (size_t)rows * (size_t)Rp; }
 };
 
-// Steps whose partial sums the reverse pass keeps before a launch adds them up.  A table of all
-// steps would be the largest buffer of a call of many steps on dense instances, which have a
-// slot for each of their 32 x 32 tiles (n = 5001, R = 4096, 500 steps: 240 MB).
+// Steps whose partial sums the reverse pass keeps at least before a launch adds them up.  A
+// table of all steps would be the largest buffer of a call of many steps on dense instances,
+// which have a slot for each of their tiles (n = 5001, R = 4096, 500 steps: 240 MB); it has
+// as many rows as fit the space that 128 x 128 tiles would take for all steps.
 constexpr int32_t REL_RING = 32;
 // (64 replicas a row at least, and more than 1024 partial sums only for more rows than this)
 static_assert(3 * sizeof(double) + 4 * sizeof(double) * CANON_PARTS / CANON_ROWS_PER_PART <=
@@ -932,10 +934,18 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         slot += (int32_t)rel_tile_blocks(probs[q].n, rp.Rp);
     }
     rp.nblk_gather = slot;
+    int32_t large = rp.nblk_gather;       // slots with tiles of 128 x 128
+    for (int32_t q = 0; q < count; ++q)
+        if (rp.dense_slot[q] >= 0)
+            large += (int32_t)((probs[q].n + 127) / 128 * ((rp.Rp + 127) / 128) -
+                               rel_tile_blocks(probs[q].n, rp.Rp));
     rp.blocks_all = 0;
     for (int32_t q = 0; q < count; ++q) rp.blocks_all += (probs[q].n + 63) / 64;
     rp.nblk_all = (int32_t)rel_gather_blocks(rp.blocks_all, rp.C);
     rp.nblk = std::max(rp.nblk_gather, rp.nblk_all);
+    const int32_t T = std::max(a.steps, 1);
+    rp.ring = (int32_t)std::min<int64_t>(
+        T, std::max<int64_t>(REL_RING, (int64_t)T * std::max(large, rp.nblk_all) / rp.nblk));
     const size_t V = rp.vec_bytes();
     rp.o_tab_all = take(sizeof(RelInst) * (size_t)count);
     rp.o_tab_csr = take(sizeof(RelInst) * std::max<size_t>(rp.csr_order.size(), 1));
@@ -953,9 +963,8 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
     for (int32_t q = 0; q < count; ++q)
         place_row_sums(rp.inst[q], rp.o_x1 + sizeof(float) * (size_t)(rp.row0[q] * rp.Rp) -
                                        rp.base[q]);
-    rp.o_part = take(sizeof(double) * 3 * (size_t)rp.nblk *
-                     (size_t)std::min(std::max(a.steps, 1), REL_RING));
-    rp.o_steps = take(sizeof(double) * 2 * (size_t)std::max(a.steps, 1));
+    rp.o_part = take(sizeof(double) * 3 * (size_t)rp.nblk * (size_t)rp.ring);
+    rp.o_steps = take(sizeof(double) * 2 * (size_t)T);
     rp.o_ploss = take(sizeof(double) * (size_t)rp.nblk);
     rp.total = off;
     return QPA_OK;
@@ -1679,8 +1688,7 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
                                   X[0] + o, M + o, 1, Rp, Rp, probs[q].n, st));
     }
     if (grads)
-        QPA_HIP(launch_rel_fill(part, (int64_t)3 * rp.nblk * std::min(std::max(T, 1), REL_RING),
-                                st));
+        QPA_HIP(launch_rel_fill(part, (int64_t)3 * rp.nblk * rp.ring, st));
     QPA_HIP(launch_rel_fill(ploss, rp.nblk, st));
     // forward pass, keeping (x, m) at the first step of every segment
     for (int32_t t = 0; t < T; ++t) {
@@ -1700,15 +1708,15 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         s = over_all(REL_MODE_LOSS, a);
         if (s != QPA_OK) return s;
     }
-    // step t of the reverse pass (T - 1, T - 2, ...) writes row (T - 1 - t) % REL_RING of the
+    // step t of the reverse pass (T - 1, T - 2, ...) writes row (T - 1 - t) % ring of the
     // table; a full one is added up and cleared
     double *steps = at<double>(ws, rp.o_steps);
     auto ring_row = [&](int32_t t) {
-        return part + (size_t)3 * rp.nblk * (size_t)((T - 1 - t) % REL_RING);
+        return part + (size_t)3 * rp.nblk * (size_t)((T - 1 - t) % rp.ring);
     };
     auto step_done = [&](int32_t t) -> qpa_status {
-        const int32_t row = (T - 1 - t) % REL_RING;
-        if (row == REL_RING - 1 || t == 0)
+        const int32_t row = (T - 1 - t) % rp.ring;
+        if (row == rp.ring - 1 || t == 0)
             QPA_HIP(launch_rel_steps(t + row, row + 1, rp.nblk, part, steps, T, d_lambda, st));
         return QPA_OK;
     };
