@@ -25,7 +25,12 @@
 // per term in ascending column order.
 // Inner products are accumulated in FP64 per thread, reduced per workgroup in a fixed
 // order and written to a table of partial sums, whose rows (a step each) further launches
-// add up in a fixed order: results do not depend on the checkpoint interval or on timing.
+// add up in a fixed order: results do not depend on timing.  The steps at the ends of the
+// checkpoint segments form their sums in the element-wise pass, the others in the product
+// launches.  Both group them alike where all instances are sparse and of one (coupling,
+// index) type: their results do not depend on the checkpoint interval either.  With dense
+// instances or several types the gradients of two intervals agree to the rounding of the
+// FP64 sums (the loss, which no interval changes, bit for bit).
 #include "fp32_tiled.h"
 #include <type_traits>
 
@@ -183,7 +188,8 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
 
 // Row launches: the CSR product with its input staged through LDS (the gather modes), and
 // the element-wise pass (REL_A) over every instance's rows with the same work items, so
-// that a step's partial sums are grouped alike whichever launch computes them.  Work item
+// that for sparse instances of one type a step's partial sums are grouped alike whichever
+// launch computes them.  Work item
 // = (block of 64 consecutive rows of one instance, 64-replica chunk c); a workgroup of 16
 // waves takes its items in the order below.  Sixteen lanes own a row, four replicas each,
 // so a wave owns four rows; the input vector (x or mu of the instance, the chunk's 64
@@ -194,8 +200,8 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
 // each staged value serves all 64 rows of the block instead of one gather per entry.
 // A row's entries come in windows of 64, 16 of them in a register across its lanes.  A step
 // of the walk broadcasts one entry's LDS offset and weight within the row's lanes as DPP
-// operands of the address addition and of the four multiply-adds, so a step serves an
-// entry of each of the wave's rows with one 16-byte read and five vector instructions.
+// operands of the address addition and of a move, so a step serves an entry of each of the
+// wave's rows with one 16-byte read and six vector instructions (four multiply-adds).
 // Lanes whose row has no further entry in the range read a column of zeros with weight 0
 // (which changes no sum).  The windows past the range's entries are loaded before the walk.
 // 96 ER QUBOs of 100 to 2000 variables (p = 0.1, 13.4 million entries), 64 replicas: 95 us
@@ -361,7 +367,7 @@ __global__ void __launch_bounds__(GR_THREADS)
                         kc += cnt;
                         more = __ballot(cnt == 16 * GR_WIN) != 0;
                         // (a wave without an entry in the range keeps its windows: n = 20000, 8
-                        // entries a row, R = 16, 180 launches: 33.0 ms loading them again, 29.6)
+                        // entries a row, R = 16, 60 steps: 33.0 ms loading them again, 29.1)
                         if (__builtin_expect(steps[0] != 0, 1)) load();
 #pragma unroll
                         for (int r = 0; r < GR_WIN; ++r) {
