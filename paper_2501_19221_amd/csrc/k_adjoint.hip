@@ -203,7 +203,10 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
 // operands of the address addition and of a move, so a step serves an entry of each of the
 // wave's rows with one 16-byte read and six vector instructions (four multiply-adds).
 // Lanes whose row has no further entry in the range read a column of zeros with weight 0
-// (which changes no sum).  The windows past the range's entries are loaded before the walk.
+// (which changes no sum).  The windows past the range's entries are loaded before the walk;
+// with FEW entries per row and range most ranges hold none of a wave's, and it keeps its
+// windows then (n = 20000, 8 entries a row, R = 16, 60 steps: 33.0 ms loading them again,
+// 29.1 so; where nearly every range has some, the check costs 1 %).
 // 96 ER QUBOs of 100 to 2000 variables (p = 0.1, 13.4 million entries), 64 replicas: 95 us
 // a launch, against 230 with one row's entry per step (an address, a weight and a product
 // for every entry) and items in the given order.  The 3.4 GB of staged values read at 128
@@ -251,7 +254,7 @@ struct GrWalk {
 // Two workgroups per CU (64 KiB of LDS each, 8 waves per SIMD): the walks are bound by
 // the latency of their LDS reads, which the second workgroup's waves hide, as they hide
 // each range's staging.
-template <int MODE, typename TW, typename TI>
+template <int MODE, typename TW, typename TI, bool FEW>
 __global__ void __launch_bounds__(GR_THREADS)
     __attribute__((amdgpu_waves_per_eu(8))) k_rel_gather(const RelInst *__restrict__ insts,
                                                            int32_t ninst, int64_t blocks,
@@ -366,9 +369,8 @@ __global__ void __launch_bounds__(GR_THREADS)
                         }
                         kc += cnt;
                         more = __ballot(cnt == 16 * GR_WIN) != 0;
-                        // (a wave without an entry in the range keeps its windows: n = 20000, 8
-                        // entries a row, R = 16, 60 steps: 33.0 ms loading them again, 29.1)
-                        if (__builtin_expect(steps[0] != 0, 1)) load();
+                        if (FEW && steps[0] == 0) break;     // no entry: the windows stay
+                        load();
 #pragma unroll
                         for (int r = 0; r < GR_WIN; ++r) {
                             if (steps[r] == 0) break;
@@ -421,44 +423,51 @@ __global__ void __launch_bounds__(256) k_rel_fill(double *__restrict__ p, int64_
         p[q] = 0.0;
 }
 
-// Sums of partial rows: wave (kind, row) adds its nblk slots one after the other, 64 loaded
-// together, and clears them.  Kind 0: d_eta terms, 1: d_alpha, 2: d_lambda.
-__global__ void __launch_bounds__(64) k_rel_steps(int32_t t_first, int32_t nblk,
-                                                  double *__restrict__ part,
-                                                  double *__restrict__ steps, int32_t T,
-                                                  double *__restrict__ d_lam) {
-    const int32_t kind = blockIdx.x, t = t_first - (int32_t)blockIdx.y, lane = threadIdx.x;
-    double *p = part + ((int64_t)blockIdx.y * 3 + kind) * nblk;
-    auto load = [&](int32_t k) { return k + lane < nblk ? p[k + lane] : 0.0; };
+// p[0] + p[1] + ... + p[n - 1], one after the other, in every lane of a wave; 64 are loaded
+// together.  f(k) for each k that this lane loaded.
+template <typename F>
+__device__ __forceinline__ double rel_ordered_sum(const double *p, int32_t n, F &&f) {
+    const int32_t lane = threadIdx.x & 63;
+    auto load = [&](int32_t k) { return k + lane < n ? p[k + lane] : 0.0; };
     double sum = 0.0, next = load(0);
-    for (int32_t k = 0; k < nblk; k += 64) {
+    for (int32_t k = 0; k < n; k += 64) {
         const double v = next;
         next = load(k + 64);
-        if (k + lane < nblk) p[k + lane] = 0.0;
+        if (k + lane < n) f(k + lane);
 #pragma unroll
         for (int i = 0; i < 64; ++i)
             sum += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
                                     __builtin_amdgcn_readlane(__double2loint(v), i));
     }
-    if (lane != 0) return;
+    return sum;
+}
+
+// Sums of partial rows: wave (kind, row) adds its nblk slots and clears them.  Kind 0: d_eta
+// terms, 1: d_alpha, 2: d_lambda.
+__global__ void __launch_bounds__(64) k_rel_steps(int32_t t_first, int32_t nblk, double *part,
+                                                  double *__restrict__ steps, int32_t T,
+                                                  double *__restrict__ d_lam) {
+    const int32_t kind = blockIdx.x, t = t_first - (int32_t)blockIdx.y;
+    double *p = part + ((int64_t)blockIdx.y * 3 + kind) * nblk;
+    const double sum = rel_ordered_sum(p, nblk, [&](int32_t k) { p[k] = 0.0; });
+    if (threadIdx.x != 0) return;
     if (kind < 2) steps[(int64_t)kind * T + t] = sum;
     else if (d_lam) d_lam[t] = sum;
 }
 
-// Final sums: the loss partials and the steps' terms, each in order.
+// Final sums, a wave each: the loss partials and the steps' terms.
 __global__ void __launch_bounds__(64) k_rel_finish(int32_t T, int32_t nblk,
                                                    const double *__restrict__ steps,
                                                    const double *__restrict__ part_loss,
                                                    double *__restrict__ loss,
                                                    double *__restrict__ d_eta,
                                                    double *__restrict__ d_alpha) {
-    const double *p = threadIdx.x == 0 ? part_loss : steps + (threadIdx.x == 1 ? 0 : T);
-    double *out = threadIdx.x == 0 ? loss : threadIdx.x == 1 ? d_eta : d_alpha;
-    if (threadIdx.x > 2 || !out) return;
-    const int32_t n = threadIdx.x == 0 ? nblk : T;
-    double sum = 0.0;
-    for (int32_t k = 0; k < n; ++k) sum += p[k];
-    *out = sum;
+    const int32_t kind = blockIdx.x;
+    double *out = kind == 0 ? loss : kind == 1 ? d_eta : d_alpha;
+    if (!out) return;
+    const double *p = kind == 0 ? part_loss : steps + (int64_t)(kind - 1) * T;
+    const double sum = rel_ordered_sum(p, kind == 0 ? nblk : T, [](int32_t) {});
+    if (threadIdx.x == 0) *out = sum;
 }
 
 template <typename F>
@@ -476,17 +485,18 @@ hipError_t rel_by_dtypes(int32_t wdt, int32_t idt, F &&f) {
 
 template <int MODE>
 hipError_t rel_gather_launch(const RelInst *insts, int32_t ninst, int64_t blocks, int32_t C,
-                             int32_t wdt, int32_t idt, const RelArgs &a, hipStream_t st) {
+                             int32_t wdt, int32_t idt, bool few, const RelArgs &a, hipStream_t st) {
     const unsigned g = (unsigned)rel_gather_blocks(blocks, C);
     if (g % 8) return hipErrorInvalidValue;       // the item order assumes whole dies
     if (MODE == REL_A) {
-        k_rel_gather<REL_A, float, int32_t><<<g, GR_THREADS, 0, st>>>(insts, ninst, blocks, C, a);
+        k_rel_gather<REL_A, float, int32_t, false><<<g, GR_THREADS, 0, st>>>(insts, ninst, blocks, C, a);
         return hipGetLastError();
     }
     return rel_by_dtypes(wdt, idt, [&](auto wtag, auto itag) {
         using TW = decltype(wtag);
         using TI = decltype(itag);
-        k_rel_gather<MODE, TW, TI><<<g, GR_THREADS, 0, st>>>(insts, ninst, blocks, C, a);
+        if (few) k_rel_gather<MODE, TW, TI, true><<<g, GR_THREADS, 0, st>>>(insts, ninst, blocks, C, a);
+        else k_rel_gather<MODE, TW, TI, false><<<g, GR_THREADS, 0, st>>>(insts, ninst, blocks, C, a);
         return hipGetLastError();
     });
 }
@@ -508,14 +518,14 @@ int64_t rel_gather_blocks(int64_t blocks, int32_t C) {
 }
 
 hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, int64_t blocks,
-                             int32_t C, int32_t wdt, int32_t idt, const RelArgs &a,
-                             hipStream_t st) {
+                             int32_t C, int32_t wdt, int32_t idt, bool few,
+                             const RelArgs &a, hipStream_t st) {
     switch (mode) {
-        case REL_FWD: return rel_gather_launch<REL_FWD>(insts, ninst, blocks, C, wdt, idt, a, st);
-        case REL_LOSS: return rel_gather_launch<REL_LOSS>(insts, ninst, blocks, C, wdt, idt, a, st);
-        case REL_A: return rel_gather_launch<REL_A>(insts, ninst, blocks, C, wdt, idt, a, st);
-        case REL_B: return rel_gather_launch<REL_B>(insts, ninst, blocks, C, wdt, idt, a, st);
-        case REL_BA: return rel_gather_launch<REL_BA>(insts, ninst, blocks, C, wdt, idt, a, st);
+        case REL_FWD: return rel_gather_launch<REL_FWD>(insts, ninst, blocks, C, wdt, idt, few, a, st);
+        case REL_LOSS: return rel_gather_launch<REL_LOSS>(insts, ninst, blocks, C, wdt, idt, few, a, st);
+        case REL_A: return rel_gather_launch<REL_A>(insts, ninst, blocks, C, wdt, idt, few, a, st);
+        case REL_B: return rel_gather_launch<REL_B>(insts, ninst, blocks, C, wdt, idt, few, a, st);
+        case REL_BA: return rel_gather_launch<REL_BA>(insts, ninst, blocks, C, wdt, idt, few, a, st);
     }
     return hipErrorInvalidValue;
 }
@@ -553,7 +563,7 @@ hipError_t launch_rel_steps(int32_t t_first, int32_t rows, int32_t nblk, double 
 hipError_t launch_rel_finish(int32_t T, int32_t nblk, const double *steps,
                              const double *part_loss, double *loss, double *d_eta,
                              double *d_alpha, hipStream_t st) {
-    k_rel_finish<<<1, 64, 0, st>>>(T, nblk, steps, part_loss, loss, d_eta, d_alpha);
+    k_rel_finish<<<3, 64, 0, st>>>(T, nblk, steps, part_loss, loss, d_eta, d_alpha);
     return hipGetLastError();
 }
 

@@ -837,6 +837,7 @@ struct RelPlan {
     struct Group {
         int32_t wdt, idt, first, count, slot0;
         int64_t items, blocks;     // rows, and blocks of 64 rows (the gather's work items)
+        bool few;                  // under one entry per row and range of 256 columns
     };
     std::vector<Group> groups;     // CSR instances by (coupling, index) type
     std::vector<int32_t> all_order;   // instance indices, longest row blocks first
@@ -912,19 +913,23 @@ qpa_status make_rel_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
         const int32_t wdt = probs[q].coupling_dtype, idt = probs[q].index_dtype;
         bool found = false;
         for (auto &g : rp.groups) found = found || (g.wdt == wdt && g.idt == idt);
-        if (!found) rp.groups.push_back({wdt, idt, 0, 0, 0, 0, 0});
+        if (!found) rp.groups.push_back({wdt, idt, 0, 0, 0, 0, 0, false});
     }
     int32_t slot = 0;
     for (auto &g : rp.groups) {
         g.first = (int32_t)rp.csr_order.size();
+        int64_t entries = 0, ranges = 0;      // of all rows
         for (const int32_t q : rp.all_order)
             if (probs[q].format == QPA_FMT_CSR && probs[q].coupling_dtype == g.wdt &&
                 probs[q].index_dtype == g.idt) {
                 rp.csr_order.push_back(q);
                 g.items += probs[q].n;
                 g.blocks += (probs[q].n + 63) / 64;
+                entries += probs[q].nnz;
+                ranges += probs[q].n * ((probs[q].n + 255) / 256);
             }
         g.count = (int32_t)rp.csr_order.size() - g.first;
+        g.few = entries < ranges;
         g.slot0 = slot;
         slot += (int32_t)rel_gather_blocks(g.blocks, rp.C);
     }
@@ -1655,7 +1660,7 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
             RelArgs b = a;
             b.slot0 = g.slot0;
             QPA_HIP(launch_rel_gather(mode, d_csr + g.first, g.count, g.blocks, rp.C, g.wdt,
-                                      g.idt, b, st));
+                                      g.idt, g.few, b, st));
         }
         for (int32_t q = 0; q < count; ++q) {
             if (rp.dense_slot[q] < 0) continue;
@@ -1746,7 +1751,7 @@ qpa_status relaxed_run(qpa_ctx *ctx, int32_t count, const qpa_problem *probs,
                 a.part = ring_row(t1 - 1);
                 a.slot0 = 0;
                 QPA_HIP(launch_rel_gather(REL_MODE_A, d_all, count, rp.blocks_all, rp.C, 0, 0,
-                                          a, st));
+                                          false, a, st));
                 s = step_done(t1 - 1);
                 if (s != QPA_OK) return s;
                 cur ^= 1;

@@ -373,12 +373,13 @@ int64_t rel_tile_blocks(int64_t n, int64_t Rp);
 // ignored by REL_MODE_A), in blocks of 64 rows: the CSR product modes (FWD, LOSS, B, BA)
 // with the product's input staged through LDS, and the element-wise REL_MODE_A over the
 // rows of every instance; `blocks` = the sum of ceil(n / 64) over the table's instances;
-// rel_gather_blocks = the launch's workgroups (each writes one partial slot).
+// rel_gather_blocks = the launch's workgroups (each writes one partial slot).  few: a row holds
+// few entries per 256 columns (a matter of speed only).
 constexpr int64_t REL_GATHER_BLOCKS_MAX = 512;     // two resident workgroups per CU
 int64_t rel_gather_blocks(int64_t blocks, int32_t C);
 hipError_t launch_rel_gather(int32_t mode, const RelInst *insts, int32_t ninst, int64_t blocks,
-                             int32_t C, int32_t wdt, int32_t idt, const RelArgs &a,
-                             hipStream_t st);
+                             int32_t C, int32_t wdt, int32_t idt, bool few,
+                             const RelArgs &a, hipStream_t st);
 // Dense instance (FP32 canonical J, n x dense_ld(n)) through the tiled product; the state pointers
 // of `a` point at the instance's first row (Rp a multiple of 32).  Not REL_MODE_A.
 hipError_t launch_rel_tiles(int32_t mode, int64_t n, const float *J, const float *b,
