@@ -225,7 +225,15 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
         pl.total = std::max(off, rows);
         return pl;
     }
-    const size_t rows = align_up(place_row_sums(pl, off));
+    size_t rows = 0;
+    if (p.format == QPA_FMT_DENSE) {
+        rows = align_up(place_row_sums(pl, off));
+    } else {                                       // sparse workspaces have the room
+        pl.o_rabs = take(sizeof(double) * n);
+        pl.o_rmax = take(sizeof(double) * n);
+        pl.o_rk = take(sizeof(double) * n);
+        pl.o_cpart = take(sizeof(double) * 4 * (size_t)CANON_PARTS);
+    }
     pl.o_x = take(sizeof(float) * Rp * np);
     pl.o_m = take(sizeof(float) * Rp * np);
     size_t sbytes = 0;
