@@ -211,7 +211,8 @@ __device__ __forceinline__ void rel_write_partials(const RelArgs &a, int64_t wg,
 // a launch, against 230 with one row's entry per step (an address, a weight and a product
 // for every entry) and items in the given order.  The 3.4 GB of staged values read at 128
 // bytes a clock take 46 us, the padded entries and the staging bring that to 67, and the
-// vector instructions alone take about 65.
+// vector instructions alone take about 65.  (Eight waves a SIMD leave 64 registers: none are
+// spilled for int16 couplings and columns, 2 to 4 for most other types.)
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int GR_THREADS = 1024, GR_WAVES = GR_THREADS / 64, GR_RPW = 4;
 constexpr int GR_ROWS = GR_WAVES * GR_RPW;       // 64 rows per block

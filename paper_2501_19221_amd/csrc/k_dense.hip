@@ -41,8 +41,9 @@ __device__ __forceinline__ float spin_of(float x) { return x >= 0.0f ? 1.0f : -1
 // Measured: n = 20, R = 256, 2000 steps 244 us (signs from a ballot, a bit extraction
 // and a sign flip per term: 448 us); n = 100, R = 150, 1000 steps 378 us (J and the
 // spins of several replicas in LDS, one LDS read of each per term: 3.98 ms); 5 cycles per
-// term.  Past 208 columns the registers run out; the per-step product takes 5.2 us there
-// (n = 209, R = 256) against 0.64 us here at 208.
+// term.  Past 208 columns the registers run out.  Up to there no number of replicas makes the
+// per-step product the faster form: us a step at n = 208 here and at n = 209 there, R = 256 0.74
+// and 5.1, R = 4096 7.2 and 10.5, R = 16384 27.6 and 28.4, R = 65536 109.5 and 108.2.
 constexpr int DR_MAXC = 13;              // columns in groups of 16: n <= 208 (registers)
 
 // acc += s_j J_j for the 16 columns of a group, ascending.  The leading nop separates a

@@ -11,13 +11,17 @@
 //     keeps 2 x 2 accumulators of 32 x 32 and the two halves are summed in LDS at the end;
 //   * 8 state waves: they load the tile's x and m into registers while the reduction
 //     runs, then wait for the field and run the PA update and write x, m and the spins.
-// What bounds the reduction is the rate at which a compute unit can read J and the spins
-// (measured 37..53 GB/s per CU, 16..22 bytes a cycle, however they are loaded), so a tile is
-// chosen for its bytes: spins travel as sign bits (1 bit per variable and replica; as
-// pre-expanded words of 4 bits each before), which makes replicas nearly free, and a tile
-// of 256 x 64 then needs 160 bytes per reduction index against 272 for 128 x 128.
-// sk4096 (n = 4096, R = 1024): 38.5 us per step against 42.7 with 4-bit words and 128 x
-// 128 tiles (320 bytes).
+// No single resource bounds it.  Counters at n = 4096: a workgroup takes 63.6 thousand clock
+// cycles with 256 of them (R = 1024) and 62.5 with 128 (R = 512), so nothing that they share
+// slows them; the matrix cores are busy for 32.8 thousand, the rest is the expansion, LDS
+// reads and loads that the eight matrix waves do not fully overlap (leaving any one of them
+// out saves 6 us of 38.9, the products 17.7).  That a step takes 38.7 us with every compute
+// unit busy and 32.2 with half of them is the clock: 11 % fewer cycles a microsecond.
+// Fewer bytes per reduction index still pay: spins travel as sign bits (1 bit per variable
+// and replica; as pre-expanded words of 4 bits each before), which makes replicas nearly
+// free, and a tile of 256 x 64 then needs 160 bytes against 272 for 128 x 128.  sk4096 (n =
+// 4096, R = 1024): 38.5 us per step against 42.7 with 4-bit words and 128 x 128 tiles (320
+// bytes).
 // Chunks are staged through LDS with direct global->LDS loads issued by the matrix waves
 // only (NST stages, NST-1 chunks in flight): per chunk the BN x 128 bf16 block of J
 // (loads of 16 bytes per lane, each filling 4 rows of 256 bytes) and the sign bits

@@ -303,7 +303,10 @@ __global__ void __launch_bounds__(RT) k_csr_resident(
 // The second spin buffer lies at a constant offset, so that both copies of the step share
 // their address registers; the schedule is loaded 64 steps at a time and broadcast.  n = 2048,
 // R = 1024, 6 entries a row: 0.845 us a step against 1.66 for the kernel above; n = 512:
-// 0.33 against 0.59; n = 4000, 3 entries a row: 1.43 against 2.23.
+// 0.33 against 0.59; n = 4000, 3 entries a row: 1.43 against 2.23.  With several variables and
+// replicas a thread the registers do not hold all of this (spilled: 39 with 2 variables in
+// groups of 8, 26 and 55 with 4 in groups of 2 and 4, 55 and 165 with 8 in groups of 1 and
+// 2; none elsewhere), which the rule at res_form takes into account.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pk_mad(uint32_t w2, uint32_t s, uint32_t acc) {
@@ -585,6 +588,7 @@ hipError_t launch_res8(const CsrView &c, int64_t R, int64_t Rp, const float *b, 
 // barrier a step; the state's -0.0 are loaded as +0.0 (a spin is x's sign bit) as above.
 // n = 2048, 6 entries a row, R = 1024: 1.14 us a step, float couplings 1.99 with spin bits,
 // integer ones (row sums from 2^8 to 2^16) 1.66; n = 512, R = 256: 0.26, 0.56 and 0.43.
+// (12 registers are spilled with 4 variables in groups of 4, 49 with 8 in groups of 2.)
 constexpr size_t resf_lds(int64_t n, int64_t nnz, int G) {
     return 2 * (size_t)n * G * 4 + sizeof(int32_t) * (size_t)(n + 1) + 6 * (size_t)nnz + 16;
 }
