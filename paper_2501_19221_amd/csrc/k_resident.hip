@@ -304,8 +304,8 @@ __global__ void __launch_bounds__(RT) k_csr_resident(
 // their address registers; the schedule is loaded 64 steps at a time and broadcast.  n = 2048,
 // R = 1024, 6 entries a row: 0.845 us a step against 1.66 for the kernel above; n = 512:
 // 0.33 against 0.59; n = 4000, 3 entries a row: 1.43 against 2.23.  With several variables and
-// replicas a thread the registers do not hold all of this (spilled: 39 with 2 variables in
-// groups of 8, 26 and 55 with 4 in groups of 2 and 4, 55 and 165 with 8 in groups of 1 and
+// replicas a thread the registers do not hold all of this (spilled: 28 with 2 variables in
+// groups of 8, 3 and 33 with 4 in groups of 2 and 4, 49 and 116 with 8 in groups of 1 and
 // 2; none elsewhere), which the rule at res_form takes into account.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
@@ -323,6 +323,29 @@ __device__ __forceinline__ uint32_t sign_bytes(const float *x, int count) {
     if (count <= 2) return (a >> 7) & 0x0101u;
     const uint32_t b = __builtin_amdgcn_perm(u(3), u(2), 0x07030C0Cu);
     return ((a | b) >> 7) & 0x01010101u;
+}
+
+// The state of the G replicas r0 .. of variable i, zeros where there is none.  Every load is
+// made (of the last variable or replica again where there is none): a load behind a condition
+// is waited for there, one after the other (Chimera C16, R = 1024: a call of one step 105 us
+// with them, 71 so).
+template <int G>
+__device__ __forceinline__ void res_state(int32_t i, int32_t n, int64_t r0, int64_t R, int64_t Rp,
+                                          const float *x, const float *m, float (&xs)[G],
+                                          float (&ms)[G]) {
+    const int64_t o = (int64_t)(i < n ? i : n - 1) * Rp + r0;
+    const int last = (int)(R - r0 < G ? R - r0 : G) - 1;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        xs[g] = x[o + (g < last ? g : last)];
+        ms[g] = m[o + (g < last ? g : last)];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const bool in = i < n && g <= last;
+        xs[g] = in ? xs[g] : 0.0f;
+        ms[g] = in ? ms[g] : 0.0f;
+    }
 }
 
 // the second spin buffer's LDS address: a constant, so that both are offsets of one address
@@ -374,15 +397,13 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
         const int32_t i = tid + u * nt;
+        res_state<G>(i, n, r0, R, Rp, x, m, xs[u], ms[u]);
+    }
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            xs[u][g] = 0.0f;
-            ms[u][g] = 0.0f;
-            if (i < n && r0 + g < R) {
-                xs[u][g] = __fadd_rn(x[(int64_t)i * Rp + r0 + g], 0.0f);
-                ms[u][g] = m[(int64_t)i * Rp + r0 + g];
-            }
-        }
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * nt;
+#pragma unroll
+        for (int g = 0; g < G; ++g) xs[u][g] = __fadd_rn(xs[u][g], 0.0f);
         if (i < n)
 #pragma unroll
             for (int p = 0; p < NW; ++p) {
@@ -537,6 +558,9 @@ __global__ void __launch_bounds__(RT) k_csr_resident8(
             };
             const int cnt = min(64, te - t);
             int k = 0;
+            // the loop's place among the 64-byte lines of the instruction cache is worth up to 6 %
+            // (Chimera C16, R = 1024: 0.755 to 0.802 us a step at four offsets); this fixes it
+            asm volatile(".p2align 6" ::: "memory");
             for (; k + 2 <= cnt; k += 2) {
                 step(nc, b0, std::false_type{}, l(k));
                 step(nc, b1, std::false_type{}, l(k + 1));
@@ -588,7 +612,6 @@ hipError_t launch_res8(const CsrView &c, int64_t R, int64_t Rp, const float *b, 
 // barrier a step; the state's -0.0 are loaded as +0.0 (a spin is x's sign bit) as above.
 // n = 2048, 6 entries a row, R = 1024: 1.14 us a step, float couplings 1.99 with spin bits,
 // integer ones (row sums from 2^8 to 2^16) 1.66; n = 512, R = 256: 0.26, 0.56 and 0.43.
-// (12 registers are spilled with 4 variables in groups of 4, 49 with 8 in groups of 2.)
 constexpr size_t resf_lds(int64_t n, int64_t nnz, int G) {
     return 2 * (size_t)n * G * 4 + sizeof(int32_t) * (size_t)(n + 1) + 6 * (size_t)nnz + 16;
 }
@@ -641,14 +664,14 @@ __global__ void __launch_bounds__(RT) k_csr_residentf(
     for (int u = 0; u < VPT; ++u) {
         const int32_t i = tid + u * RT;
         bi[u] = i < n ? b[i] : 0.0f;
+        res_state<G>(i, n, r0, R, Rp, x, m, xs[u], ms[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int32_t i = tid + u * RT;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            xs[u][g] = 0.0f;
-            ms[u][g] = 0.0f;
-            if (i < n && r0 + g < R) {
-                xs[u][g] = __fadd_rn(x[(int64_t)i * Rp + r0 + g], 0.0f);
-                ms[u][g] = m[(int64_t)i * Rp + r0 + g];
-            }
+            xs[u][g] = __fadd_rn(xs[u][g], 0.0f);
             if (i < n) sp[i * G + g] = xs[u][g] < 0.0f ? -1.0f : 1.0f;
         }
     }
@@ -700,15 +723,41 @@ __global__ void __launch_bounds__(RT) k_csr_residentf(
             for (int c = 0; c < CACHE; ++c)
 #pragma unroll
                 for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(cw[u][c], sv[c][g], acc[g]);
-            if (rest)
-                for (int32_t k = crest[u]; k < cend[u]; ++k) {
-                    const int32_t j = col[k];
-                    if (skip_diag && j == i) continue;
-                    float s[G];
-                    resf_read<G>(now + j * G, s);
+            if (rest) {
+                if constexpr (VPT == 1 && G <= 4) {
+                    // four entries' reads together, as in the byte form; one past the row or on
+                    // the diagonal has weight 0, which changes no sum
+                    for (int32_t k = crest[u]; k < cend[u]; k += 4) {
+                        int32_t j[4];
+                        float wk[4], s[4][G];
 #pragma unroll
-                    for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(wf[k], s[g], acc[g]);
+                        for (int d = 0; d < 4; ++d) {
+                            const int32_t kk = min(k + d, cend[u] - 1);
+                            j[d] = col[kk];
+                            wk[d] = wf[kk];
+                        }
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            const bool out = (k + d >= cend[u]) | (skip_diag & (j[d] == i));
+                            wk[d] = __uint_as_float(__float_as_uint(wk[d]) & ((uint32_t)out - 1u));
+                            resf_read<G>(now + j[d] * G, s[d]);
+                        }
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)
+#pragma unroll
+                            for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(wk[d], s[d][g], acc[g]);
+                    }
+                } else {
+                    for (int32_t k = crest[u]; k < cend[u]; ++k) {
+                        const int32_t j = col[k];
+                        if (skip_diag && j == i) continue;
+                        float s[G];
+                        resf_read<G>(now + j * G, s);
+#pragma unroll
+                        for (int g = 0; g < G; ++g) acc[g] = __fmaf_rn(wf[k], s[g], acc[g]);
+                    }
                 }
+            }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const float h = __fadd_rn(acc[g], bi[u]);
