@@ -560,8 +560,10 @@ __global__ void __launch_bounds__(256) k_slot_init_batch(const SlotInitTask *__r
          k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r = k / t.np, i = k - r * t.np;
         const float xv = init_x(t.seed, sigma0, t.n, t.R, r, i);
-        t.x[k] = xv;
-        t.m[k] = 0.0f;
+        if (r < t.R) {               // (no step reads the padding's)
+            t.x[k] = xv;
+            t.m[k] = 0.0f;
+        }
         t.s8[(i / MF_NPAD) * t.Rp * MF_NPAD + r * MF_NPAD + i % MF_NPAD] =
             xv < 0.0f ? (uint8_t)0xFF : (uint8_t)0x01;
         if (r == 0) t.bfp[i] = i < t.n ? t.bf[i] : 0.0f;

@@ -113,8 +113,8 @@ struct Plan {
     size_t o_sc, o_cpart, o_lam, o_bf, o_bi, o_bd, o_rabs, o_rmax, o_rk, o_Jf, o_Jb, o_x, o_m, o_h,
         o_s0, o_s1, o_part, o_ei, o_ed, o_sp, o_best, o_words, o_boff, o_bcur, o_btsum,
         o_bsrc, o_bdrec, o_bbits, o_bcrow, total;
-    size_t keep;          // without state buffers: bytes before the scratch that a caller's own
-                          // buffers may share (below)
+    size_t keep;          // without state buffers, and for a batch: bytes before those that a
+                          // caller's own buffers may share (below)
 };
 
 // The canonicalisation's row sums at byte `off`; returns their end.  They are dead once its
@@ -225,6 +225,18 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
         pl.total = std::max(off, rows);
         return pl;
     }
+    // a batch instance that runs as tiles scores from buffers in the place of its state
+    auto take_scores = [&]() {
+        pl.o_part = take(sizeof(double) * (size_t)pl.eblk * R);
+        pl.o_ei = take(sizeof(int64_t) * R);
+        pl.o_ed = take(sizeof(double) * R);
+        pl.o_sp = take(sizeof(int8_t) * R * n);
+        pl.o_best = take(sizeof(int32_t) * 4);
+    };
+    if (batch_rp > 0) {
+        take_scores();
+        pl.keep = off;
+    }
     size_t rows = 0;
     if (p.format == QPA_FMT_DENSE) {
         rows = align_up(place_row_sums(pl, off));
@@ -249,14 +261,14 @@ Plan make_plan(const qpa_problem &p, const qpa_params &a, int64_t batch_rp = 0, 
     }
     pl.o_s0 = sbytes ? take(sbytes) : 0;
     pl.o_s1 = sbytes ? take(sbytes) : 0;
+    if (batch_rp > 0) {              // (batches keep no fields)
+        pl.total = off;
+        return pl;
+    }
     // the last step's fields share their place with the scoring scratch: qpa_steps asks for
     // fields and does not score
     pl.o_h = off;
-    pl.o_part = take(sizeof(double) * (size_t)pl.eblk * R);
-    pl.o_ei = take(sizeof(int64_t) * R);
-    pl.o_ed = take(sizeof(double) * R);
-    pl.o_sp = take(sizeof(int8_t) * R * n);
-    pl.o_best = take(sizeof(int32_t) * 4);
+    take_scores();
     pl.o_words = p.format == QPA_FMT_DENSE
                      ? take(sizeof(uint64_t) * R * (size_t)((n + 63) / 64))
                      : energy_packs_spins(p, pl.R) ? take(n) : 0;
@@ -989,6 +1001,7 @@ static_assert(BATCH_MAX_N <= EBITS_MAX_N, "every densified batch instance fits t
 // Dense matrix-core buffers of a batch instance that may run as BF16 tiles.
 struct DenseSlot {
     bool cand = false;
+    bool small = false;      // in the place of the instance's sparse state; int8 tiles only
     int64_t np = 0, Rp = 0;
     size_t o_Jb = 0, o_bfp = 0, o_x = 0, o_m = 0, o_s0 = 0, o_s1 = 0;
 };
@@ -1042,7 +1055,9 @@ constexpr double SPARSE_ADDS_DEFAULT = 1.0e12, DENSE_BPS_DEFAULT = 3.0e12;
 // to 256.  The choice also sets the size of the workspace that a caller has to bring: an
 // instance that moves to tiles needs their padded buffers besides its sparse ones (n = 513
 // with 8 entries a row, 8 replicas: 2.1 MB against 0.5 MB), so only those move that are
-// cheaper there by this margin.
+// cheaper there by this margin -- and, of the integer ones that are cheaper at 128 only, those
+// whose tile buffers fit in the place of the sparse state (1200 instances of 110 variables,
+// 300 replicas, 60 steps: 58 ms against 82 on the sparse path).
 constexpr int64_t BATCH_PRICE_PAD = 256;
 static_assert(BATCH_PRICE_PAD % MF_BN8 == 0, "a price of whole tiles");
 double csr_step_work(int64_t nnz, int64_t R) { return (double)nnz * (double)R; }
@@ -1092,7 +1107,6 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
                         k, (long long)probs[k].n, (long long)BATCH_MAX_N);
         Plan pl = make_plan(probs[k], a, groups * 64);
         bp.base[k] = off;
-        off += align_up(pl.total);
         bp.inst[k] = pl;
         bp.ntasks += (int32_t)groups;
         bp.max_n = std::max<int32_t>(bp.max_n, (int32_t)probs[k].n);
@@ -1110,28 +1124,48 @@ qpa_status make_batch_plan(qpa_ctx *ctx, int32_t count, const qpa_problem *probs
         const bool cheaper =
             cheaper_at(np) && cheaper_at(round_up(probs[k].n, BATCH_PRICE_PAD));
         const int32_t force = a.flags & (QPA_BATCH_SPARSE | QPA_BATCH_DENSE);
-        if (exact_ok && force != QPA_BATCH_SPARSE && (cheaper || force == QPA_BATCH_DENSE)) {
-            ds.cand = true;
-            ds.np = np;
-            ds.Rp = Rp;
+        // the slot's buffers from byte `at` on; returns their end.  x and m hold `rows` replicas
+        auto place = [&](size_t at, int64_t rows, int64_t rpad) {
             auto tk = [&](size_t bytes) {
-                size_t o = off;
-                off += align_up(bytes);
+                size_t o = at;
+                at += align_up(bytes);
                 return o;
             };
+            ds.np = np;
+            ds.Rp = rpad;
             ds.o_Jb = tk(sizeof(uint16_t) * (size_t)(np * np));
             ds.o_bfp = tk(sizeof(float) * (size_t)np);
-            ds.o_x = tk(sizeof(float) * (size_t)(Rp * np));
-            ds.o_m = tk(sizeof(float) * (size_t)(Rp * np));
+            ds.o_x = tk(sizeof(float) * (size_t)(rows * np));
+            ds.o_m = tk(sizeof(float) * (size_t)(rows * np));
             // room for byte spins (int8 tiles), eight times the sign bits of BF16 tiles
-            ds.o_s0 = tk((size_t)(Rp * np));
-            ds.o_s1 = tk((size_t)(Rp * np));
-            const int32_t it = (int32_t)std::max(
-                (np / MF_BN) * (Rp / MF_BM),
-                (np / MF_BN8) * ((a.replicas + MF_BM8 - 1) / MF_BM8));
-            bp.ntiles_max += it;
-            bp.inst_tiles_max = std::max(bp.inst_tiles_max, it);
+            ds.o_s0 = tk((size_t)(rpad * np));
+            ds.o_s1 = tk((size_t)(rpad * np));
+            return at;
+        };
+        const int32_t it8 = (int32_t)((np / MF_BN8) * ((a.replicas + MF_BM8 - 1) / MF_BM8));
+        int32_t it = 0;
+        size_t end = off + pl.total;
+        if (exact_ok && force != QPA_BATCH_SPARSE && (cheaper || force == QPA_BATCH_DENSE)) {
+            ds.cand = true;
+            end = place(align_up(end), Rp, Rp);
+            it = std::max((int32_t)((np / MF_BN) * (Rp / MF_BM)), it8);
+        } else if (pl.is_int && force == 0 && cheaper_at(np)) {
+            // cheaper at 128 only: int8 tiles where they fit the place of the state (with the
+            // row sums and, as it has been asked for, a buffer of fields), which the
+            // instance then does not use, less the longer tile table
+            const size_t room = align_up(pl.total) - pl.keep +
+                                align_up(sizeof(float) * (size_t)(pl.Rp * pl.np));
+            const size_t table = align_up(sizeof(MfmaTile) * (size_t)(it8 * (1 + 3 * XCDS)));
+            const size_t last = place(off + pl.keep, a.replicas, groups * 64);
+            if (last - (off + pl.keep) + table <= room) {
+                ds.cand = ds.small = true;
+                end = std::max(end, last);
+                it = it8;
+            }
         }
+        off = align_up(end);
+        bp.ntiles_max += it;
+        bp.inst_tiles_max = std::max(bp.inst_tiles_max, it);
         bp.dense.push_back(ds);
     }
     auto take = [&](size_t bytes) {
@@ -2047,7 +2081,7 @@ qpa_status qpa_solve_batch(qpa_ctx *ctx, int32_t count, const qpa_problem *probl
     AuxGuard g1{ctx, st};
     s = aux_issue(ctx, count, "tile set-up", [&](int32_t k, hipStream_t ak) -> hipError_t {
         const DenseSlot &ds = bp.dense[k];
-        if (!ds.cand) return hipSuccess;
+        if (!ds.cand || (ds.small && !slot8[k])) return hipSuccess;
         if (bp.inst[k].is_int && hsc[k].max_abs > 256.0) return hipSuccess;
         const bool i8 = bp.inst[k].is_int && hsc[k].max_abs <= 127.0 &&
                         problems[k].coupling_dtype != QPA_F32;

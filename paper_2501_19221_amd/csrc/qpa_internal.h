@@ -256,7 +256,7 @@ struct SlotInitTask {
     const float *bf;             // canonical FP32 field (n)
     int8_t *J8;                  // np x np
     float *bfp;                  // np
-    float *x, *m;                // [Rp][np]
+    float *x, *m;                // [R][np]
     uint8_t *s8;                 // byte spins, Rp * np
     int64_t n, np, R, Rp;
     uint64_t seed;
